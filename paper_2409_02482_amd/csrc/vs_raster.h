@@ -34,7 +34,14 @@ constexpr int kRasterThreads = 256;
 // 8.78 ms; 40 rows (six blocks) 5.63 / 8.47 ms.
 __host__ __device__ constexpr int bin_rows(int B) { return B == 64 ? 56 : B; }
 constexpr int kSmallSpan = 16384;   // small-triangle path: bbox extents <= 64 px, so edge values fit int32
-constexpr int kSmallArea = 256;     // ... and at most this many candidate pixels in the tile
+// ... and at most this many candidate pixels in the tile.  A lane tests one candidate in about 50
+// cycles and draws one in about 350; the wavefront path spends about 350 instructions on a triangle
+// of a few 8 x 8 blocks.  Raster kernel at 256 / 512 / 1024 candidates: coarse shells (k = 7, 25,280
+// triangles a layer, 16 views at 1000^2) 0.84 / 0.71 / 0.66 ms, a 256^2 view of 1,292-triangle shells
+// 39 / 42 / 44 us, the metric scene 2.35 / 2.36 / 2.36 ms.
+constexpr int kSmallArea = 512;
+constexpr uint32_t kBigQueue = 192; // larger triangles of a bin that its block queues (31.2 KiB of LDS: still five blocks a CU)
+static_assert(kBigQueue <= (uint32_t)kRasterThreads, "one round deals the whole queue");
 
 // Fill n u64 words with a value (grid-stride).
 __global__ void __launch_bounds__(256) k_fill_u64(uint64_t* __restrict__ p, int64_t n, uint64_t val) {
@@ -479,11 +486,27 @@ __global__ void __launch_bounds__(256) k_tile_view_slot(const vs_view* __restric
   tile_view[g] = find_view_tile(views, n_views, g, slot);
 }
 
+__device__ inline int4 readlane4(int4 v, int lane) {
+  return make_int4(__builtin_amdgcn_readlane(v.x, lane), __builtin_amdgcn_readlane(v.y, lane),
+                   __builtin_amdgcn_readlane(v.z, lane), __builtin_amdgcn_readlane(v.w, lane));
+}
+
 // One block per bin.  Small triangles (bounding box <= 64 px on each side and
-// few candidate pixels) are walked by one lane with exact int32 edge values;
-// larger ones are tested by the lane's whole wavefront, each lane owning
-// B*bin_rows(B)/64 pixels, with exact FP64 edge values.  Wavefronts work independently
-// on the LDS tile (64-bit atomic minimum).
+// few candidate pixels) are walked with exact int32 edge values by one lane, or
+// by 2 to 16 lanes that take their rows in turn where the chunk of (at most
+// 256) triangles being drawn is smaller than the block: the walk is a serial
+// chain of LDS reads, FP64 depths and LDS minima, so idle lanes beside it are
+// time lost, while a repeated set-up costs little.  Larger triangles are queued
+// for the whole block, dealt round its wavefronts after the chunks, and drawn
+// one 8 x 8 pixel block of the tile at a time with exact FP64 edge values.
+// Wavefronts work independently on the LDS tile (64-bit atomic minimum).
+// Against one lane per triangle and larger ones tested over the whole tile by
+// the wavefront that met them: metric scene 3.11 -> 2.36 ms, k = 9 scene 2.95 ->
+// 2.87 ms, a single 1024^2 view 92 -> 70 us, coarse shells (k = 7, 25,280
+// triangles a layer, 16 views at 1000^2) 3.50 -> 0.71 ms, a 256^2 view of
+// 1,292-triangle shells 234 -> 42 us.  Sharing only chunks of at most 64 or 32
+// triangles: metric 2.75 and 3.07 ms; two or four lanes per triangle in full
+// chunks too: metric 2.39 and 2.58 ms, k = 9 scene 3.26 and 4.19 ms.
 //
 // The bin's list holds its front-facing triangles first.  They are drawn
 // first; then the tile's largest key per 8 x 8 sub-tile is taken, and a
@@ -511,7 +534,8 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
   __shared__ __align__(16) unsigned long long tile[B * BH];
   __shared__ unsigned long long smax[kNs * kNsY];
   __shared__ int32_t queue[2 * kRasterThreads];   // back-facing triangles that may lower a key
-  __shared__ uint32_t qn;
+  __shared__ int32_t bigs[kBigQueue];             // large triangles, left for the whole block
+  __shared__ uint32_t qn, bign;
   const int k = L.k;
   const int64_t n_bins = n_tiles * k;
   // XCD-contiguous remap of the block index
@@ -529,6 +553,7 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
   const int x0 = tx * B, y0 = ty * BH;
   const int x1 = min(x0 + B, W) - 1, y1 = min(y0 + BH, H) - 1;
   const int tid = threadIdx.x, lane = tid & 63;
+  if (tid == 0) qn = bign = 0;
   for (int p = tid; p < B * BH / 2; p += kRasterThreads)   // 16-byte stores
     reinterpret_cast<ulonglong2*>(tile)[p] = make_ulonglong2(kEmpty, kEmpty);
   const ProjVert* P = proj + (int64_t)v * vpv + L.vert_off[l];
@@ -543,10 +568,67 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
   const uint32_t n_front = (overflow || count_frags) ? n : min(cursor[2 * bid], cnt);
   unsigned long long frags = 0;
   __syncthreads();
-  // Draw triangle t of this layer (t < 0: nothing).  Called by every thread of the block in
-  // step (the wavefront path for large triangles loops over the wavefront's lanes).
-  auto draw = [&](int32_t tq) {
-    int32_t big = -1;   // a triangle for the whole wavefront
+  // Triangles drawn by the whole wavefront, one after the other: every lane's triangle (big < 0:
+  // none) is loaded at once, so that the wavefront waits for memory once, and handed round.  For
+  // each, the lanes first test one 8 x 8 pixel block each (an edge function is linear, so its
+  // largest value over a block sits at a corner), then the wavefront visits the surviving blocks,
+  // one pixel a lane.
+  auto draw_bigs = [&](int32_t big) {
+    TriLoad q;
+    q.a = q.b = q.c = make_int4(0, 0, 0, 0);
+    if (big >= 0) load_vertices<true>(load_ids(tri, (uint32_t)big), nvert, P, q);
+    for (uint64_t bm = __ballot(big >= 0); bm; bm &= bm - 1) {
+      const int from = (int)__builtin_ctzll(bm);
+      const int32_t t = __builtin_amdgcn_readlane(big, from);
+      TriLoad u;
+      u.a = readlane4(q.a, from); u.b = readlane4(q.b, from); u.c = readlane4(q.c, from);
+      u.id[0] = u.id[1] = u.id[2] = 0;
+      u.bad = false;
+      TriSetup T;
+      setup_loaded(u, T);   // a valid triangle: its first setup said so
+      const unsigned long long lbkey = depth_lower_key(T, (uint32_t)t);
+      const PixRange pr = pixel_range(T, W, H);
+      const int lx = lane & 7, ly = lane >> 3;
+      double E[3], ax[3], ay[3];   // edge values at this lane's pixel of the bin's first block; steps per pixel
+      edge_values(T, 256.0 * (x0 + lx) + 128.0, 256.0 * (y0 + ly) + 128.0, E);
+      ax[0] = (T.Y[1] - T.Y[2]) * 256.0; ay[0] = (T.X[2] - T.X[1]) * 256.0;
+      ax[1] = (T.Y[2] - T.Y[0]) * 256.0; ay[1] = (T.X[0] - T.X[2]) * 256.0;
+      ax[2] = (T.Y[0] - T.Y[1]) * 256.0; ay[2] = (T.X[1] - T.X[0]) * 256.0;
+      // this lane's block (lx, ly): its first pixel is 7 lx right of and 7 ly below this lane's own pixel
+      bool may = x0 + 8 * lx <= min(pr.i1, x1) && x0 + 8 * lx + 7 >= pr.i0 && y0 + 8 * ly <= min(pr.j1, y1) &&
+                 y0 + 8 * ly + 7 >= pr.j0 && lx < kNs && ly < kNsY;
+#pragma unroll
+      for (int e = 0; e < 3; ++e) {
+        const double at = E[e] + 7.0 * (lx * ax[e] + ly * ay[e]);
+        may = may && at + 7.0 * (fmax(ax[e], 0.0) + fmax(ay[e], 0.0)) >= T.th[e];
+      }
+      for (uint64_t m = __ballot(may); m; m &= m - 1) {
+        const int b = (int)__builtin_ctzll(m), bx = b & 7, by = b >> 3;
+        const double e0 = E[0] + 8.0 * (bx * ax[0] + by * ay[0]);
+        const double e1 = E[1] + 8.0 * (bx * ax[1] + by * ay[1]);
+        const double e2 = E[2] + 8.0 * (bx * ax[2] + by * ay[2]);
+        if (x0 + 8 * bx + lx > x1 || y0 + 8 * by + ly > y1) continue;
+        if (e0 >= T.th[0] && e1 >= T.th[1] && e2 >= T.th[2]) {
+          unsigned long long* slotp = &tile[(8 * by + ly) * B + 8 * bx + lx];
+          if (__hip_atomic_load(slotp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > lbkey)
+            atomicMin(slotp, (unsigned long long)depth_key(T, e0, e1, e2, (uint32_t)t));
+          ++frags;
+        }
+      }
+    }
+  };
+  // A triangle for the whole wavefront rather than one lane (its box clipped to the bin is i0..i1 x j0..j1).
+  auto is_big = [&](const TriSetup& T, int i0, int i1, int j0, int j1) {
+    const double spanx = fmax(T.X[0], fmax(T.X[1], T.X[2])) - fmin(T.X[0], fmin(T.X[1], T.X[2]));
+    const double spany = fmax(T.Y[0], fmax(T.Y[1], T.Y[2])) - fmin(T.Y[0], fmin(T.Y[1], T.Y[2]));
+    return !(spanx <= kSmallSpan && spany <= kSmallSpan && (i1 - i0 + 1) * (j1 - j0 + 1) <= kSmallArea);
+  };
+  // Lanes that share one triangle of a chunk of m, as a power of two: a chunk that leaves lanes idle
+  // gives each triangle several of them, which take its rows in turn.
+  auto share = [](uint32_t m) { return m > 128 ? 0 : m > 64 ? 1 : m > 32 ? 2 : m > 16 ? 3 : 4; };
+  // Draw every parts-th row from row part of triangle tq of this layer (tq < 0: nothing); large ones are
+  // queued for flush_bigs.
+  auto draw = [&](int32_t tq, int part, int parts) {
     TriSetup T;
     if (tq >= 0 && setup_triangle<true>(tri, (uint32_t)tq, nvert, P, T) == kTriOk) {
       const int32_t t = tq;
@@ -554,20 +636,17 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
       const int ci0 = max(pr.i0, x0), ci1 = min(pr.i1, x1), cj0 = max(pr.j0, y0), cj1 = min(pr.j1, y1);
       if (ci0 <= ci1 && cj0 <= cj1) {
         const unsigned long long lbkey = depth_lower_key(T, (uint32_t)t);
-        const double spanx = fmax(T.X[0], fmax(T.X[1], T.X[2])) - fmin(T.X[0], fmin(T.X[1], T.X[2]));
-        const double spany = fmax(T.Y[0], fmax(T.Y[1], T.Y[2])) - fmin(T.Y[0], fmin(T.Y[1], T.Y[2]));
-        const int area = (ci1 - ci0 + 1) * (cj1 - cj0 + 1);
-        if (spanx <= kSmallSpan && spany <= kSmallSpan && area <= kSmallArea) {
+        if (!is_big(T, ci0, ci1, cj0, cj1)) {
           // exact int32 edge walk: every edge value inside the bbox is below 2^30 in magnitude
           double E[3];
-          edge_values(T, 256.0 * ci0 + 128.0, 256.0 * cj0 + 128.0, E);
+          edge_values(T, 256.0 * ci0 + 128.0, 256.0 * (cj0 + part) + 128.0, E);
           int32_t er0 = (int32_t)E[0] - (int32_t)T.th[0];
           int32_t er1 = (int32_t)E[1] - (int32_t)T.th[1];
           int32_t er2 = (int32_t)E[2] - (int32_t)T.th[2];
           const int32_t ax0 = (int32_t)(-(T.Y[2] - T.Y[1]) * 256.0), ay0 = (int32_t)((T.X[2] - T.X[1]) * 256.0);
           const int32_t ax1 = (int32_t)(-(T.Y[0] - T.Y[2]) * 256.0), ay1 = (int32_t)((T.X[0] - T.X[2]) * 256.0);
           const int32_t ax2 = (int32_t)(-(T.Y[1] - T.Y[0]) * 256.0), ay2 = (int32_t)((T.X[1] - T.X[0]) * 256.0);
-          for (int j = cj0; j <= cj1; ++j) {
+          for (int j = cj0 + part; j <= cj1; j += parts) {
             int32_t e0 = er0, e1 = er1, e2 = er2;
             for (int i = ci0; i <= ci1; ++i) {
               if ((e0 | e1 | e2) >= 0) {
@@ -581,30 +660,41 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
               }
               e0 += ax0; e1 += ax1; e2 += ax2;
             }
-            er0 += ay0; er1 += ay1; er2 += ay2;
+            er0 += ay0 * parts; er1 += ay1 * parts; er2 += ay2 * parts;
           }
-        } else {
-          big = t;
+        } else if (part == 0) {
+          const uint32_t at = atomicAdd(&bign, 1u);
+          if (at < kBigQueue) bigs[at] = t;
         }
       }
     }
-    for (uint64_t bm = __ballot(big >= 0); bm; bm &= bm - 1) {
-      const int32_t t = __builtin_amdgcn_readlane(big, __builtin_ctzll(bm));
-      TriSetup Tb;
-      setup_triangle<true>(tri, (uint32_t)t, nvert, P, Tb);
-      const unsigned long long lbkey = depth_lower_key(Tb, (uint32_t)t);
-      for (int p = lane; p < B * BH; p += 64) {
-        const int i = x0 + (p % B), j = y0 + (p / B);
-        if (i > x1 || j > y1) continue;
-        double E[3];
-        edge_values(Tb, 256.0 * i + 128.0, 256.0 * j + 128.0, E);
-        if (E[0] >= Tb.th[0] && E[1] >= Tb.th[1] && E[2] >= Tb.th[2]) {
-          if (__hip_atomic_load(&tile[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > lbkey)
-            atomicMin(&tile[p], (unsigned long long)depth_key(Tb, E[0], E[1], E[2], (uint32_t)t));
-          ++frags;
+  };
+  // Draw the large triangles that draw() met among entries c0..c1, dealt round the wavefronts; if they
+  // were more than the queue holds, the entries are gone through again.  Called by the whole block.
+  auto flush_bigs = [&](uint32_t c0, uint32_t c1) {
+    __syncthreads();
+    const uint32_t nb = bign;
+    if (nb == 0) return;   // uniform
+    const uint32_t dealt = lane * (kRasterThreads / 64) + (tid >> 6);
+    if (nb <= kBigQueue) {
+      draw_bigs(dealt < nb ? bigs[dealt] : -1);
+    } else {
+      for (uint32_t c = c0; c < c1; c += kRasterThreads) {
+        int32_t t = -1;
+        if (c + dealt < c1) {
+          const int32_t tc = overflow ? (int32_t)(c + dealt) : lst[c + dealt];
+          TriSetup T;
+          if (setup_triangle<true>(tri, (uint32_t)tc, nvert, P, T) == kTriOk) {
+            const PixRange pr = pixel_range(T, W, H);
+            const int ci0 = max(pr.i0, x0), ci1 = min(pr.i1, x1), cj0 = max(pr.j0, y0), cj1 = min(pr.j1, y1);
+            if (ci0 <= ci1 && cj0 <= cj1 && is_big(T, ci0, ci1, cj0, cj1)) t = tc;
+          }
         }
+        draw_bigs(t);
       }
     }
+    __syncthreads();
+    if (tid == 0) bign = 0;
   };
   // The first two chunks of back-facing entries and their records are requested before the
   // front-facing phase, so that their latency hides behind it.
@@ -615,11 +705,12 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
   const uint4 pr1 = pt1 >= 0 ? srec4[pt1] : make_uint4(0u, 0u, 0u, 0u);
   // phase 1: front-facing entries (every entry of an overflowing bin, or with fragment counting)
   for (uint32_t c0 = 0; c0 < n_front; c0 += kRasterThreads) {
-    const uint32_t c = c0 + tid;
-    draw(c < n_front ? (overflow ? (int32_t)c : lst[c]) : -1);
+    const int sh = share(n_front - c0);
+    const uint32_t c = c0 + (tid >> sh);
+    draw(c < n_front ? (overflow ? (int32_t)c : lst[c]) : -1, tid & ((1 << sh) - 1), 1 << sh);
   }
+  flush_bigs(0, n_front);
   if (n_front < n) {   // uniform: back-facing entries follow
-    if (tid == 0) qn = 0;
     __syncthreads();
     {
       // sub-tile maxima without LDS atomics: the kThr consecutive lanes of a sub-tile
@@ -676,7 +767,8 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
       uint32_t q = qn;
       const bool last = c0 + kRasterThreads >= n;
       while (q >= kRasterThreads || (last && q > 0)) {   // uniform
-        draw(tid < (int)q ? queue[tid] : -1);
+        const int sh = share(q), e = tid >> sh;
+        draw(e < (int)q ? queue[e] : -1, tid & ((1 << sh) - 1), 1 << sh);
         const uint32_t rest = q > kRasterThreads ? q - kRasterThreads : 0;
         const int32_t moved = tid < (int)rest ? queue[kRasterThreads + tid] : 0;
         __syncthreads();
@@ -686,6 +778,7 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
         q = rest;
       }
     }
+    flush_bigs(n_front, n);
   }
   __syncthreads();
   // coalesced store of the finished tile: pairs of keys as 16-byte stores when

@@ -1,0 +1,54 @@
+"""GPU raster at the edges of its triangle paths: chunk sizes at which a triangle's lanes change, boxes next to the
+one-lane limit, large triangles, and more of them in one bin than its queue holds.  Visibility bit-exact against the
+oracle, fragment counts equal."""
+import numpy as np
+import pytest
+
+import oracle as O
+import scenes as S
+from vs_testlib import assert_vis_equal, gpu_render, say, vis_numpy
+
+pytestmark = pytest.mark.gpu
+
+
+def _soup(seed, n, boxes, size):
+    """n triangles of both windings at random depths whose screen boxes are about the given pixel sizes."""
+    rng = np.random.default_rng([91, seed, n])
+    w, h = size
+    cam = S.make_camera(w, h, (0.0, 0.0, 3.0))
+    box = np.asarray(boxes, float)[rng.integers(0, len(boxes), n)]
+    at = rng.uniform([0.0, 0.0], [max(w - 1, 1), max(h - 1, 1)], (n, 2)) - box * rng.uniform(0.2, 0.8, (n, 1))
+    corner = rng.uniform(0.0, 1.0, (n, 3, 2))
+    corner[:, 0, 0], corner[:, 1, 1], corner[:, 2] = 0.0, 0.0, 1.0   # the box's extents are met
+    flip = rng.random(n) < 0.5
+    corner[flip] = corner[flip][:, [0, 2, 1]]
+    px = at[:, None, :] + corner * box[:, None, :]
+    z = rng.uniform(1.0, 4.0, (n, 1)) * rng.uniform(0.9, 1.1, (n, 3))
+    p = np.stack([(px[..., 0] - cam.cx) / cam.fx * z, (px[..., 1] - cam.cy) / cam.fy * z, z], -1)
+    xyz = (p.reshape(-1, 3) - cam.t) @ cam.R   # R^T (p - t)
+    uv = rng.uniform(0.0, 1.0, (3 * n, 2))
+    mesh = S.Mesh(xyz.astype(np.float32), uv.astype(np.float32), np.arange(3 * n, dtype=np.int32).reshape(n, 3))
+    tex = [S.uniform_texture(91, 0, 8, 8, opaque=True)]
+    return S.Scene(f"soup{n}", [mesh], tex, [cam])
+
+
+SMALL, EDGE, LARGE = [(3, 3), (9, 5)], [(22, 22), (32, 15), (26, 18), (63, 7), (64, 8)], [(66, 10), (40, 40), (200, 150)]
+
+
+@pytest.mark.parametrize("bin", [8, 16, 32, 64])
+@pytest.mark.parametrize("n,boxes,size", [
+    (1, EDGE, (64, 56)), (16, EDGE, (64, 56)), (17, EDGE, (64, 56)), (33, EDGE, (61, 53)), (65, SMALL, (64, 56)),
+    (128, SMALL, (64, 56)), (129, EDGE, (64, 56)), (256, SMALL, (64, 56)), (300, SMALL + EDGE, (64, 56)),
+    (5, LARGE, (201, 133)), (192, LARGE, (64, 56)), (500, LARGE, (64, 56)), (700, SMALL + EDGE + LARGE, (201, 133))])
+def test_triangle_paths(bin, n, boxes, size):
+    import torch
+    assert torch.cuda.is_available()
+    sc = _soup(len(boxes), n, boxes, size)
+    want, ref = O.raster(sc.layers[0], sc.cameras[0])
+    assert (want != np.uint64(0xFFFFFFFFFFFFFFFF)).any()
+    for count in (False, True):
+        say(f"[gpu] soup n={n} {size} bin {bin} count {count}")
+        P, layers, views, vis, ws, _, _ = gpu_render(sc, bin=bin, count_fragments=count)
+        assert_vis_equal(vis_numpy(views, vis, 1, 0)[0][None], want[None], f"n={n} bin {bin}")
+        if count:
+            assert P.read_status(ws)["fragments"] == ref["fragments"]
