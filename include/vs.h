@@ -418,7 +418,7 @@ size_t vs_ngp_workspace_bytes(const vs_ngp_config* cfg, int32_t k, const int32_t
  * params[l] at every texel centre.  params, tex: host arrays [k] of device
  * pointers (16-byte aligned); width, height: host arrays [k], 1..VS_MAX_TEX_DIM.
  * ws (device, vs_ngp_workspace_bytes, 256-byte aligned) may be NULL; when
- * given, the network's per-texel activations are kept there for
+ * given, the network's per-texel inputs are kept there for
  * vs_ngp_backward. */
 vs_status vs_ngp_bake(const float* const* params, const vs_ngp_config* cfg, int32_t k, const int32_t* width,
                       const int32_t* height, float* const* tex, void* ws, size_t ws_bytes, void* stream);

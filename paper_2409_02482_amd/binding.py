@@ -408,7 +408,7 @@ def _sizes(textures_hw):
 
 def ngp_bake(params, cfg: NgpConfig, sizes, tex=None, ws: Optional[torch.Tensor] = None, stream=None):
     """vs_ngp_bake: RGBA textures [H, W, 4] of the neural textures params[l] at sizes[l] = (W, H);
-    with ws (ngp_workspace) the activations are kept for ngp_backward."""
+    with ws (ngp_workspace) the network's inputs are kept for ngp_backward."""
     k = len(params)
     _count(sizes, k, "sizes")
     for l, p in enumerate(params):

@@ -820,22 +820,29 @@ vs_status ngp_table(const char* who, const float* const* params, int32_t k, cons
   return VS_OK;
 }
 
+// About `blocks` blocks shared out over the layers by their tiles, at least one and at most a tile's worth each.
+vs::NgpBlocks ngp_blocks(const vs::NgpTable& T, int64_t blocks) {
+  vs::NgpBlocks Q;
+  std::memset(&Q, 0, sizeof(Q));
+  for (int l = 0; l < T.k; ++l) {
+    const int64_t tiles = T.block_off[l + 1] - T.block_off[l];
+    Q.off[l + 1] = Q.off[l] + (int32_t)std::min(tiles, std::max<int64_t>(1, blocks * tiles / T.block_off[T.k]));
+  }
+  return Q;
+}
+
 struct NgpWs {
-  size_t a1, a2, a3, d1, d2, d0, total;
+  size_t a1, de, total;
 };
 
 // rows: 256 per texel tile of every layer
 NgpWs ngp_ws(const vs::NgpShape& S, int64_t rows) {
   NgpWs w;
-  size_t off = 0;
-  auto take = [&](size_t bytes) { const size_t o = off; off += (bytes + 255) / 256 * 256; return o; };
-  w.a1 = take((size_t)rows * 2 * S.levels * 4);
-  w.a2 = take((size_t)rows * vs::kNgpHidden * 4);
-  w.a3 = take((size_t)rows * vs::kNgpHidden * 4);
-  w.d1 = take((size_t)rows * vs::kNgpHidden * 4);
-  w.d2 = take((size_t)rows * vs::kNgpHidden * 4);
-  w.d0 = take((size_t)rows * vs::kNgpOut * 4);
-  w.total = off;
+  const size_t bytes = ((size_t)rows * 2 * S.levels * 4 + 255) / 256 * 256;
+  w.a1 = 0;
+  w.de = bytes;
+  // 2 L + 4 x 64 + 4 floats a row, which the ABI has asked for from the start; only 4 L of them are used
+  w.total = std::max(2 * bytes, bytes + ((size_t)rows * (4 * vs::kNgpHidden + vs::kNgpOut) * 4 + 255) / 256 * 256);
   return w;
 }
 
@@ -867,11 +874,7 @@ vs::NgpStage ngp_stage(void* ws, const NgpWs& w, int64_t rows) {
   vs::NgpStage G;
   G.R = rows;
   G.a1 = (float*)(base + w.a1);
-  G.a2 = (float*)(base + w.a2);
-  G.a3 = (float*)(base + w.a3);
-  G.d1 = (float*)(base + w.d1);
-  G.d2 = (float*)(base + w.d2);
-  G.d0 = (float*)(base + w.d0);
+  G.de = (float*)(base + w.de);
   return G;
 }
 
@@ -897,8 +900,8 @@ extern "C" vs_status vs_ngp_bake(const float* const* params, const vs_ngp_config
     G = ngp_stage(ws, w, rows);
   }
   hipStream_t s = (hipStream_t)stream;
-  const unsigned grid = (unsigned)T.block_off[k];
-  auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, T, S, G); };
+  const vs::NgpBlocks Q = ngp_blocks(T, 512);   // as many blocks as the CUs hold at once: two each
+  auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)Q.off[k]), dim3(256), 0, s, T, S, G, Q); };
   if (S.levels <= 8) {
     if (ws) launch(vs::k_ngp_bake<8, true>); else launch(vs::k_ngp_bake<8, false>);
   } else {
@@ -935,34 +938,16 @@ extern "C" vs_status vs_ngp_backward(const float* const* params, const vs_ngp_co
   const vs::NgpStage G = ngp_stage(ws, w, R);
   hipStream_t s = (hipStream_t)stream;
   const unsigned grid = (unsigned)T.block_off[k];
-  hipLaunchKernelGGL(vs::k_ngp_texel_bwd1, dim3(grid), dim3(256), 0, s, T, S, G);
-  if (S.levels <= 8) hipLaunchKernelGGL(vs::k_ngp_texel_bwd2<8>, dim3(grid), dim3(256), 0, s, T, S, G);
-  else hipLaunchKernelGGL(vs::k_ngp_texel_bwd2<16>, dim3(grid), dim3(256), 0, s, T, S, G);
-  if ((st = check_launch("vs_ngp_backward"))) return st;
-  // weight products: per layer dW1, db1 from (D1, e), dW2, db2 from (D2, h1), dW3, db3 from (D0, h2)
-  vs::NgpGemm Q;
-  std::memset(&Q, 0, sizeof(Q));
-  const int nin = 2 * S.levels;
-  int64_t max_rows = 0;
-  for (int l = 0; l < k; ++l) {
-    const int64_t r0 = T.block_off[l] * 256, rows = (T.block_off[l + 1] - T.block_off[l]) * 256;
-    max_rows = std::max(max_rows, rows);
-    float* gp = grad_params[l];
-    const int g0 = 3 * l;
-    Q.D[g0] = G.d1 + r0; Q.A[g0] = G.a1 + r0; Q.gw[g0] = gp + S.o_w1; Q.gb[g0] = gp + S.o_b1;
-    Q.M[g0] = vs::kNgpHidden; Q.K[g0] = nin;
-    Q.D[g0 + 1] = G.d2 + r0; Q.A[g0 + 1] = G.a2 + r0; Q.gw[g0 + 1] = gp + S.o_w2; Q.gb[g0 + 1] = gp + S.o_b2;
-    Q.M[g0 + 1] = vs::kNgpHidden; Q.K[g0 + 1] = vs::kNgpHidden;
-    Q.D[g0 + 2] = G.d0 + r0; Q.A[g0 + 2] = G.a3 + r0; Q.gw[g0 + 2] = gp + S.o_w3; Q.gb[g0 + 2] = gp + S.o_b3;
-    Q.M[g0 + 2] = vs::kNgpOut; Q.K[g0 + 2] = vs::kNgpHidden;
-    for (int q = 0; q < 3; ++q) Q.rows[g0 + q] = rows;
+  // as many blocks as the CUs hold at once: two each up to 8 levels, one beyond
+  const vs::NgpBlocks Q = ngp_blocks(T, S.levels <= 8 ? 512 : 256);
+  if (S.levels <= 8) {
+    hipLaunchKernelGGL(vs::k_ngp_backward<8>, dim3((unsigned)Q.off[k]), dim3(256), 0, s, T, S, G, Q);
+    hipLaunchKernelGGL(vs::k_ngp_scatter<8>, dim3(grid), dim3(256), 0, s, T, S, G);
+  } else {
+    hipLaunchKernelGGL(vs::k_ngp_backward<16>, dim3((unsigned)Q.off[k]), dim3(256), 0, s, T, S, G, Q);
+    hipLaunchKernelGGL(vs::k_ngp_scatter<16>, dim3(grid), dim3(256), 0, s, T, S, G);
   }
-  Q.R = R;
-  Q.n_gemm = 3 * k;
-  // enough blocks to fill the chip, each with at least a few 64-row tiles
-  Q.blocks_per_gemm = (int32_t)std::max<int64_t>(1, std::min<int64_t>(256, max_rows / 512));
-  hipLaunchKernelGGL(vs::k_ngp_wgrad, dim3((unsigned)(Q.n_gemm * Q.blocks_per_gemm)), dim3(256), 0, s, Q);
-  if ((st = check_launch("vs_ngp_backward (weights)"))) return st;
+  if ((st = check_launch("vs_ngp_backward"))) return st;
   return ok();
 }
 

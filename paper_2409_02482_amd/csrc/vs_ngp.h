@@ -10,11 +10,9 @@
 //   z2 = W2 h1 + b2, h2 = relu(z2) (64), o = W3 h2 + b3 (4), texel = sigmoid(o).
 // Parameters per layer, flat f32:
 //   tables [L][T][2] | W1 [64][2L] | b1 [64] | W2 [64][64] | b2 [64] | W3 [4][64] | b3 [4].
-// The per-texel products run on the matrix cores (see k_ngp_bake).  The
-// backward pass (two per-texel kernels, to keep each one's registers, and so
-// its occupancy, moderate) writes the layer inputs and the deltas of every
-// texel to a workspace; the weight gradients are then tall-skinny products
-// over texels (k_ngp_wgrad).
+// All products run on the matrix cores (see k_ngp_bake and k_ngp_backward);
+// the backward evaluates the layers again from the staged encodings, and a
+// second kernel scatters dL/de into the tables (k_ngp_scatter).
 #pragma once
 
 #include "vs_common.h"
@@ -26,7 +24,7 @@ constexpr int kNgpOut = 4;
 constexpr int kNgpMaxLevels = 16;
 constexpr uint32_t kNgpPrimeY = 2654435761u;
 constexpr int kNgpTile = 16;   // texels per tile side; a block of 256 threads covers one tile
-constexpr int kNgpSlots = 400; // LDS vertex sums per level in the table scatter (a 20 x 20 window)
+constexpr int kNgpSlots = 576; // vertices of a level's LDS window in the table scatter (24 x 24)
 
 struct NgpShape {
   int32_t levels, log2_table;
@@ -48,16 +46,11 @@ struct NgpTable {
 };
 
 // Staging for the backward, feature-major [feature][R] over R = 256 * tiles
-// rows (every access of a wavefront, and every GEMM tile load, is then
-// consecutive): A1 = e, A2 = h1, A3 = h2, D1, D2, DO.  Rows of texels outside
-// the texture hold zeros.
+// rows (every access of a wavefront is then consecutive).  Rows of texels
+// outside the texture hold zeros.
 struct NgpStage {
-  float* a1;   // [2L][R]
-  float* a2;   // [64][R]
-  float* a3;   // [64][R]
-  float* d1;   // [64][R]
-  float* d2;   // [64][R]
-  float* d0;   // [4][R]
+  float* a1;   // [2L][R] encodings e, from the bake
+  float* de;   // [2L][R] dL/de, between the backward's two kernels
   int64_t R;
 };
 
@@ -65,36 +58,9 @@ __device__ inline uint32_t ngp_index(uint32_t x, uint32_t y, int32_t N, int32_t 
   return dense ? y * (uint32_t)(N + 1) + x : ((x ^ (y * kNgpPrimeY)) & mask);
 }
 
-struct NgpTexel {
-  int l;
-  int32_t i, j;
-  bool valid;
-  int64_t t;     // texel index within the layer, j W + i
-  int64_t row;   // staging row
-};
-
-__device__ inline NgpTexel ngp_texel(const NgpTable& T) {
-  NgpTexel r;
-  const int64_t b = blockIdx.x;
-  int l = 0;
-  while (l + 1 < T.k && T.block_off[l + 1] <= b) ++l;
-  r.l = l;
-  const int W = T.w[l], H = T.h[l];
-  const int tiles_x = (W + kNgpTile - 1) / kNgpTile;
-  const int64_t tb = b - T.block_off[l];
-  const int ty = (int)(tb / tiles_x), tx = (int)(tb - (int64_t)ty * tiles_x);
-  r.i = tx * kNgpTile + (threadIdx.x & 15);
-  r.j = ty * kNgpTile + (threadIdx.x >> 4);
-  r.valid = r.i < W && r.j < H;
-  r.t = (int64_t)r.j * W + r.i;
-  r.row = b * 256 + threadIdx.x;
-  return r;
-}
-
-// Encoding of one texel centre; also the per-level corner indices and weights.
+// Encoding of one texel centre.
 template <int LMAX>
-__device__ inline void ngp_encode(const float* __restrict__ tables, const NgpShape& S, double u, double v, float (&e)[2 * LMAX],
-                                  uint32_t (&idx)[LMAX][4], float (&wt)[LMAX][4]) {
+__device__ inline void ngp_encode(const float* __restrict__ tables, const NgpShape& S, double u, double v, float (&e)[2 * LMAX]) {
   const uint32_t T = 1u << S.log2_table, mask = T - 1u;
 #pragma unroll
   for (int lv = 0; lv < LMAX; ++lv) {
@@ -115,16 +81,26 @@ __device__ inline void ngp_encode(const float* __restrict__ tables, const NgpSha
       const float2 f = tab[q];
       e[2 * lv] += w * f.x;
       e[2 * lv + 1] += w * f.y;
-      idx[lv][c] = q;
-      wt[lv][c] = w;
     }
   }
+}
+
+// Orders this wavefront's LDS accesses (a wavefront's LDS instructions execute in order).
+__device__ inline void ngp_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ inline float ngp_sigmoid(float x) { return 1.0f / (1.0f + expf(-x)); }
 
 // texture = sigmoid(MLP(encoding)) at every texel centre of every layer; with
-// STAGE the layer inputs e, h1 and h2 are kept for the backward.
+// STAGE the encodings e are kept for the backward, which evaluates the layers
+// again.  Seven 1024^2 textures of 8 levels: 1.08 ms, of which the matrix cores
+// need 0.57 (459k texel rows of 96 MFMAs at 32 cycles) and the encodings alone
+// take 0.24; 2.03 ms with h1 and h2 staged as well (0.5 KB per texel) and the
+// weights laid out by every tile's block.  One, two or four texel rows per weight
+// fragment: 1.11, 1.11 and 1.08 ms; three blocks a CU spill (1.06 - 1.36 ms).
 //
 // The three layers are dense products over the block's 256 texels and run on
 // the matrix cores (v_mfma_f32_16x16x4_f32, FP32 in and out) in transposed
@@ -136,17 +112,27 @@ __device__ inline float ngp_sigmoid(float x) { return 1.0f / (1.0f + expf(-x)); 
 // back as the next B operand, with the K index permuted to 4 (l / 16) + r; the
 // weights (A operands) are laid out in LDS in that permuted order, one 64-lane
 // fragment per MFMA.  Encodings go through LDS to become layer 1's B operand.
+// Blocks of the bake and the backward: layer l's tiles are shared by blocks off[l] .. off[l + 1] - 1, each of
+// which takes a contiguous run of them, so that a block lays out its layer's weights once.
+struct NgpBlocks {
+  int32_t off[kMaxLayers + 1];
+};
+
 typedef float ngp_f4 __attribute__((ext_vector_type(4)));
 
 template <int LMAX, bool STAGE>
-__global__ void __launch_bounds__(256) k_ngp_bake(NgpTable T, NgpShape S, NgpStage G) {
+__global__ void __launch_bounds__(256, 2) k_ngp_bake(NgpTable T, NgpShape S, NgpStage G, NgpBlocks Q) {
   constexpr int KIN = 2 * LMAX, KS1 = KIN / 4, EST = KIN + 1;
+  constexpr int NT = 4;                   // a wavefront's texel rows (N tiles), taken together
   __shared__ float w1f[4 * KS1 * 64];     // [mt][ks][lane]: W1[16 mt + lane % 16][4 ks + lane / 16]
   __shared__ float w2f[64 * 64];          // [mt][it][r][lane]: W2[16 mt + lane % 16][16 it + 4 (lane / 16) + r]
   __shared__ float w3f[16 * 64];          // [it][r][lane]: W3[lane % 16][16 it + 4 (lane / 16) + r] (rows >= 4: 0)
   __shared__ float es[4][64 * EST];       // per wave: the encodings of its 64 texels
-  const NgpTexel x = ngp_texel(T);
-  const int l = x.l, tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+  int l = 0;
+  while (l + 1 < T.k && Q.off[l + 1] <= (int)blockIdx.x) ++l;
+  const int part = (int)blockIdx.x - Q.off[l], parts = Q.off[l + 1] - Q.off[l];
+  const int64_t tiles = T.block_off[l + 1] - T.block_off[l];
   const float* P = T.params[l];
   const int nin = 2 * S.levels;
   for (int f = tid; f < 4 * KS1 * 64; f += 256) {
@@ -162,369 +148,491 @@ __global__ void __launch_bounds__(256) k_ngp_bake(NgpTable T, NgpShape S, NgpSta
     const int ln = f & 63, fr = f >> 6, it = fr >> 2, r = fr & 3, m = ln & 15;
     w3f[f] = m < kNgpOut ? P[S.o_w3 + m * kNgpHidden + 16 * it + 4 * (ln >> 4) + r] : 0.f;
   }
-  // this thread's encoding (zeros outside the texture)
-  float e[KIN];
-  uint32_t idx[LMAX][4];
-  float wt[LMAX][4];
-#pragma unroll
-  for (int q = 0; q < KIN; ++q) e[q] = 0.f;
-  if (x.valid) {
-    const double u = ((double)x.i + 0.5) / (double)T.w[l], v = ((double)x.j + 0.5) / (double)T.h[l];
-    ngp_encode<LMAX>(P, S, u, v, e, idx, wt);
-  }
-  float* ew = es[wv];
-#pragma unroll
-  for (int q = 0; q < KIN; ++q) ew[lane * EST + q] = e[q];
-  if (STAGE) {
-    const uint32_t row = (uint32_t)x.row, R = (uint32_t)G.R;
-#pragma unroll
-    for (int q = 0; q < KIN; ++q)
-      if (q < nin) G.a1[q * R + row] = e[q];
-  }
   __syncthreads();
-
   const int g = lane >> 4, n = lane & 15;
-  const float* b1 = P + S.o_b1;
-  const float* b2 = P + S.o_b2;
-  const float* b3 = P + S.o_b3;
-  const int W = T.w[l], H = T.h[l];
+  ngp_f4 b1[4], b2[4], b3;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      b1[mt][r] = P[S.o_b1 + 16 * mt + 4 * g + r];
+      b2[mt][r] = P[S.o_b2 + 16 * mt + 4 * g + r];
+    }
+    b3[r] = g == 0 ? P[S.o_b3 + r] : 0.f;
+  }
+  const int W = T.w[l], H = T.h[l], tiles_x = (W + kNgpTile - 1) / kNgpTile;
+  float* ew = es[wv];
+  const int64_t t0 = tiles * part / parts, t1 = tiles * (part + 1) / parts;
 #pragma unroll 1
-  for (int it_n = 0; it_n < 4; ++it_n) {
-    // N tile: texels 16 it_n + n of this wave = texel row 4 wv + it_n of the tile
-    const int nb = 64 * wv + 16 * it_n + n;
-    const int ti = x.i - (tid & 15) + (nb & 15), tj = x.j - (tid >> 4) + (nb >> 4);
-    const bool valid = ti < W && tj < H;
-    ngp_f4 h[4];
+  for (int64_t tile = t0; tile < t1; ++tile) {
+    const int ty = (int)(tile / tiles_x), tx = (int)(tile - (int64_t)ty * tiles_x);
+    const int i = tx * kNgpTile + n, j = ty * kNgpTile + (tid >> 4);
+    // this thread's encoding (zeros outside the texture)
+    float e[KIN];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) h[mt][r] = b1[16 * mt + 4 * g + r];
-#pragma unroll
-    for (int ks = 0; ks < KS1; ++ks) {
-      const float bop = ew[(16 * it_n + n) * EST + 4 * ks + g];
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-        h[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w1f[(mt * KS1 + ks) * 64 + lane], bop, h[mt], 0, 0, 0);
+    for (int q = 0; q < KIN; ++q) e[q] = 0.f;
+    if (i < W && j < H) {
+      const double u = ((double)i + 0.5) / (double)W, v = ((double)j + 0.5) / (double)H;
+      ngp_encode<LMAX>(P, S, u, v, e);
     }
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) h[mt][r] = fmaxf(h[mt][r], 0.f);
-    ngp_f4 z[4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) z[mt][r] = b2[16 * mt + 4 * g + r];
-#pragma unroll
-    for (int it = 0; it < 4; ++it)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-          z[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2f[((mt * 4 + it) * 4 + r) * 64 + lane], h[it][r], z[mt], 0, 0,
-                                                       0);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) z[mt][r] = fmaxf(z[mt][r], 0.f);
-    ngp_f4 o;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) o[r] = g == 0 ? b3[r] : 0.f;
-#pragma unroll
-    for (int it = 0; it < 4; ++it)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        o = __builtin_amdgcn_mfma_f32_16x16x4f32(w3f[(it * 4 + r) * 64 + lane], z[it][r], o, 0, 0, 0);
-    if (g == 0 && valid)
-      reinterpret_cast<float4*>(T.tex[l])[(int64_t)tj * W + ti] =
-          make_float4(ngp_sigmoid(o[0]), ngp_sigmoid(o[1]), ngp_sigmoid(o[2]), ngp_sigmoid(o[3]));
+    for (int q = 0; q < KIN; ++q) ew[lane * EST + q] = e[q];
     if (STAGE) {
       // 32-bit element offsets (the workspace holds < 2^31 floats per array)
-      const uint32_t row = (uint32_t)(blockIdx.x * 256 + nb), R = (uint32_t)G.R;
+      const uint32_t row = (uint32_t)((T.block_off[l] + tile) * 256 + tid), R = (uint32_t)G.R;
+#pragma unroll
+      for (int q = 0; q < KIN; ++q)
+        if (q < nin) G.a1[q * R + row] = e[q];
+    }
+    ngp_wave_sync();
+    // N tile c: texels 16 c + n of this wave = texel row 4 wv + c of the tile
+    ngp_f4 h[NT][4], z[NT][4], o[NT];
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        h[c][mt] = b1[mt];
+        z[c][mt] = b2[mt];
+      }
+      o[c] = b3;
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS1; ++ks) {
+      float bop[NT];
+#pragma unroll
+      for (int c = 0; c < NT; ++c) bop[c] = ew[(16 * c + n) * EST + 4 * ks + g];
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        const float aop = w1f[(mt * KS1 + ks) * 64 + lane];
+#pragma unroll
+        for (int c = 0; c < NT; ++c) h[c][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, bop[c], h[c][mt], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < NT; ++c)
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const uint32_t m = 16 * mt + 4 * g + r;
-          G.a2[m * R + row] = valid ? h[mt][r] : 0.f;
-          G.a3[m * R + row] = valid ? z[mt][r] : 0.f;
+        for (int r = 0; r < 4; ++r) h[c][mt][r] = fmaxf(h[c][mt][r], 0.f);
+#pragma unroll
+    for (int it = 0; it < 4; ++it)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+          const float aop = w2f[((mt * 4 + it) * 4 + r) * 64 + lane];
+#pragma unroll
+          for (int c = 0; c < NT; ++c)
+            z[c][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, h[c][it][r], z[c][mt], 0, 0, 0);
         }
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z[c][mt][r] = fmaxf(z[c][mt][r], 0.f);
     }
+#pragma unroll
+    for (int it = 0; it < 4; ++it)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float aop = w3f[(it * 4 + r) * 64 + lane];
+#pragma unroll
+        for (int c = 0; c < NT; ++c) o[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, z[c][it][r], o[c], 0, 0, 0);
+      }
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+      const int tj = ty * kNgpTile + 4 * wv + c;
+      if (g == 0 && i < W && tj < H)
+        reinterpret_cast<float4*>(T.tex[l])[(int64_t)tj * W + i] =
+            make_float4(ngp_sigmoid(o[c][0]), ngp_sigmoid(o[c][1]), ngp_sigmoid(o[c][2]), ngp_sigmoid(o[c][3]));
+    }
+    ngp_wave_sync();   // the encodings are written again for the next tile
   }
 }
 
-// Adds (v0, v1) into the feature pair q of a table for every active lane,
-// summing lanes that share q first when the level is coarse (many texels per
-// cell): one leader per distinct index and round, the others' values reduced
-// across the wavefront.
-__device__ inline void ngp_table_add(float* __restrict__ g, uint32_t q, float v0, float v1, bool active, bool merge) {
-  if (!merge) {
-    if (active) {
-      unsafeAtomicAdd(g + 2 * (int64_t)q, v0);
-      unsafeAtomicAdd(g + 2 * (int64_t)q + 1, v1);
-    }
-    return;
-  }
-  uint64_t pend = __ballot(active);
-  while (pend) {
-    const int leader = __builtin_ctzll(pend);
-    const uint32_t k0 = __builtin_amdgcn_readlane(q, leader);
-    const bool same = active && q == k0;
-    float s0 = same ? v0 : 0.0f, s1 = same ? v1 : 0.0f;
-    for (int off = 32; off > 0; off >>= 1) {
-      s0 += __shfl_xor(s0, off);
-      s1 += __shfl_xor(s1, off);
-    }
-    if ((int)__lane_id() == leader) {
-      unsafeAtomicAdd(g + 2 * (int64_t)k0, s0);
-      unsafeAtomicAdd(g + 2 * (int64_t)k0 + 1, s1);
-    }
-    pend &= ~__ballot(same);
-  }
-}
+// Backward of the network, for every layer, from dL/dtex of a texture baked with
+// the same parameters: weight and bias gradients, and dL/de (staged).
+//
+// Every product of one texel row (16 texels, the N tile) runs on the matrix
+// cores (v_mfma_f32_16x16x4_f32) as in the bake, one wavefront per row:
+//   forward again: h1 = relu(W1 e + b1), h2 = relu(W2 h1 + b2)
+//   d0 = dL/dtex t (1 - t) from the baked texel t
+//   d2 = (W3^T d0) [h2 > 0], d1 = (W2^T d2) [h1 > 0], de = W1^T d1
+//   dW3 += d0 h2^T, dW2 += d2 h1^T, dW1 += d1 e^T over the row's texels
+// An output D[4 (l / 16) + r][l % 16] is chained into the next product as its B
+// operand with the K index permuted (as in the bake); the weight gradients
+// contract over texels instead, so both factors pass through the wavefront's LDS
+// (row stride kNgpRow) and come back unit-per-lane.  260 MFMAs per row.  The
+// weight gradients stay in registers (96 accumulators per lane) over all the
+// tiles of a block, are summed over its wavefronts in LDS and added to the
+// gradient once per block; two blocks share a CU (LDS).  What bounds it is the
+// FP32 matrix rate: 459k rows of 260 MFMAs at 32 cycles are 1.6 ms of the 1,024
+// SIMDs at 2.4 GHz (seven 1024^2 textures).  It replaces a chain of kernels that
+// staged h1, h2, d1 and d2 (1.1 KB per texel written, 1.9 KB read) and formed the
+// weight gradients on the VALU: 11.4 ms -> 2.2 ms and 0.27 ms for the scatter below.
+constexpr int kNgpRow = 76;
 
-// Backward, first half, per texel (after a staging bake of the same
-// parameters): do = dL/dtex * t (1 - t) from the baked texel t, and
-// d2 = (W3^T do) [h2 > 0] (h2 > 0 exactly where z2 > 0); both staged.
-__global__ void __launch_bounds__(256) k_ngp_texel_bwd1(NgpTable T, NgpShape S, NgpStage G) {
-#pragma clang fp contract(fast)
-  const NgpTexel x = ngp_texel(T);
-  const int l = x.l;
-  const float* P = T.params[l];
-  const uint32_t r = (uint32_t)x.row, R = (uint32_t)G.R;
-  float d0[4] = {0.f, 0.f, 0.f, 0.f};
-  if (x.valid) {
-    const float4 g = reinterpret_cast<const float4*>(T.gtex[l])[x.t];
-    const float4 t = reinterpret_cast<const float4*>(T.tex[l])[x.t];
-    d0[0] = g.x * t.x * (1.0f - t.x); d0[1] = g.y * t.y * (1.0f - t.y);
-    d0[2] = g.z * t.z * (1.0f - t.z); d0[3] = g.w * t.w * (1.0f - t.w);
-  }
-  const float* W3 = P + S.o_w3;
-#pragma unroll
-  for (int j = 0; j < kNgpHidden; ++j) {
-    float acc = 0.f;
-#pragma unroll
-    for (int c = 0; c < kNgpOut; ++c) acc += W3[c * kNgpHidden + j] * d0[c];
-    G.d2[j * R + r] = G.a3[j * R + r] > 0.0f ? acc : 0.0f;
-  }
-#pragma unroll
-  for (int c = 0; c < kNgpOut; ++c) G.d0[c * R + r] = d0[c];
-}
-
-// Backward, second half, per texel: d1 = (W2^T d2) [h1 > 0] (staged), de = W1^T d1,
-// and de scattered into the hash tables through the encoding's corners and weights.
-// The two products run on the matrix cores as in the bake (transposed form,
-// 16 texels per N tile, d1 chained into the de product through a permuted K);
-// de goes through LDS back to its texel's thread for the scatter.
 template <int LMAX>
-__global__ void __launch_bounds__(256) k_ngp_texel_bwd2(NgpTable T, NgpShape S, NgpStage G) {
-  constexpr int KIN = 2 * LMAX, MT1 = (KIN + 15) / 16, DST = KIN + 1;
-  constexpr int W2N = 64 * 64, W1N = MT1 * 16 * 64, DEN = 256 * DST;
-  // one LDS buffer, two phases: the products' operands and de, then the per-level vertex sums
-  __shared__ float lds[W2N + W1N + DEN];
-  static_assert(LMAX * kNgpSlots * 2 <= W2N + W1N + DEN, "vertex sums must fit the product buffers");
-  float* w2t = lds;                      // [mt][ks][lane]: W2[4 ks + lane / 16][16 mt + lane % 16]
-  float* w1t = lds + W2N;                // [mt][it][r][lane]: W1[16 it + 4 (lane / 16) + r][16 mt + lane % 16]
-  float* des = lds + W2N + W1N;          // de per texel of the block
-  const NgpTexel x = ngp_texel(T);
-  const int l = x.l, tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, g = lane >> 4, n = lane & 15;
+__global__ void __launch_bounds__(256, LMAX <= 8 ? 2 : 1) k_ngp_backward(NgpTable T, NgpShape S, NgpStage G, NgpBlocks Q) {
+  constexpr int KIN = 2 * LMAX, KS1 = KIN / 4, MT1 = (KIN + 15) / 16;
+  constexpr int W1F = 4 * KS1 * 64, W2N = 64 * 64, W1T = MT1 * 16 * 64;
+  __shared__ float wts[W1F + 2 * W2N + W1T + 4 * 64];           // the weights' fragments, and at the end the block's sums
+  __shared__ __align__(16) float buf_all[4][2][16 * kNgpRow];   // per wavefront: two [texel][unit] factors
+  static_assert(64 * KIN + 64 + 64 * 64 + 64 + 4 * 64 + 4 <= W1F + 2 * W2N + W1T + 4 * 64, "the sums fit the weights' space");
+  float* w1f = wts;          // [mt][ks][lane]: W1[16 mt + lane % 16][4 ks + lane / 16]
+  float* w2f = w1f + W1F;    // [mt][it][r][lane]: W2[16 mt + lane % 16][16 it + 4 (lane / 16) + r]
+  float* w2t = w2f + W2N;    // [mt][it][r][lane]: W2[16 it + 4 (lane / 16) + r][16 mt + lane % 16]
+  float* w1t = w2t + W2N;    // [mt][it][r][lane]: W1[16 it + 4 (lane / 16) + r][16 mt + lane % 16]
+  float* w3t = w1t + W1T;    // [mt][lane]: W3[lane / 16][16 mt + lane % 16]
+  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, g = lane >> 4, n = lane & 15;
+  int l = 0;
+  while (l + 1 < T.k && Q.off[l + 1] <= (int)blockIdx.x) ++l;
+  const int part = (int)blockIdx.x - Q.off[l], parts = Q.off[l + 1] - Q.off[l];
+  const int64_t tiles = T.block_off[l + 1] - T.block_off[l];
+  const int W = T.w[l], H = T.h[l], tiles_x = (W + kNgpTile - 1) / kNgpTile;
   const float* P = T.params[l];
   const int nin = 2 * S.levels;
   const uint32_t R = (uint32_t)G.R;
+  for (int f = tid; f < 4 * KS1 * 64; f += 256) {
+    const int ln = f & 63, fr = f >> 6, mt = fr / KS1, ks = fr - mt * KS1;
+    const int m = 16 * mt + (ln & 15), kk = 4 * ks + (ln >> 4);
+    w1f[f] = kk < nin ? P[S.o_w1 + m * nin + kk] : 0.f;
+  }
   for (int f = tid; f < 64 * 64; f += 256) {
-    const int ln = f & 63, fr = f >> 6, mt = fr >> 4, ks = fr & 15;
-    w2t[f] = P[S.o_w2 + (4 * ks + (ln >> 4)) * kNgpHidden + 16 * mt + (ln & 15)];
+    const int ln = f & 63, fr = f >> 6, mt = fr >> 4, it = (fr >> 2) & 3, r = fr & 3;
+    const int a = 16 * mt + (ln & 15), b = 16 * it + 4 * (ln >> 4) + r;
+    w2f[f] = P[S.o_w2 + a * kNgpHidden + b];
+    w2t[f] = P[S.o_w2 + b * kNgpHidden + a];
   }
   for (int f = tid; f < MT1 * 16 * 64; f += 256) {
     const int ln = f & 63, fr = f >> 6, mt = fr >> 4, it = (fr >> 2) & 3, r = fr & 3;
     const int q = 16 * mt + (ln & 15), j = 16 * it + 4 * (ln >> 4) + r;
     w1t[f] = q < nin ? P[S.o_w1 + j * nin + q] : 0.f;
   }
+  for (int f = tid; f < 4 * 64; f += 256) w3t[f] = P[S.o_w3 + ((f >> 4) & 3) * kNgpHidden + 16 * (f >> 6) + (f & 15)];
   __syncthreads();
+  float* x0 = buf_all[wv][0];
+  float* x1 = buf_all[wv][1];
+  ngp_f4 b1[4], b2[4];
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      b1[mt][r] = P[S.o_b1 + 16 * mt + 4 * g + r];
+      b2[mt][r] = P[S.o_b2 + 16 * mt + 4 * g + r];
+    }
+  // accumulators: dW2[16 mt + 4 g + r][16 nt + n], dW1[16 mt + 4 g + r][16 nt + n], dW3[n][16 mt + 4 g + r] (n < 4),
+  // and per lane the sums of d2 and d1 (unit 16 mt + n) and d0 (output g) over its share of the texels
+  ngp_f4 c2[4][4], c1[4][MT1], c3[4];
+  float s2[4], s1[4], s0 = 0.f;
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b) c2[a][b] = ngp_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int b = 0; b < MT1; ++b) c1[a][b] = ngp_f4{0.f, 0.f, 0.f, 0.f};
+    c3[a] = ngp_f4{0.f, 0.f, 0.f, 0.f};
+    s2[a] = s1[a] = 0.f;
+  }
+  const int64_t t0 = tiles * part / parts, t1 = tiles * (part + 1) / parts;
 #pragma unroll 1
-  for (int it_n = 0; it_n < 4; ++it_n) {
-    const int nb = 64 * wv + 16 * it_n + n;
-    const uint32_t row = (uint32_t)(blockIdx.x * 256 + nb);
-    ngp_f4 d1[4];
+  for (int64_t row4 = 4 * t0; row4 < 4 * t1; ++row4) {   // this wavefront's texel rows: four of each tile
+    const int64_t tile = row4 >> 2;
+    const int rr = 4 * wv + (int)(row4 & 3);
+    const int ty = (int)(tile / tiles_x), tx = (int)(tile - (int64_t)ty * tiles_x);
+    const int ti = tx * kNgpTile + n, tj = ty * kNgpTile + rr;
+    const bool valid = ti < W && tj < H;
+    const uint32_t row = (uint32_t)((T.block_off[l] + tile) * 256 + 16 * rr + n);
+    float e[KS1];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) d1[mt] = ngp_f4{0.f, 0.f, 0.f, 0.f};
+    for (int ks = 0; ks < KS1; ++ks) e[ks] = 4 * ks + g < nin ? G.a1[(uint32_t)(4 * ks + g) * R + row] : 0.f;
+    float d0 = 0.f;
+    if (valid) {
+      const int64_t at = ((int64_t)tj * W + ti) * 4 + g;
+      const float t = T.tex[l][at];
+      d0 = T.gtex[l][at] * t * (1.0f - t);
+    }
+    s0 += d0;
+    // forward
+    ngp_f4 h1[4], h2[4];
 #pragma unroll
-    for (int ks = 0; ks < 16; ++ks) {
-      const float bop = G.d2[(4 * ks + g) * R + row];   // zero outside the texture
+    for (int mt = 0; mt < 4; ++mt) h1[mt] = b1[mt];
+#pragma unroll
+    for (int ks = 0; ks < KS1; ++ks)
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt)
-        d1[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2t[(mt * 16 + ks) * 64 + lane], bop, d1[mt], 0, 0, 0);
+        h1[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w1f[(mt * KS1 + ks) * 64 + lane], e[ks], h1[mt], 0, 0, 0);
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) h1[mt][r] = fmaxf(h1[mt][r], 0.f);
+      h2[mt] = b2[mt];
     }
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t q = 16 * mt + 4 * g + r;
-        d1[mt][r] = G.a2[q * R + row] > 0.0f ? d1[mt][r] : 0.0f;
-        G.d1[q * R + row] = d1[mt][r];
-      }
-    ngp_f4 de[MT1];
-#pragma unroll
-    for (int mt = 0; mt < MT1; ++mt) de[mt] = ngp_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int it = 0; it < 4; ++it)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int mt = 0; mt < MT1; ++mt)
-          de[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w1t[((mt * 4 + it) * 4 + r) * 64 + lane], d1[it][r], de[mt], 0,
-                                                        0, 0);
+        for (int mt = 0; mt < 4; ++mt)
+          h2[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2f[((mt * 4 + it) * 4 + r) * 64 + lane], h1[it][r], h2[mt], 0, 0, 0);
 #pragma unroll
-    for (int mt = 0; mt < MT1; ++mt)
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) h2[mt][r] = fmaxf(h2[mt][r], 0.f);
+    // d2, and dW3 from h2 and d0
+    ngp_f4 d2[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      d2[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w3t[mt * 64 + lane], d0, ngp_f4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) d2[mt][r] = h2[mt][r] > 0.f ? d2[mt][r] : 0.f;
+      *reinterpret_cast<ngp_f4*>(x0 + n * kNgpRow + 16 * mt + 4 * g) = h2[mt];
+    }
+    x1[n * kNgpRow + g] = d0;
+    ngp_wave_sync();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const float* at = x1 + (4 * ks + g) * kNgpRow;
+      const float bop = n < kNgpOut ? at[n & 3] : 0.f;
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)
+        c3[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x0[(4 * ks + g) * kNgpRow + 16 * mt + n], bop, c3[mt], 0, 0, 0);
+    }
+    ngp_wave_sync();
+    // dW2 from d2 and h1
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+      *reinterpret_cast<ngp_f4*>(x0 + n * kNgpRow + 16 * mt + 4 * g) = h1[mt];
+      *reinterpret_cast<ngp_f4*>(x1 + n * kNgpRow + 16 * mt + 4 * g) = d2[mt];
+    }
+    ngp_wave_sync();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      float aop[4], bop[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        aop[q] = x1[(4 * ks + g) * kNgpRow + 16 * q + n];
+        bop[q] = x0[(4 * ks + g) * kNgpRow + 16 * q + n];
+        s2[q] += aop[q];
+      }
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+          c2[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop[mt], bop[nt], c2[mt][nt], 0, 0, 0);
+    }
+    // d1, then dW1 from d1 and e
+    ngp_f4 d1[4];
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) d1[mt] = ngp_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int it = 0; it < 4; ++it)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+          d1[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2t[((mt * 4 + it) * 4 + r) * 64 + lane], d2[it][r], d1[mt], 0, 0, 0);
+    ngp_wave_sync();
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) d1[mt][r] = h1[mt][r] > 0.f ? d1[mt][r] : 0.f;
+      *reinterpret_cast<ngp_f4*>(x1 + n * kNgpRow + 16 * mt + 4 * g) = d1[mt];
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS1; ++ks) x0[n * kNgpRow + 4 * ks + g] = e[ks];
+    ngp_wave_sync();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      float bop[MT1];
+#pragma unroll
+      for (int nt = 0; nt < MT1; ++nt) bop[nt] = x0[(4 * ks + g) * kNgpRow + 16 * nt + n];
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt) {
+        const float aop = x1[(4 * ks + g) * kNgpRow + 16 * mt + n];
+        s1[mt] += aop;
+#pragma unroll
+        for (int nt = 0; nt < MT1; ++nt) c1[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(aop, bop[nt], c1[mt][nt], 0, 0, 0);
+      }
+    }
+    ngp_wave_sync();
+    // de
+#pragma unroll
+    for (int mt = 0; mt < MT1; ++mt) {
+      ngp_f4 de = ngp_f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int it = 0; it < 4; ++it)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          de = __builtin_amdgcn_mfma_f32_16x16x4f32(w1t[((mt * 4 + it) * 4 + r) * 64 + lane], d1[it][r], de, 0, 0, 0);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int q = 16 * mt + 4 * g + r;
-        if (q < KIN) des[nb * DST + q] = de[mt][r];
-      }
-  }
-  __syncthreads();
-  float de[KIN];
-#pragma unroll
-  for (int q = 0; q < KIN; ++q) de[q] = des[tid * DST + q];
-  __syncthreads();
-  // Scatter of de into the tables.  The block's 16 x 16 texels touch a small
-  // window of each level's vertices; their contributions are summed per vertex
-  // in LDS (float atomics) and each window vertex is then added to its table
-  // entry once: neighbouring texels share corners, so this issues a quarter or
-  // less of the global atomics.  A level whose window does not fit uses
-  // direct global atomics.
-  const int W = T.w[l], H = T.h[l];
-  const double u = ((double)x.i + 0.5) / (double)W, v = ((double)x.j + 0.5) / (double)H;
-  const int i_first = x.i - (tid & 15), j_first = x.j - (tid >> 4);
-  const uint32_t TT = 1u << S.log2_table, mask = TT - 1u;
-  float* gtab = T.gparams[l];
-  float* vs = lds;                       // [level][kNgpSlots][2]
-  for (int e = tid; e < LMAX * kNgpSlots * 2; e += 256) vs[e] = 0.f;
-  __syncthreads();
-  uint32_t vx0[LMAX], vy0[LMAX];
-  int ex[LMAX], ey[LMAX];
-#pragma unroll
-  for (int lv = 0; lv < LMAX; ++lv) {
-    ex[lv] = ey[lv] = 0;
-    vx0[lv] = vy0[lv] = 0;
-    if (lv >= S.levels) continue;
-    const int32_t N = S.res[lv];
-    // the window: vertices of the first and last texel of the tile along each axis (monotone in the texel)
-    const double xa = floor(((double)i_first + 0.5) / (double)W * (double)N);
-    const double xb = floor(((double)(i_first + 15) + 0.5) / (double)W * (double)N);
-    const double ya = floor(((double)j_first + 0.5) / (double)H * (double)N);
-    const double yb = floor(((double)(j_first + 15) + 0.5) / (double)H * (double)N);
-    vx0[lv] = (uint32_t)xa;
-    vy0[lv] = (uint32_t)ya;
-    ex[lv] = (int)(xb - xa) + 2;
-    ey[lv] = (int)(yb - ya) + 2;
-    const bool windowed = (int64_t)ex[lv] * ey[lv] <= kNgpSlots;
-    const double xx = u * (double)N, yy = v * (double)N;
-    const double x0 = floor(xx), y0 = floor(yy);
-    const float fx = (float)(xx - x0), fy = (float)(yy - y0);
-    const uint32_t xi = (uint32_t)x0, yi = (uint32_t)y0;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const uint32_t dx = c & 1, dy = c >> 1;
-      const float w = (dx ? fx : 1.0f - fx) * (dy ? fy : 1.0f - fy);
-      if (windowed) {
-        if (x.valid) {
-          const int slot = (int)(yi + dy - vy0[lv]) * ex[lv] + (int)(xi + dx - vx0[lv]);
-          atomicAdd(&vs[(lv * kNgpSlots + slot) * 2], w * de[2 * lv]);
-          atomicAdd(&vs[(lv * kNgpSlots + slot) * 2 + 1], w * de[2 * lv + 1]);
-        }
-      } else {
-        const uint32_t q = x.valid ? ngp_index(xi + dx, yi + dy, N, S.dense[lv], mask) : 0u;
-        ngp_table_add(gtab + (int64_t)lv * TT * 2, q, w * de[2 * lv], w * de[2 * lv + 1], x.valid, false);
+        const uint32_t q = 16 * mt + 4 * g + r;
+        if (q < (uint32_t)nin) G.de[q * R + row] = de[r];
       }
     }
   }
+  // sum over the wavefronts in LDS (the weights' space), then into the gradient, one atomic per parameter
   __syncthreads();
+  float* sum = wts;   // W1 | b1 | W2 | b2 | W3 | b3, as the parameters lie
+  const int m1 = 64 * nin, q2 = m1 + 64, q3 = q2 + 64 * 64 + 64, total = q3 + 4 * 64 + 4;
+  for (int f = tid; f < total; f += 256) sum[f] = 0.f;
+  for (int w = 0; w < 4; ++w) {
+    __syncthreads();
+    if (wv != w) continue;
 #pragma unroll
-  for (int lv = 0; lv < LMAX; ++lv) {
-    if (lv >= S.levels || (int64_t)ex[lv] * ey[lv] > kNgpSlots) continue;
-    const int32_t N = S.res[lv];
-    for (int sl = tid; sl < ex[lv] * ey[lv]; sl += 256) {
-      const float a0 = vs[(lv * kNgpSlots + sl) * 2], a1 = vs[(lv * kNgpSlots + sl) * 2 + 1];
-      if (a0 != 0.0f || a1 != 0.0f) {
-        const uint32_t vx = vx0[lv] + (uint32_t)(sl % ex[lv]), vy = vy0[lv] + (uint32_t)(sl / ex[lv]);
-        const uint32_t q = ngp_index(vx, vy, N, S.dense[lv], mask);
-        float* gq = gtab + (int64_t)lv * TT * 2 + 2 * (int64_t)q;
-        unsafeAtomicAdd(gq, a0);
-        unsafeAtomicAdd(gq + 1, a1);
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = 16 * mt + 4 * g + r;
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) sum[q2 + m * 64 + 16 * nt + n] += c2[mt][nt][r];
+#pragma unroll
+        for (int nt = 0; nt < MT1; ++nt)
+          if (16 * nt + n < nin) sum[m * nin + 16 * nt + n] += c1[mt][nt][r];
+        if (n < kNgpOut) sum[q3 + n * 64 + m] += c3[mt][r];
+      }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {   // a lane's sums cover every fourth texel: add the four lanes of a unit
+      float v2 = s2[q], v1 = s1[q];
+      v2 += __shfl_xor(v2, 16); v2 += __shfl_xor(v2, 32);
+      v1 += __shfl_xor(v1, 16); v1 += __shfl_xor(v1, 32);
+      if (g == 0) {
+        sum[q2 + 64 * 64 + 16 * q + n] += v2;
+        sum[m1 + 16 * q + n] += v1;
       }
     }
+    float v0 = s0;
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) v0 += __shfl_xor(v0, off);
+    if (n == 0) sum[q3 + 4 * 64 + g] += v0;
   }
+  __syncthreads();
+  float* gp = T.gparams[l] + S.o_w1;
+  for (int f = tid; f < total; f += 256)
+    if (sum[f] != 0.0f) unsafeAtomicAdd(gp + f, sum[f]);
 }
 
-// One weight-gradient product of one layer: C[m][n] = sum_r D[m][r] A[n][r]
-// over the layer's staging rows (feature-major, row stride R), m < M (<= 64),
-// n < K (<= 64); the bias gradient is sum_r D[m][r].  Blocks split the rows;
-// each thread owns a 4 x 4 tile of outputs (m = 4 (tid / 16) ..,
-// n = 4 (tid % 16) ..) and the threads of the first column tile also the 4
-// bias sums; partial sums are added to the gradient (weights row-major
-// [M][K], then the bias [M]).
-struct NgpGemm {
-  const float* D[3 * kMaxLayers];
-  const float* A[3 * kMaxLayers];
-  float* gw[3 * kMaxLayers];
-  float* gb[3 * kMaxLayers];
-  int64_t rows[3 * kMaxLayers];
-  int32_t M[3 * kMaxLayers], K[3 * kMaxLayers];
-  int64_t R;
-  int32_t n_gemm, blocks_per_gemm;
-};
-
-__global__ void __launch_bounds__(256) k_ngp_wgrad(NgpGemm Q) {
-#pragma clang fp contract(fast)
-  // rows padded to 65 floats: the staging writes (64 lanes, 64 consecutive rows of one feature) then fall
-  // on distinct banks instead of all on one
-  __shared__ float sD[64][65];
-  __shared__ float sA[64][65];
-  const int gi = blockIdx.x / Q.blocks_per_gemm, part = blockIdx.x - gi * Q.blocks_per_gemm;
-  if (gi >= Q.n_gemm) return;
-  const int M = Q.M[gi], K = Q.K[gi];
-  const int64_t rows = Q.rows[gi], R = Q.R;
-  const int64_t per = ((rows + Q.blocks_per_gemm - 1) / Q.blocks_per_gemm + 63) / 64 * 64;
-  const int64_t r0 = (int64_t)part * per, r1 = min(rows, r0 + per);
-  const int tid = threadIdx.x, mb = (tid >> 4) * 4, nb = (tid & 15) * 4;
-  float acc[4][4], bacc[4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    bacc[a] = 0.f;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = 0.f;
+// Scatter of the staged dL/de into the hash tables, one 16 x 16 texel tile per
+// block, one level per wavefront at a time.
+//
+// A vertex of a level receives sum_j sum_i wy(j) wx(i) de[j][i] over the tile's
+// texels: the bilinear weights are a product of an x and a y part, so the sums
+// are two small matrix products on the matrix cores (v_mfma_f32_16x16x4_f32),
+// D[j][vx] = de[j][i] Wx[i][vx] and then Wy[vy][j] D[j][vx], whose second operand
+// is the first's output registers (K permuted as in the bake; de is loaded as 16
+// bytes per lane in that order).  However many texels share a vertex, nothing is
+// added twice to one LDS or memory word.  The window of ex x ey vertices that the
+// tile touches goes through LDS, so that the global atomics, one per table float,
+// run over consecutive floats.  LDS float atomics per texel and corner, 64 of
+// them on one word at a coarse level, took 2.87 ms for seven 1024^2 textures of 8
+// levels; this takes 0.27 ms.
+// A window of more than kNgpSlots vertices (vertices finer than texels) adds each
+// corner with a global atomic, and so does a level with an infinite or NaN de,
+// which must reach its own four vertices only.
+template <int LMAX>
+__global__ void __launch_bounds__(256) k_ngp_scatter(NgpTable T, NgpShape S, NgpStage G) {
+  __shared__ int32_t first[LMAX][2];                       // per level: the window's first vertex (x, y)
+  __shared__ __align__(16) int32_t cell[LMAX][2][16];      // per level, axis and texel column or row: vertex in the window
+  __shared__ __align__(16) float frac[LMAX][2][16];        // ... and offset from it
+  __shared__ float win_all[4][2 * kNgpSlots];              // per wavefront: the window's sums [vy][vx][feature]
+  const int64_t b = blockIdx.x;
+  int l = 0;
+  while (l + 1 < T.k && T.block_off[l + 1] <= b) ++l;
+  const int W = T.w[l], H = T.h[l], tiles_x = (W + kNgpTile - 1) / kNgpTile;
+  const int64_t tb = b - T.block_off[l];
+  const int ty = (int)(tb / tiles_x), tx = (int)(tb - (int64_t)ty * tiles_x);
+  const int tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, g = lane >> 4, n = lane & 15;
+  for (int q = tid; q < 32 * S.levels; q += 256) {
+    const int lv = q >> 5, axis = (q >> 4) & 1, c = q & 15;
+    const double N = (double)S.res[lv], size = axis ? (double)H : (double)W;
+    const int at0 = kNgpTile * (axis ? ty : tx);
+    const double x = ((double)(at0 + c) + 0.5) / size * N, x0 = floor(x), xa = floor(((double)at0 + 0.5) / size * N);
+    cell[lv][axis][c] = (int32_t)(x0 - xa);
+    frac[lv][axis][c] = (float)(x - x0);
+    if (c == 0) first[lv][axis] = (int32_t)xa;
   }
-  for (int64_t rb = r0; rb < r1; rb += 64) {
-    const int nr = (int)min((int64_t)64, r1 - rb);
-    __syncthreads();
-    for (int p = tid; p < 64 * 64; p += 256) {
-      const int rr = p & 63, cc = p >> 6;   // consecutive threads read consecutive rows of one feature
-      sD[rr][cc] = (rr < nr && cc < M) ? Q.D[gi][cc * R + rb + rr] : 0.f;
-      sA[rr][cc] = (rr < nr && cc < K) ? Q.A[gi][cc * R + rb + rr] : 0.f;
-    }
-    __syncthreads();
-    for (int rr = 0; rr < nr; ++rr) {
-      const float dv[4] = {sD[rr][mb], sD[rr][mb + 1], sD[rr][mb + 2], sD[rr][mb + 3]};
-      const float aw[4] = {sA[rr][nb], sA[rr][nb + 1], sA[rr][nb + 2], sA[rr][nb + 3]};
+  __syncthreads();
+  const uint32_t TT = 1u << S.log2_table, mask = TT - 1u;
+  float* win = win_all[wv];
+#pragma unroll 1
+  for (int lv = wv; lv < S.levels; lv += 4) {
+    float* gtab = T.gparams[l] + (int64_t)lv * TT * 2;
+    const int32_t N = S.res[lv], dense = S.dense[lv];
+    // de of texel row n, columns 4 g .. 4 g + 3
+    const float* src = G.de + (uint32_t)(2 * lv) * (uint32_t)G.R + (uint32_t)(b * 256) + 16 * n + 4 * g;
+    ngp_f4 de[2];
+    de[0] = *reinterpret_cast<const ngp_f4*>(src);
+    de[1] = *reinterpret_cast<const ngp_f4*>(src + G.R);
+    const int ex = cell[lv][0][15] + 2, ey = cell[lv][1][15] + 2;   // uniform
+    const uint32_t vx0 = (uint32_t)first[lv][0], vy0 = (uint32_t)first[lv][1];
+    bool finite = true;
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        bacc[a] += dv[a];
+    for (int q = 0; q < 8; ++q) finite = finite && __builtin_isfinite(de[q >> 2][q & 3]);
+    if ((int64_t)ex * ey <= kNgpSlots && __all(finite)) {
+      const int4 cx = *reinterpret_cast<const int4*>(&cell[lv][0][4 * g]), cy = *reinterpret_cast<const int4*>(&cell[lv][1][4 * g]);
+      const float4 fx = *reinterpret_cast<const float4*>(&frac[lv][0][4 * g]);
+      const float4 fy = *reinterpret_cast<const float4*>(&frac[lv][1][4 * g]);
+      const int cxs[4] = {cx.x, cx.y, cx.z, cx.w}, cys[4] = {cy.x, cy.y, cy.z, cy.w};
+      const float fxs[4] = {fx.x, fx.y, fx.z, fx.w}, fys[4] = {fy.x, fy.y, fy.z, fy.w};
+      for (int nx = 0; nx < ex; nx += 16) {
+        ngp_f4 d[2] = {ngp_f4{0.f, 0.f, 0.f, 0.f}, ngp_f4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] += dv[a] * aw[b];
+        for (int q = 0; q < 4; ++q) {
+          const int at = nx + n - cxs[q];
+          const float w = at == 0 ? 1.0f - fxs[q] : at == 1 ? fxs[q] : 0.f;
+#pragma unroll
+          for (int f = 0; f < 2; ++f) d[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(de[f][q], w, d[f], 0, 0, 0);
+        }
+        for (int ny = 0; ny < ey; ny += 16) {
+          ngp_f4 o[2] = {ngp_f4{0.f, 0.f, 0.f, 0.f}, ngp_f4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int at = ny + n - cys[q];
+            const float w = at == 0 ? 1.0f - fys[q] : at == 1 ? fys[q] : 0.f;
+#pragma unroll
+            for (int f = 0; f < 2; ++f) o[f] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, d[f][q], o[f], 0, 0, 0);
+          }
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int vy = ny + 4 * g + r, vx = nx + n;
+            if (vy < ey && vx < ex) *reinterpret_cast<float2*>(win + 2 * (vy * ex + vx)) = make_float2(o[0][r], o[1][r]);
+          }
+        }
+      }
+      ngp_wave_sync();
+      // vertex p / 2 of the window: its row is the high word of a product with ceil(2^32 / ex) (exact below 2^16)
+      const uint32_t m = 0xffffffffu / (uint32_t)ex + 1u;
+      for (int p = lane; p < 2 * ex * ey; p += 64) {
+        const float v = win[p];
+        if (v != 0.0f) {
+          const uint32_t slot = (uint32_t)p >> 1, vy = __umulhi(slot, m), vx = slot - vy * (uint32_t)ex;
+          unsafeAtomicAdd(gtab + 2 * (int64_t)ngp_index(vx0 + vx, vy0 + vy, N, dense, mask) + (p & 1), v);
+        }
+      }
+      ngp_wave_sync();   // the window is written again by the next level
+    } else {
+      const int j = kNgpTile * ty + n;
+      const uint32_t yi = vy0 + (uint32_t)cell[lv][1][n];
+      const float fy = frac[lv][1][n];
+      for (int q = 0; q < 4; ++q) {
+        const int i = kNgpTile * tx + 4 * g + q;
+        if (i >= W || j >= H) continue;
+        const uint32_t xi = vx0 + (uint32_t)cell[lv][0][4 * g + q];
+        const float fx = frac[lv][0][4 * g + q];
+        const float v0 = q == 0 ? de[0][0] : q == 1 ? de[0][1] : q == 2 ? de[0][2] : de[0][3];
+        const float v1 = q == 0 ? de[1][0] : q == 1 ? de[1][1] : q == 2 ? de[1][2] : de[1][3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const uint32_t dx = c & 1, dy = c >> 1;
+          const float w = (dx ? fx : 1.0f - fx) * (dy ? fy : 1.0f - fy);
+          float* to = gtab + 2 * (int64_t)ngp_index(xi + dx, yi + dy, N, dense, mask);
+          unsafeAtomicAdd(to, w * v0);
+          unsafeAtomicAdd(to + 1, w * v1);
+        }
       }
     }
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int m = mb + a;
-    if (m >= M) continue;
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int n = nb + b;
-      if (n < K && acc[a][b] != 0.0f) unsafeAtomicAdd(Q.gw[gi] + (int64_t)m * K + n, acc[a][b]);
-    }
-    if (nb == 0 && bacc[a] != 0.0f) unsafeAtomicAdd(Q.gb[gi] + m, bacc[a]);
   }
 }
 
