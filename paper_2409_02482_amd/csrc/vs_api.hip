@@ -529,19 +529,37 @@ vs_status vs_render_backward(const vs_mesh* layers, const vs_texture* tex, int32
   hipStream_t s = (hipStream_t)stream;
   const int64_t tiles = total_tiles(views, vs::kShadeTileSlot);
   const auto* tile_view = (const int32_t*)(base + lay.tile_view);
-  const int count_paths = sflags & VS_SHADE_COUNT_PATHS;
-  auto launch = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)vs::shade_grid_blocks(tiles)), dim3(256), 0, s, views->dev,
-                       views->n_views, tile_view, tiles, L, X, proj,
-                       L.vert_off[k], vis, (const float4*)grad_rgba, (const float4*)target, scale, loss,
-                       (float4*)out_rgba, target ? sse : nullptr, wrap, eps, status, count_paths);
+  vs::BwdArgs args;
+  args.L = L;
+  args.X = X;
+  args.views = views->dev;
+  args.tile_view = tile_view;
+  args.n_tiles = tiles;
+  args.proj = proj;
+  args.vpv = L.vert_off[k];
+  args.vis = vis;
+  args.grad_out = (const float4*)grad_rgba;
+  args.target = (const float4*)target;
+  args.out = (float4*)out_rgba;
+  args.sse = target ? sse : nullptr;
+  args.status = status;
+  args.n_views = views->n_views;
+  args.loss = loss;
+  args.wrap = wrap;
+  args.count_paths = sflags & VS_SHADE_COUNT_PATHS;
+  args.loss_scale = scale;
+  args.eps_T = eps;
+  auto launch = [&](auto kern, int per_block = 1) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)vs::shade_grid_blocks(tiles, per_block)), dim3(256 * per_block), 0, s, args);
   };
   // per-layer state lives in registers, so the common layer counts get their own instantiation
-  if (k <= 4) launch(vs::k_shade_bwd<4>);
-  else if (k <= 7) launch(vs::k_shade_bwd<7>);
-  else if (k <= 8) launch(vs::k_shade_bwd<8>);
-  else if (k <= 9) launch(vs::k_shade_bwd<9>);
-  else launch(vs::k_shade_bwd<16>);
+  static_assert(vs::kShadeLossLayers == 4, "the instantiation below");
+  if (k <= 4 && args.sse) launch(vs::k_shade_bwd<4, vs::kShadeLossTiles>, vs::kShadeLossTiles);
+  else if (k <= 4) launch(vs::k_shade_bwd<4, 1>);
+  else if (k <= 7) launch(vs::k_shade_bwd<7, 1>);
+  else if (k <= 8) launch(vs::k_shade_bwd<8, 1>);
+  else if (k <= 9) launch(vs::k_shade_bwd<9, 1>);
+  else launch(vs::k_shade_bwd<16, 1>);
   if ((st = check_launch("vs_render_backward"))) return st;
   return ok();
 }

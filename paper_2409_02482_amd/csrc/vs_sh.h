@@ -96,7 +96,7 @@ __global__ void __launch_bounds__(256, DEG == 3 ? 4 : 1) k_shade_sh(const vs_vie
   const int64_t pix = (int64_t)c.y * W + c.x;
   const uint64_t* vrow = vis + (int64_t)k * V.pix_offset + pix;
   const ProjVert* pview = proj + (int64_t)c.v * vpv;
-  const double px = 256.0 * c.x + 128.0, py = 256.0 * c.y + 128.0;
+  const int32_t px = 256 * c.x + 128, py = 256 * c.y + 128;
   // view ray through the pixel centre, world space: R^T ((x + 1/2 - cx) / fx, (y + 1/2 - cy) / fy, 1)
   float dx, dy, dz;
   {
