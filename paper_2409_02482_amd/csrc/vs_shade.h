@@ -291,7 +291,8 @@ __device__ inline int32_t abs_index(int32_t r, int32_t d, int32_t n, int wrap) {
 // registers (8 and 9 layers spill 5 and 14).  Windows of 320, 272 and 240 texels
 // at six, seven and eight blocks: metric scene 6.73 / 6.36 / 6.61 ms, 128 views at
 // 800^2 9.35 / 8.90 / 9.03, k = 9 scene 6.72 / 6.66 / 6.90, 384 texels at five
-// blocks 7.25 / 9.77 / 6.91.
+// blocks 7.25 / 9.77 / 6.91.  Up to 16 layers, five blocks of 288 (384 texels at two, four blocks of
+// 320): 12 layers, six views of 700 x 600, 550 us (690, 611); 16 layers 771 us (931, 842).
 // Two tiles per block (kShadeLossTiles) halve the atomics into the one double of
 // the loss sum, which the memory side takes one after the other (5.8 ns each,
 // beside all others): up to 4 layers they take longer than the pixels.  Three
@@ -299,8 +300,8 @@ __device__ inline int32_t abs_index(int32_t r, int32_t d, int32_t n, int wrap) {
 // without a sum; without a sum two tiles cost 3 % (four layers), and from 5 layers
 // on they cost more than they save (metric 6.36 -> 6.93 ms).
 template <int KMAX, int TILES> struct BwdShape {
-  static constexpr int win = KMAX > 9 ? 384 : TILES == 1 ? 272 : 252;
-  static constexpr int waves = KMAX > 9 ? 2 : TILES == 1 ? 7 : 8;
+  static constexpr int win = KMAX > 9 ? 288 : TILES == 1 ? 272 : 252;
+  static constexpr int waves = KMAX > 9 ? 5 : TILES == 1 ? 7 : 8;
 };
 constexpr int kShadeLossTiles = 2;
 constexpr int kShadeLossLayers = 4;   // ... up to this many layers
