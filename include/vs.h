@@ -211,10 +211,10 @@ size_t vs_raster_workspace_bytes(const vs_mesh* layers, int32_t k, const vs_view
  * Per (view, layer, pixel) the slot keeps the key of the nearest covering
  * triangle (conventions above: snapping, fill rule, key).
  * layers: host array [k] of device meshes, layer 0 outermost.  1 <= k <= 16.
- * n_views * total triangles must be below 2^30.  Bin-list offsets are 64-bit,
- * so any total of (triangle, bin) entries is handled; bins whose list does
- * not fit the reserved capacity (below 2^32 entries) are rasterised by the
- * exact full-layer path and counted in VS_STAT_BIN_OVERFLOW.
+ * n_views * total triangles must be below 2^30.  Any total of (triangle, bin)
+ * entries is handled: triangles whose entries do not fit the reserved capacity
+ * (below 2^32 entries) are gone through one by one in every bin that they may
+ * reach, and these bins are counted in VS_STAT_BIN_OVERFLOW.
  * vis:    device u64 [sum_v k H_v W_v], written in full.  Slot of (view v,
  *         layer l, pixel (x, y)) = k * pix_offset[v] + l * H_v W_v + y W_v + x.
  * ws:     device workspace of at least vs_raster_workspace_bytes bytes,

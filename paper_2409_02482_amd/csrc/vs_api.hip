@@ -104,12 +104,10 @@ vs_status build_layers(const vs_mesh* layers, int32_t k, vs::LayerTable& L) {
     L.n_tri[l] = m.n_tri;
     L.vert_off[l + 1] = L.vert_off[l] + m.n_vert;
     L.tri_off[l + 1] = L.tri_off[l] + m.n_tri;
-    L.tri_pad[l + 1] = L.tri_pad[l] + ((int64_t)m.n_tri + 63) / 64 * 64;
   }
   for (int l = k + 1; l <= VS_MAX_LAYERS; ++l) {
     L.vert_off[l] = L.vert_off[k];
     L.tri_off[l] = L.tri_off[k];
-    L.tri_pad[l] = L.tri_pad[k];
   }
   return VS_OK;
 }
@@ -135,6 +133,13 @@ int bin_slot(int bin) { return bin == 8 ? 0 : bin == 16 ? 1 : bin == 32 ? 2 : bi
 
 constexpr int kDefaultBin = 64;
 
+vs::BinGroups bin_groups(const vs::LayerTable& L, int reps) {
+  vs::BinGroups q;
+  std::memset(&q, 0, sizeof(q));
+  for (int l = 0; l < L.k; ++l) q.off[l + 1] = q.off[l] + (int32_t)((L.n_tri[l] + (int64_t)256 * reps - 1) / (256 * reps));
+  return q;
+}
+
 vs::WsLayout ws_layout(const vs::LayerTable& L, const vs_views* views, int bin, int64_t capacity = 0) {
   vs::WsLayout w;
   const int n_views = views->n_views;
@@ -144,10 +149,19 @@ vs::WsLayout ws_layout(const vs::LayerTable& L, const vs_views* views, int bin, 
   w.n_tiles16 = tot.tile_offset[1];
   w.n_tiles_bin = w.slot >= 0 ? tot.tile_offset[w.slot] : 0;
   w.n_bins = w.n_tiles_bin * L.k;
-  w.n_partial = (w.n_bins + 1023) / 1024;
   const uint64_t tris = (uint64_t)n_views * (uint64_t)L.tri_off[L.k];
+  w.reps = vs::bin_reps(L.tri_off[L.k], n_views);
+  w.n_groups = (int64_t)n_views * bin_groups(L, w.reps).off[L.k];
   const uint64_t factor = w.bin == 8 ? 4 : w.bin == 16 ? 3 : 2;
-  w.capacity = capacity > 0 ? (uint64_t)capacity : std::max<uint64_t>(tris * factor, 1u << 20);
+  // 4 + `factor` words per triangle (a back face's entry has 4, a front face's one) and five per bin, less the
+  // groups' records and the parts' counters
+  const int64_t parts = (int64_t)vs::kPools * n_views, pool_bytes = parts * vs::kPoolApart * 4;
+  const int64_t words = 4 * (int64_t)tris + (int64_t)std::max<uint64_t>(tris * factor, 1u << 20) + 5 * w.n_bins -
+                        4 * w.n_groups - pool_bytes / 4;
+  // a caller's count of entries: 4 words per triangle and one per entry, of which runs take up to 5 per entry
+  w.capacity = capacity > 0 ? 4 * tris + (uint64_t)capacity : (uint64_t)std::max<int64_t>(words, 4 * (int64_t)tris);
+  const uint64_t usable = std::min<uint64_t>({w.capacity, (uint64_t)vs::kSegAll, capacity > 0 ? 5 * (uint64_t)capacity : ~0ull});
+  w.pool_words = (uint32_t)(usable / (uint64_t)parts / 4 * 4);
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off += vs::align_up(bytes, 256); return o; };
   w.status = take(256);
@@ -155,11 +169,8 @@ vs::WsLayout ws_layout(const vs::LayerTable& L, const vs_views* views, int bin, 
   w.proj = take((size_t)n_views * (size_t)L.vert_off[L.k] * sizeof(vs::ProjVert));
   // everything below depends on the bin size; render and backward read only the part above
   w.bin_view = take((size_t)w.n_tiles_bin * 4);
-  w.count = take((size_t)w.n_bins * 4);
-  w.offset = take((size_t)w.n_bins * 8);
-  w.cursor = take((size_t)w.n_bins * 8);
-  w.spans = take((size_t)n_views * (size_t)L.tri_off[L.k] * sizeof(vs::SpanRec));
-  w.partial = take((size_t)w.n_partial * 8);
+  w.recs = take((size_t)w.n_groups * sizeof(vs::GroupRec));
+  w.pools = take((size_t)pool_bytes);
   w.list = take((size_t)w.capacity * 4);
   w.total = off;
   return w;
@@ -252,20 +263,30 @@ vs_status vs_raster_layers(const vs_mesh* layers, int32_t k, const vs_views* vie
   auto* proj = (vs::ProjVert*)(base + lay.proj);
   auto* tile_view = (int32_t*)(base + lay.tile_view);
   auto* bin_view = (int32_t*)(base + lay.bin_view);
-  auto* count = (uint32_t*)(base + lay.count);
-  auto* offset = (uint64_t*)(base + lay.offset);
-  auto* cursor = (uint32_t*)(base + lay.cursor);
-  auto* spans = (vs::SpanRec*)(base + lay.spans);
-  auto* partial = (uint64_t*)(base + lay.partial);
-  auto* list = (int32_t*)(base + lay.list);
+  auto* recs = (vs::GroupRec*)(base + lay.recs);
+  auto* list = (uint32_t*)(base + lay.list);
+  auto* pools = (uint32_t*)(base + lay.pools);
   const int64_t vpv = L.vert_off[k];
   const int nv = views->n_views;
   const int64_t ntri = L.tri_off[k];
-  hipLaunchKernelGGL(vs::k_fill_u64, dim3(1), dim3(256), 0, s, (uint64_t*)status, (int64_t)VS_STAT_COUNT, 0ull);
-  hipLaunchKernelGGL(vs::k_tile_view, dim3(grid_1d(lay.n_tiles16, 256)), dim3(256), 0, s, views->dev, nv, tile_view,
-                     lay.n_tiles16);
-  hipLaunchKernelGGL(vs::k_project, dim3(grid_1d(vpv, 256), nv), dim3(256), 0, s, views->dev, L, proj, vpv);
-  if (flags & VS_RASTER_DIRECT) {
+  const bool direct = flags & VS_RASTER_DIRECT;
+  vs::SetupArgs setup;
+  setup.views = views->dev;
+  setup.proj = proj;
+  setup.vpv = vpv;
+  setup.tile_view = tile_view;
+  setup.bin_view = bin_view;
+  setup.n_tiles16 = lay.n_tiles16;
+  setup.n_tiles_bin = direct ? 0 : lay.n_tiles_bin;
+  setup.status = status;
+  setup.pools = pools;
+  setup.n_views = nv;
+  setup.slot = lay.slot;
+  setup.proj_blocks = (int32_t)grid_1d(vpv, 256);
+  setup.tile_blocks = (int32_t)grid_1d(lay.n_tiles16, 256);
+  const unsigned setup_grid = (unsigned)setup.proj_blocks * (unsigned)nv + (unsigned)setup.tile_blocks + grid_1d(setup.n_tiles_bin, 256);
+  hipLaunchKernelGGL(vs::k_setup, dim3(setup_grid), dim3(256), 0, s, setup, L);
+  if (direct) {
     const int64_t total_slots = (int64_t)k * views->host[nv].pix_offset;
     hipLaunchKernelGGL(vs::k_fill_u64, dim3((unsigned)std::min<int64_t>(grid_1d(total_slots, 256), 65536)),
                        dim3(256), 0, s, vis, total_slots, (uint64_t)VS_EMPTY);
@@ -275,44 +296,33 @@ vs_status vs_raster_layers(const vs_mesh* layers, int32_t k, const vs_views* vie
     return ok();
   }
   const int B = lay.bin, slot = lay.slot;
-  const unsigned fill_grid = (unsigned)std::min<int64_t>(grid_1d(lay.n_bins, 256), 65536);
-  hipLaunchKernelGGL(vs::k_tile_view_slot, dim3(grid_1d(lay.n_tiles_bin, 256)), dim3(256), 0, s, views->dev, nv,
-                     bin_view, lay.n_tiles_bin, slot);
-  hipLaunchKernelGGL(vs::k_fill_u32, dim3(fill_grid), dim3(256), 0, s, count, lay.n_bins, 0u);
-  hipLaunchKernelGGL(vs::k_fill_u32, dim3(fill_grid), dim3(256), 0, s, cursor, 2 * lay.n_bins, 0u);
-  const dim3 count_grid(vs::bin_grid_x<vs::kCountReps>(L.tri_pad[k]), (unsigned)nv);
-  const dim3 scatter_grid(vs::bin_grid_x<vs::kScatterReps>(L.tri_pad[k]), (unsigned)nv);
-  auto bin_count = [&](auto kern) {
-    hipLaunchKernelGGL(kern, count_grid, dim3(256), 0, s, views->dev, L, (const vs::ProjVert*)proj, vpv, slot, count,
-                       cursor, spans, status);
+  const vs::BinGroups groups = bin_groups(L, lay.reps);
+  const dim3 bin_grid((unsigned)((groups.off[k] + 7) / 8 * 8), (unsigned)nv);
+  auto binned = [&](auto kern) {
+    hipLaunchKernelGGL(kern, bin_grid, dim3(256), 0, s, views->dev, L, groups, (const vs::ProjVert*)proj, vpv, recs,
+                       list, lay.pool_words, pools, status);
   };
-  auto bin_scatter = [&](auto kern) {
-    hipLaunchKernelGGL(kern, scatter_grid, dim3(256), 0, s, views->dev, L, slot, (const vs::SpanRec*)spans,
-                       (const uint32_t*)count, (const uint64_t*)offset, cursor, list, lay.capacity);
-  };
-  switch (B) {
-    case 8: bin_count(vs::k_bin_count<8>); break;
-    case 16: bin_count(vs::k_bin_count<16>); break;
-    case 32: bin_count(vs::k_bin_count<32>); break;
-    default: bin_count(vs::k_bin_count<64>); break;
+  switch (B * 8 + lay.reps) {
+    case 8 * 8 + 1: binned(vs::k_bin<8, 1>); break;
+    case 8 * 8 + 2: binned(vs::k_bin<8, 2>); break;
+    case 8 * 8 + 4: binned(vs::k_bin<8, 4>); break;
+    case 16 * 8 + 1: binned(vs::k_bin<16, 1>); break;
+    case 16 * 8 + 2: binned(vs::k_bin<16, 2>); break;
+    case 16 * 8 + 4: binned(vs::k_bin<16, 4>); break;
+    case 32 * 8 + 1: binned(vs::k_bin<32, 1>); break;
+    case 32 * 8 + 2: binned(vs::k_bin<32, 2>); break;
+    case 32 * 8 + 4: binned(vs::k_bin<32, 4>); break;
+    case 64 * 8 + 1: binned(vs::k_bin<64, 1>); break;
+    case 64 * 8 + 2: binned(vs::k_bin<64, 2>); break;
+    default: binned(vs::k_bin<64, 4>); break;
   }
-  hipLaunchKernelGGL(vs::k_scan_local, dim3((unsigned)lay.n_partial), dim3(256), 0, s, count,
-                     (const uint32_t*)cursor, offset, partial, lay.n_bins);
-  hipLaunchKernelGGL(vs::k_scan_partials, dim3(1), dim3(1024), 0, s, partial, lay.n_partial);
-  hipLaunchKernelGGL(vs::k_scan_add, dim3(grid_1d(lay.n_bins, 256)), dim3(256), 0, s, offset,
-                     (const uint64_t*)partial, lay.n_bins);
-  switch (B) {
-    case 8: bin_scatter(vs::k_bin_scatter<8>); break;
-    case 16: bin_scatter(vs::k_bin_scatter<16>); break;
-    case 32: bin_scatter(vs::k_bin_scatter<32>); break;
-    default: bin_scatter(vs::k_bin_scatter<64>); break;
-  }
+  const int group_log = lay.reps == 4 ? 10 : lay.reps == 2 ? 9 : 8;
   const unsigned nblk = (unsigned)((lay.n_bins + 7) / 8 * 8);
   auto raster = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3(nblk), dim3(vs::kRasterThreads), 0, s, views->dev, (const int32_t*)bin_view,
-                       lay.n_tiles_bin, L, (const vs::ProjVert*)proj, vpv, slot, (const uint32_t*)count,
-                       (const uint64_t*)offset, (const uint32_t*)cursor, (const int32_t*)list,
-                       (const vs::SpanRec*)spans, lay.capacity, (unsigned long long*)vis, status, count_frags);
+                       lay.n_tiles_bin, L, groups, group_log, (const vs::ProjVert*)proj, vpv, slot,
+                       (const vs::GroupRec*)recs, (const uint32_t*)list,
+                       (unsigned long long*)vis, status, count_frags);
   };
   switch (B) {
     case 8: raster(vs::k_raster_bins<8>); break;

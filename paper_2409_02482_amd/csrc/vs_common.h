@@ -27,7 +27,6 @@ struct LayerTable {
   int32_t n_tri[kMaxLayers];
   int64_t vert_off[kMaxLayers + 1];  // prefix of n_vert: layer l's vertices in one view's projected block
   int64_t tri_off[kMaxLayers + 1];   // prefix of n_tri
-  int64_t tri_pad[kMaxLayers + 1];   // prefix of n_tri rounded up to 64: one layer per wavefront in per-triangle launches
   int32_t k;
 };
 
@@ -54,16 +53,13 @@ struct WsLayout {
   size_t tile_view;  // int32 [16-pixel tiles of all views]: owning view (shading)
   size_t bin_view;   // int32 [raster bin tiles of all views]: owning view
   size_t proj;       // ProjVert [n_views][sum n_vert]
-  size_t count;      // u32 [n_bins] entries per bin (before the scan: only those of triangles
-                     //   for which the bin is not the first; the scan adds the reservations)
-  size_t offset;     // u64 [n_bins] exclusive prefix of count
-  size_t cursor;     // u32 [2 n_bins] per bin and side (front from the head, others from the
-                     //   tail): first-bin places reserved by the count, then the scatter's
-  size_t spans;      // SpanRec [n_views][sum n_tri]: box, depth bound and first-bin place of every triangle
-  size_t partial;    // u64 [ceil(n_bins / 1024)] scan block totals
-  size_t list;       // int32 [capacity] triangle ids of all bins
-  int64_t n_tiles16, n_tiles_bin, n_bins, n_partial;
-  uint64_t capacity;
+  size_t recs;       // GroupRec [n_views][groups of a view]
+  size_t pools;      // u32: words taken from each part of the list
+  size_t list;       // u32 [capacity]: the groups' runs (tile tables, triangle ids, back faces' records)
+  int64_t n_tiles16, n_tiles_bin, n_bins, n_groups;   // groups: of all views
+  int reps;          // triangles per thread of a group's block
+  uint32_t pool_words;   // words of a part of the list
+  uint64_t capacity;   // words of the list
   int bin, slot;
   size_t total;
 };
@@ -249,6 +245,32 @@ __device__ inline uint64_t depth_lower_key(const TriSetup& T, uint32_t t) {
   const double zlo = (1.0 / maxw) * (1.0 - 1e-12);
   const float lo = __double2float_rd(zlo);
   return ((uint64_t)__float_as_uint(lo) << 32) | (uint64_t)t;
+}
+
+// Wavefront min / max without the LDS pipe: inclusive row scans with DPP
+// row shifts (row_shr:n moves lane i - n into lane i; lanes with no source
+// keep the identity), so lane 15 of each 16-lane row holds the row's result.
+// Call with every lane active.
+// Then row_bcast:15 (rows 1 and 3 take lane 15 / 47) and row_bcast:31 (rows 2 and 3
+// take lane 31) carry the row results to lane 63.
+__device__ inline int32_t wave_min(int32_t v) {
+  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x111, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x112, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x114, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x118, 0xf, 0xf, false));
+  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x142, 0xa, 0xf, false));
+  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(v, 63);
+}
+
+__device__ inline int32_t wave_max(int32_t v) {
+  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x111, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x112, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x114, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x118, 0xf, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x142, 0xa, 0xf, false));
+  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(v, 63);
 }
 
 // Binary search of the view that owns flat index g in a prefix array read

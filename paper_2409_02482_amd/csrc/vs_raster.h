@@ -1,23 +1,21 @@
 // Visibility kernels (steps 1-3): vertex projection and per-layer
 // rasterisation into 64-bit (depth, triangle id) keys.
 //
-// Binned pipeline (one call of vs_raster_layers):
-//   k_project      snapped screen positions and w = 1/z for every (view, layer, vertex)
-//   k_bin_count    per triangle: setup, cull, bounding box -> screen tiles of
-//                  B x bin_rows(B) pixels; reserve the triangle's place in its
-//                  first bin = (view, tile, layer), count it in its other bins,
-//                  and record its packed tile span and place
-//   k_scan_*       exclusive prefix sum of the bins' entry counts -> list offsets
-//   k_bin_scatter  write triangle ids into the bin lists (front faces first)
-//   k_raster_bins  one block per bin: an LDS tile of keys starts EMPTY, the
+// Binned pipeline (one call of vs_raster_layers), three launches:
+//   k_setup        snapped screen positions and w = 1/z for every (view, layer, vertex);
+//                  view tables of the tiles; counters cleared
+//   k_bin          per group of 256 to 1,024 consecutive triangles of a layer: set-up, cull,
+//                  bounding boxes -> screen tiles of B x bin_rows(B) pixels; the group's
+//                  triangle ids sorted by tile (front faces first), with a table of the
+//                  tiles' starts, written as one run of the list
+//   k_raster_bins  one block per bin = (view, tile, layer): finds the groups that reach its
+//                  tile from their records; an LDS tile of keys starts EMPTY, the
 //                  bin's triangles take 64-bit LDS minima, and the finished
 //                  tile is stored once, coalesced (so no clear pass is needed);
 //                  a fragment whose depth lower bound already loses to the
 //                  tile's key skips the exact FP64 depth, and a back-facing
 //                  triangle whose bound loses everywhere in its bounding box
 //                  is skipped whole
-// First-bin reservations are aggregated per wavefront: lanes whose first bin
-// and side agree elect one lane that reserves for the whole group.
 #pragma once
 
 #include "vs_common.h"
@@ -40,8 +38,9 @@ constexpr int kSmallSpan = 16384;   // small-triangle path: bbox extents <= 64 p
 // triangles a layer, 16 views at 1000^2) 0.84 / 0.71 / 0.66 ms, a 256^2 view of 1,292-triangle shells
 // 39 / 42 / 44 us, the metric scene 2.35 / 2.36 / 2.36 ms.
 constexpr int kSmallArea = 512;
-constexpr uint32_t kBigQueue = 192; // larger triangles of a bin that its block queues (31.2 KiB of LDS: still five blocks a CU)
-static_assert(kBigQueue <= (uint32_t)kRasterThreads, "one round deals the whole queue");
+constexpr uint32_t kBigQueue = 16;   // larger back-facing triangles of a bin that its block queues, and
+constexpr int kSegs = 56;            // groups whose entries it draws at once (31.2 KiB of LDS: five blocks a CU)
+static_assert(kBigQueue <= (uint32_t)kRasterThreads && kSegs <= 64, "one round deals the whole queue; one wavefront sums the groups up");
 
 // Fill n u64 words with a value (grid-stride).
 __global__ void __launch_bounds__(256) k_fill_u64(uint64_t* __restrict__ p, int64_t n, uint64_t val) {
@@ -49,22 +48,49 @@ __global__ void __launch_bounds__(256) k_fill_u64(uint64_t* __restrict__ p, int6
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = val;
 }
 
-__global__ void __launch_bounds__(256) k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t val) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = val;
-}
+// The list is shared out in kPools equal parts per view, one for the groups of each XCD, in which runs
+// are reserved by atomics on the parts' own words, kPoolApart words from each other: requests to one
+// word are served one after the other (about 6 ns each; on a single word 168k groups would take 1 ms).
+// A run that its part has no room for goes to the view's next parts.
+constexpr int kPools = 8;
+constexpr int kPoolApart = 16;
 
-// Step 1 for every (view, layer, vertex).  grid.x covers the vertices of all
-// layers of one view (vert_off prefix), grid.y = view.
-__global__ void __launch_bounds__(256) k_project(const vs_view* __restrict__ views, LayerTable L,
-                                                 ProjVert* __restrict__ proj, int64_t vpv) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int v = blockIdx.y;
-  if (g >= vpv) return;
-  int l = 0;
-  while (l + 1 < L.k && L.vert_off[l + 1] <= g) ++l;
-  const int64_t i = g - L.vert_off[l];
-  proj[(int64_t)v * vpv + g] = project_vertex(L.xyz[l] + 3 * i, views[v].cam);
+// Everything that binning, drawing and shading find ready, one launch: the first blocks take step 1
+// for every (view, layer, vertex), proj_blocks per view; the next ones tile_view[g] = view owning
+// 16-pixel tile g, and then bin_view[g] likewise for the bins' tiles (n_tiles_bin = 0: none).
+struct SetupArgs {
+  const vs_view* views;
+  ProjVert* proj;
+  int64_t vpv;
+  int32_t* tile_view;
+  int32_t* bin_view;
+  int64_t n_tiles16, n_tiles_bin;
+  unsigned long long* status;
+  uint32_t* pools;
+  int32_t n_views, slot, proj_blocks, tile_blocks;
+};
+
+__global__ void __launch_bounds__(256) k_setup(SetupArgs A, LayerTable L) {
+  const uint32_t all_proj = (uint32_t)A.proj_blocks * (uint32_t)A.n_views;
+  if (blockIdx.x < all_proj) {
+    const int v = (int)(blockIdx.x / (uint32_t)A.proj_blocks);
+    const int64_t g = (int64_t)(blockIdx.x - (uint32_t)v * (uint32_t)A.proj_blocks) * 256 + threadIdx.x;
+    if (blockIdx.x == 0 && threadIdx.x < VS_STAT_COUNT) A.status[threadIdx.x] = 0ull;
+    if (g < kPools) A.pools[(v * kPools + (int)g) * kPoolApart] = 0u;
+    if (g >= A.vpv) return;
+    int l = 0;
+    while (l + 1 < L.k && L.vert_off[l + 1] <= g) ++l;
+    A.proj[(int64_t)v * A.vpv + g] = project_vertex(L.xyz[l] + 3 * (g - L.vert_off[l]), A.views[v].cam);
+    return;
+  }
+  const uint32_t b = blockIdx.x - all_proj;
+  const bool bins = b >= (uint32_t)A.tile_blocks;   // uniform
+  const int64_t g = (int64_t)(bins ? b - (uint32_t)A.tile_blocks : b) * 256 + threadIdx.x;
+  if (bins) {
+    if (g < A.n_tiles_bin) A.bin_view[g] = find_view_tile(A.views, A.n_views, g, A.slot);
+  } else if (g < A.n_tiles16) {
+    A.tile_view[g] = find_view_tile(A.views, A.n_views, g, 1);
+  }
 }
 
 // Pixel-centre range covered by the triangle's fixed-point bounding box, clipped to the view.
@@ -86,125 +112,92 @@ __device__ inline int cull_slot(int r) {
                                                                         : VS_STAT_BAD_INDEX;
 }
 
-// Record of one (view, layer, triangle) written by k_bin_count: its pixel
-// bounding box clipped to the view, packed in 64 bits,
-//   i0 | i1 << 13 | j0 << 26 | j1 << 39 | front << 52 | valid << 53,
-// and the depth bits of its lower-bound key (depth_lower_key >> 32).
-// "front" marks a negative screen area before orientation normalisation,
+// List record of one back-facing triangle in one bin, four words: its pixel
+// bounding box clipped to the view, packed in 52 bits,
+//   i0 | i1 << 13 | j0 << 26 | j1 << 39,
+// the depth bits of its lower-bound key (depth_lower_key >> 32), and its id.
+// "Front" marks a negative screen area before orientation normalisation,
 // which is the front side of an outward, counter-clockwise wound closed mesh
-// under this camera convention (y down).  It orders the bin lists, front
-// faces first; the raster uses the box and the bound to skip, without
-// loading its vertices, a back-facing triangle that cannot lower any key.
-constexpr uint64_t kSpanValid = 1ull << 53;
-constexpr uint64_t kSpanFront = 1ull << 52;
-
-struct alignas(16) SpanRec {
-  uint64_t box;
-  uint32_t zlo;    // high word of the triangle's depth lower-bound key
-  uint32_t rank;   // entries of the same side of its first bin reserved before it
-};
-
-__device__ inline uint64_t pack_box(int i0, int i1, int j0, int j1, bool front) {
-  return (uint64_t)i0 | ((uint64_t)i1 << 13) | ((uint64_t)j0 << 26) | ((uint64_t)j1 << 39) |
-         (front ? kSpanFront : 0ull) | kSpanValid;
+// under this camera convention (y down).  Front faces are drawn first; the
+// raster uses the box and the bound to skip, without loading its vertices, a
+// back-facing triangle that cannot lower any key.
+__device__ inline uint64_t pack_box(int i0, int i1, int j0, int j1) {
+  return (uint64_t)i0 | ((uint64_t)i1 << 13) | ((uint64_t)j0 << 26) | ((uint64_t)j1 << 39);
 }
 
 __device__ inline void unpack_box(uint64_t b, int& i0, int& i1, int& j0, int& j1) {
   i0 = (int)(b & 8191); i1 = (int)((b >> 13) & 8191); j0 = (int)((b >> 26) & 8191); j1 = (int)((b >> 39) & 8191);
 }
 
-// Triangles per thread in the count and scatter launches.  Count: the vertex
-// ids of all four are requested first, then the vertex records two at a time,
-// the next one's loads issued as soon as a record slot is free (four records
-// loaded up front needed 97 registers and were slower); the four first-bin
-// reservations are in flight together and the records are written once they
-// return.  Scatter: the records and first-bin list ranges of all four are read
-// together; only a triangle's other bins still take a returning atomic there.
-// Eight per thread in the scatter: 102 registers, metric raster phase 5.00
-// against 4.98 ms, k = 9 scene 7.96 against 7.67 ms.
-constexpr int kCountReps = 4;
-constexpr int kScatterReps = 4;
+// Groups of 256 R consecutive triangles of one layer, numbered over the layers of a view.
+struct BinGroups {
+  int32_t off[kMaxLayers + 1];
+};
 
-// Grid of a count/scatter launch with R triangles per thread: x = blocks of
-// R x 256 padded triangles of one view (each layer's range rounded up to 64,
-// so that a wavefront never spans two layers), rounded up to a multiple of
-// the XCD count; y = view.
-template <int R>
-__host__ __device__ inline uint32_t bin_grid_x(int64_t n_tri_padded) {
-  return (uint32_t)((((n_tri_padded + 255) / 256 + R - 1) / R + 7) / 8 * 8);
+// Record of one group in one view.  Its tiles' rectangle is counted in macro tiles of
+// 2^shift x 2^shift bins (shift 0 unless the rectangle has more than kGroupTiles of them).  The
+// group's run of the list, from word `base` (a multiple of 4): per macro tile of the rectangle, row
+// by row, how many front-facing entries and, << 16, how many others come before its own, then both
+// totals in the same form; the front-facing entries (triangle ids); and, from the next multiple of 4
+// words, the others (records of 4 words).
+struct alignas(16) GroupRec {
+  uint16_t tx0, ty0, tw, th;   // tw = 0: reaches no bin
+  uint32_t base;               // kGroupNoRun: no room in the list, its bins go through all of its triangles
+  uint32_t shift;
+};
+constexpr uint32_t kGroupNoRun = 0xffffffffu;
+constexpr int kGroupTiles = 4096;
+constexpr uint32_t kSegAll = 0xf0000000u;   // a raster segment of all triangles from id base - kSegAll on; the list ends before it
+
+
+// Triangles per thread of a group's block: larger groups cost a bin fewer runs to go through, smaller
+// ones fill the chip.  One 1024^2 view of seven layers (696 groups of 1,024), binning and raster kernel
+// with one, two or four: 15.8 + 87, 15.4 + 74, 16.3 + 75 us; with eight, the metric scene takes 414 + 2639
+// us against 388 + 2660 with four, the k = 9 scene 1423 + 3261 against 1336 + 3452.
+inline int bin_reps(int64_t n_tri, int n_views) {
+  const int64_t groups = (n_tri + 1023) / 1024 * n_views;
+  return groups >= 2048 ? 4 : groups >= 300 ? 2 : 1;
 }
 
-// Block of 256 padded triangles that repetition r of this block handles.
-// Blocks are dealt round-robin to the 8 XCDs, and gridDim.x is a multiple of
-// 8, so blockIdx.x % 8 is the XCD: the remap gives each XCD a contiguous
-// eighth of the view's triangles (triangles that share vertices share that
-// XCD's L2).
-template <int R>
-__device__ inline uint32_t bin_block(int r) {
-  const uint32_t chunk = gridDim.x >> 3;
-  return ((blockIdx.x & 7u) * chunk + (blockIdx.x >> 3)) * R + r;
-}
-
-// Which (layer, triangle) of view blockIdx.y this thread handles in block vb;
-// g is the triangle's index over all layers of the view.  The layer is the
-// same on every lane of a wavefront, so the layer search and its table
-// entries are scalar.
-__device__ inline bool bin_thread(const LayerTable& L, uint32_t vb, int& l, int32_t& t, int64_t& g) {
-  const int k = L.k;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t gw = (int64_t)vb * 256 + wave * 64;   // the wavefront's first padded index
-  int lw = 0;
-  while (lw + 1 < k && L.tri_pad[lw + 1] <= gw) ++lw;
-  l = lw;
-  t = 0;
-  g = 0;
-  const int64_t gp = gw + (threadIdx.x & 63);
-  if (gp >= L.tri_pad[k]) return false;
-  t = (int32_t)(gp - L.tri_pad[l]);
-  if (t >= L.n_tri[l]) return false;   // padding
-  g = L.tri_off[l] + t;
-  return true;
-}
-
-// Bins of one view: (tile, layer) pairs, tile-major, starting at
-// tile_offset[slot] * k in the counters of all views (so a view's bin index
-// fits 32 bits: at most 1024^2 tiles times 16 layers).
-__device__ inline int64_t view_bins_base(const vs_view& V, int slot, int k) {
-  return (int64_t)V.tile_offset[slot] * k;
-}
-
-// Per triangle: reserve its place among the entries of its side (front-facing
-// or not) in its first bin, count it in its other bins, and record its box,
-// depth bound and that place.
-template <int B>
-__global__ void __launch_bounds__(256) k_bin_count(const vs_view* __restrict__ views, LayerTable L,
-                                                   const ProjVert* __restrict__ proj, int64_t vpv, int slot,
-                                                   uint32_t* __restrict__ count, uint32_t* __restrict__ cursor,
-                                                   SpanRec* __restrict__ spans,
-                                                   unsigned long long* __restrict__ status) {
-  constexpr int R = kCountReps;
+// One block per group.  Its triangles' tiles are counted in LDS, so that only the group's one
+// reservation of list space leaves the compute unit, and the counts' prefix sums give both the table
+// and every entry's place.  It replaces a count with atomics per triangle, three scan launches and a
+// scatter that read the records back: metric scene 1.49 -> 0.39 ms, k = 9 scene 3.61 -> 1.34 ms, one
+// 1024^2 view 99 -> 15 us (the raster kernel, which now looks the runs up, 2.36 -> 2.66 ms, 2.87 -> 3.45 ms and
+// 70 -> 74 us).
+template <int B, int R>
+__global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, LayerTable L, BinGroups Q,
+                                             const ProjVert* __restrict__ proj, int64_t vpv,
+                                             GroupRec* __restrict__ recs, uint32_t* __restrict__ list, uint32_t pool_words,
+                                             uint32_t* __restrict__ pools,
+                                             unsigned long long* __restrict__ status) {
   constexpr int BH = bin_rows(B);
+  __shared__ uint32_t hist[kGroupTiles];   // per macro tile: front entries, other entries << 16; then their next places
+  __shared__ int32_t ext[4][4];
+  __shared__ uint32_t sums[4][2];
+  __shared__ uint32_t run_base;
+  const int k = L.k, tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
+  // XCD-contiguous remap: blocks are dealt round-robin to the 8 XCDs and gridDim.x is a multiple of 8,
+  // so that triangles that share vertices share that XCD's L2
+  const int grp = (int)((blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+  if (grp >= Q.off[k]) return;
   const int v = blockIdx.y;
-  const int k = L.k;
+  int l = 0;
+  while (l + 1 < k && Q.off[l + 1] <= grp) ++l;
   const vs_view& V = views[v];
   const int W = V.cam.width, H = V.cam.height;
-  const int ntx = (W + B - 1) / B;
-  uint32_t* cv = count + view_bins_base(V, slot, k);
-  uint32_t* uv = cursor + 2 * view_bins_base(V, slot, k);   // per bin: front, other side
-  const ProjVert* pview = proj + (int64_t)v * vpv;
-  SpanRec* sview = spans + (int64_t)v * L.tri_off[k];
-  bool ok[R];
-  int l[R];
-  int32_t t[R];
-  int64_t g[R];
-  int3 ids[R];
+  const ProjVert* P = proj + (int64_t)v * vpv + L.vert_off[l];
+  const int32_t* tri = L.tri[l];
+  const int32_t n_vert = L.n_vert[l], n_tri = L.n_tri[l];
+  const int32_t t0 = (grp - Q.off[l]) * (256 * R) + tid;
+  GroupRec* rec = recs + (int64_t)v * Q.off[k] + grp;
   // ids of every repetition first (small); vertex records two at a time, the
   // next record's loads issued as soon as a record slot is free
+  int3 ids[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    ok[r] = bin_thread(L, bin_block<R>(r), l[r], t[r], g[r]);
     ids[r] = make_int3(0, 0, 0);
-    if (ok[r]) ids[r] = load_ids(L.tri[l[r]], (uint32_t)t[r]);
+    if (t0 + 256 * r < n_tri) ids[r] = load_ids(tri, (uint32_t)(t0 + 256 * r));
   }
   auto fetch = [&](int r, TriLoad& q) {
     // defined on every lane: left undefined, the records stay live across the
@@ -212,278 +205,147 @@ __global__ void __launch_bounds__(256) k_bin_count(const vs_view* __restrict__ v
     q.a = q.b = q.c = make_int4(0, 0, 0, 0);
     q.id[0] = q.id[1] = q.id[2] = 0;
     q.bad = false;
-    if (ok[r]) load_vertices(ids[r], L.n_vert[l[r]], pview + L.vert_off[l[r]], q);
+    if (t0 + 256 * r < n_tri) load_vertices(ids[r], n_vert, P, q);
   };
   TriLoad qa, qb;
   fetch(0, qa);
   if (R > 1) fetch(1, qb);
-  const int lane = (int)__lane_id();
-  const uint64_t lt = __lanemask_lt();
-  uint64_t boxes[R];   // the records' box and bound words (zero for a culled or off-screen triangle),
-  uint32_t zlos[R];    // written once the places are known
-  uint32_t base[R], rank[R];
-  int leader_of[R];
+  uint64_t box[R];
+  uint32_t zlo[R];
+  uint32_t live = 0, front = 0;
+  int32_t ex0 = INT32_MAX, ey0 = INT32_MAX, ex1 = -1, ey1 = -1;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     TriLoad& qr = (r & 1) ? qb : qa;
-    int tx0 = 0, tx1 = 0, ty0 = 0, ty1 = 0;
-    bool live = ok[r], front = false;
-    if (live) {
+    box[r] = 0;
+    zlo[r] = 0;
+    const int32_t t = t0 + 256 * r;
+    if (t < n_tri) {
       TriSetup T;
       const int st = setup_loaded(qr, T);
-      SpanRec span;
-      span.box = 0; span.zlo = 0; span.rank = 0;
       if (st != kTriOk) {
         atomicAdd(status + cull_slot(st), 1ull);
-        live = false;
       } else {
         const PixRange pr = pixel_range(T, W, H);
-        if (pr.i0 > pr.i1 || pr.j0 > pr.j1) {
-          live = false;
-        } else {
-          tx0 = pr.i0 / B; tx1 = pr.i1 / B; ty0 = pr.j0 / BH; ty1 = pr.j1 / BH;
-          front = T.orig_sign < 0;
-          span.box = pack_box(pr.i0, pr.i1, pr.j0, pr.j1, front);
-          span.zlo = (uint32_t)(depth_lower_key(T, (uint32_t)t[r]) >> 32);
+        if (pr.i0 <= pr.i1 && pr.j0 <= pr.j1) {
+          const int tx0 = pr.i0 / B, tx1 = pr.i1 / B, ty0 = pr.j0 / BH, ty1 = pr.j1 / BH;
+          box[r] = pack_box(pr.i0, pr.i1, pr.j0, pr.j1);
+          zlo[r] = (uint32_t)(depth_lower_key(T, (uint32_t)t) >> 32);
+          ex0 = min(ex0, tx0); ey0 = min(ey0, ty0); ex1 = max(ex1, tx1); ey1 = max(ey1, ty1);
+          live |= 1u << r;
+          if (T.orig_sign < 0) front |= 1u << r;
         }
       }
-      boxes[r] = span.box;
-      zlos[r] = span.zlo;
     }
     if (r + 2 < R) fetch(r + 2, qr);   // this record slot is free now
-    // first bin of every lane, and its side: lanes of the same (bin, side) class
-    // elect one lane (register exchanges only), which reserves their places
-    // among the bin's entries of that side (the scan adds these reservations to
-    // the bin's count); every lane's place is the reservation plus its rank
-    const int32_t b0 = live ? (ty0 * ntx + tx0) * k + l[r] : -1;
-    const int32_t c0 = live ? 2 * b0 + (front ? 0 : 1) : -1;
-    uint64_t active = __ballot(c0 >= 0);
-    uint32_t group = 0;
-    rank[r] = 0;
-    leader_of[r] = lane;
-    while (active) {
-      const int leader = (int)__builtin_ctzll(active);
-      const int32_t lc = __builtin_amdgcn_readlane(c0, leader);
-      const uint64_t same = __ballot(c0 == lc);
-      if (c0 == lc) {
-        leader_of[r] = leader;
-        rank[r] = (uint32_t)__popcll(same & lt);
-      }
-      if (lane == leader) group = (uint32_t)__popcll(same);
-      active &= ~same;
-    }
-    base[r] = 0;
-    if (group) base[r] = atomicAdd(uv + c0, group);
-    if (live) {
-      for (int ty = ty0; ty <= ty1; ++ty)
-        for (int tx = tx0; tx <= tx1; ++tx) {
-          if (ty == ty0 && tx == tx0) continue;
-          atomicAdd(cv + (ty * ntx + tx) * k + l[r], 1u);
-        }
-    }
   }
-  // the reservations of every repetition were in flight together; each record
-  // is written once (a 16-byte store), with its place
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const uint32_t e = __shfl(base[r], leader_of[r]) + rank[r];
-    if (ok[r]) {
-      SpanRec span;
-      span.box = boxes[r];
-      span.zlo = zlos[r];
-      span.rank = e;
-      sview[g[r]] = span;
-    }
+  // the group's rectangle of tiles
+  ex0 = wave_min(ex0); ey0 = wave_min(ey0); ex1 = wave_max(ex1); ey1 = wave_max(ey1);
+  if (lane == 0) {
+    ext[wv][0] = ex0; ext[wv][1] = ey0; ext[wv][2] = ex1; ext[wv][3] = ey1;
   }
-}
-
-// Exclusive scan of the per-bin entry counts into 64-bit list offsets (the
-// total can pass 2^32 when triangles cover many bins; a bin's own count stays
-// below 2^30 because n_views * triangles does).
-// Pass 1: each block takes 1024 bins.  A bin's entries are those counted in
-// count (triangles for which it is not the first bin) plus the places its
-// first-bin triangles reserved on both sides (first[2 b], first[2 b + 1]);
-// the sum is written back to count, then the local prefixes and the block's
-// total.
-__global__ void __launch_bounds__(256) k_scan_local(uint32_t* __restrict__ count, const uint32_t* __restrict__ first,
-                                                    uint64_t* __restrict__ out, uint64_t* __restrict__ partial,
-                                                    int64_t n) {
-  __shared__ uint64_t s[256];
-  const int tid = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * 1024 + tid * 4;
-  uint32_t v[4];
-  uint64_t sum = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    v[q] = base + q < n ? count[base + q] + first[2 * (base + q)] + first[2 * (base + q) + 1] : 0u;
-    if (base + q < n) count[base + q] = v[q];
-    sum += v[q];
-  }
-  s[tid] = sum;
   __syncthreads();
-  for (int off = 1; off < 256; off <<= 1) {
-    const uint64_t add = tid >= off ? s[tid - off] : 0u;
-    __syncthreads();
-    s[tid] += add;
-    __syncthreads();
-  }
-  uint64_t run = s[tid] - sum;  // exclusive prefix of this thread
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (base + q < n) out[base + q] = run;
-    run += v[q];
+  for (int w = 0; w < 4; ++w) {
+    ex0 = min(ex0, ext[w][0]); ey0 = min(ey0, ext[w][1]); ex1 = max(ex1, ext[w][2]); ey1 = max(ey1, ext[w][3]);
   }
-  if (tid == 255) partial[blockIdx.x] = s[255];
-}
-
-// Pass 2: one block scans the block totals in place (exclusive), carrying across chunks.
-__global__ void __launch_bounds__(1024) k_scan_partials(uint64_t* __restrict__ partial, int64_t n) {
-  __shared__ uint64_t s[1024];
-  __shared__ uint64_t carry;
-  const int tid = threadIdx.x;
-  if (tid == 0) carry = 0;
+  ex0 = __builtin_amdgcn_readfirstlane(ex0); ey0 = __builtin_amdgcn_readfirstlane(ey0);
+  ex1 = __builtin_amdgcn_readfirstlane(ex1); ey1 = __builtin_amdgcn_readfirstlane(ey1);
+  GroupRec out;
+  out.tx0 = out.ty0 = out.tw = out.th = 0;
+  out.base = kGroupNoRun;
+  out.shift = 0;
+  if (ex1 < ex0) {   // uniform
+    if (tid == 0) *rec = out;
+    return;
+  }
+  int s = 0;
+  while (((ex1 >> s) - (ex0 >> s) + 1) * ((ey1 >> s) - (ey0 >> s) + 1) > kGroupTiles) ++s;
+  const int rx = ex0 >> s, ry = ey0 >> s, tw = (ex1 >> s) - rx + 1, th = (ey1 >> s) - ry + 1, n = tw * th;
+  for (int e = tid; e < n; e += 256) hist[e] = 0;
   __syncthreads();
-  for (int64_t base = 0; base < n; base += 1024) {
-    const uint64_t v = base + tid < n ? partial[base + tid] : 0u;
-    s[tid] = v;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-      const uint64_t add = tid >= off ? s[tid - off] : 0u;
-      __syncthreads();
-      s[tid] += add;
-      __syncthreads();
-    }
-    if (base + tid < n) partial[base + tid] = carry + s[tid] - v;
-    __syncthreads();
-    if (tid == 1023) carry += s[1023];
-    __syncthreads();
-  }
-}
-
-// Pass 3: add the block prefixes.
-__global__ void __launch_bounds__(256) k_scan_add(uint64_t* __restrict__ out, const uint64_t* __restrict__ partial,
-                                                  int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] += partial[i / 1024];
-}
-
-// Write triangle ids into the bin lists: front-facing triangles from the
-// head of a bin's list, the others from its tail.  A triangle's place in its
-// first bin (most triangles have only one) was reserved by the count, so it
-// takes no atomic here; its other bins are reserved here, after every
-// first-bin entry of the same side.  A bin whose list would end
-// past the capacity is left unwritten; the raster of that bin then scans every
-// triangle of its layer instead (slow but exact) and the overflow is counted.
-template <int B>
-__global__ void __launch_bounds__(256) k_bin_scatter(const vs_view* __restrict__ views, LayerTable L, int slot,
-                                                     const SpanRec* __restrict__ spans,
-                                                     const uint32_t* __restrict__ count,
-                                                     const uint64_t* __restrict__ offset,
-                                                     uint32_t* __restrict__ cursor, int32_t* __restrict__ list,
-                                                     uint64_t capacity) {
-  constexpr int R = kScatterReps;
-  constexpr int BH = bin_rows(B);
-  const int v = blockIdx.y;
-  const int k = L.k;
-  const vs_view& V = views[v];
-  const int ntx = (V.cam.width + B - 1) / B;
-  const int64_t vb = view_bins_base(V, slot, k);
-  const uint32_t* cv = count + vb;
-  const uint64_t* ov = offset + vb;
-  uint32_t* uv = cursor + 2 * vb;   // per bin: [2 b] front entries from the head, [2 b + 1] the others from the tail
-  const SpanRec* sview = spans + (int64_t)v * L.tri_off[k];
-  bool ok[R];
-  int l[R];
-  int32_t t[R];
-  int64_t g[R];
-  uint64_t span[R];
-  uint32_t rank[R];
+  // each (triangle, macro tile): use(its histogram word, what to add to it)
+  auto each = [&](auto use) {
 #pragma unroll
-  for (int r = 0; r < R; ++r) {
-    ok[r] = bin_thread(L, bin_block<R>(r), l[r], t[r], g[r]);
-    uint4 rec = make_uint4(0u, 0u, 0u, 0u);
-    if (ok[r]) rec = reinterpret_cast<const uint4*>(sview)[g[r]];
-    span[r] = (uint64_t)rec.x | ((uint64_t)rec.y << 32);
-    rank[r] = rec.w;
-  }
-  // the first bins' list ranges, all in flight together
-  int32_t b0[R];
-  uint64_t off[R];
-  uint32_t cnt[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    ok[r] = ok[r] && (span[r] & kSpanValid);
-    b0[r] = -1;
-    off[r] = 0;
-    cnt[r] = 0;
-    if (ok[r]) {
+    for (int r = 0; r < R; ++r) {
+      if (!((live >> r) & 1u)) continue;
       int i0, i1, j0, j1;
-      unpack_box(span[r], i0, i1, j0, j1);
-      b0[r] = ((j0 / BH) * ntx + i0 / B) * k + l[r];
-      off[r] = ov[b0[r]];
-      cnt[r] = cv[b0[r]];
+      unpack_box(box[r], i0, i1, j0, j1);
+      const int x0 = (i0 / B) >> s, y0 = (j0 / BH) >> s, x1 = (i1 / B) >> s, y1 = (j1 / BH) >> s;
+      const bool f = (front >> r) & 1u;
+      for (int y = y0; y <= y1; ++y)
+        for (int x = x0; x <= x1; ++x) use(r, &hist[(y - ry) * tw + (x - rx)], f);
+    }
+  };
+  each([&](int, uint32_t* h, bool f) { atomicAdd(h, f ? 1u : 0x10000u); });
+  __syncthreads();
+  // exclusive prefix sums over the tiles, `per` consecutive ones per thread
+  const int per = (n + 255) / 256, e0 = min(tid * per, n), e1 = min(e0 + per, n);
+  uint32_t mine_f = 0, mine_o = 0;
+  for (int e = e0; e < e1; ++e) {
+    mine_f += hist[e] & 0xffffu;
+    mine_o += hist[e] >> 16;
+  }
+  uint32_t f = mine_f, o = mine_o;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t fb = __shfl_up(f, off), ob = __shfl_up(o, off);
+    if (lane >= off) {
+      f += fb;
+      o += ob;
     }
   }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    if (!ok[r]) continue;
-    const bool front = (span[r] & kSpanFront) != 0;
-    const uint64_t end = off[r] + cnt[r];
-    // first bin: the place reserved by the count
-    if (end <= capacity) list[front ? off[r] + rank[r] : end - 1 - rank[r]] = t[r];
-    // the span's other bins, four at a time: their list ranges and reservations
-    // are all in flight before any entry is written
-    int i0, i1, j0, j1;
-    unpack_box(span[r], i0, i1, j0, j1);
-    const int tx0 = i0 / B, tx1 = i1 / B, ty0 = j0 / BH, ty1 = j1 / BH;
-    int tx = tx0, ty = ty0;   // the bin before the next one to take
-    int left = (tx1 - tx0 + 1) * (ty1 - ty0 + 1) - 1;
-    while (left > 0) {
-      int32_t bq[4];
-      uint64_t oq[4];
-      uint32_t cq[4], rq[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        bq[e] = -1;
-        if (e < left) {
-          if (++tx > tx1) {
-            tx = tx0;
-            ++ty;
-          }
-          bq[e] = (ty * ntx + tx) * k + l[r];
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        oq[e] = 0;
-        cq[e] = 0;
-        rq[e] = 0;
-        if (bq[e] >= 0) {
-          oq[e] = ov[bq[e]];
-          cq[e] = cv[bq[e]];
-          rq[e] = atomicAdd(uv + 2 * bq[e] + (front ? 0 : 1), 1u);
-        }
-      }
-      // one wait for all four reservations (the empty statement uses them on every
-      // lane), so that the stores below issue back to back
-      __asm__ volatile("" ::"v"(rq[0]), "v"(rq[1]), "v"(rq[2]), "v"(rq[3]), "v"(cq[0]), "v"(cq[1]), "v"(cq[2]),
-                       "v"(cq[3]));
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint64_t bend = oq[e] + cq[e];
-        if (bq[e] >= 0 && bend <= capacity) list[front ? oq[e] + rq[e] : bend - 1 - rq[e]] = t[r];
-      }
-      left -= 4;
-    }
+  if (lane == 63) {
+    sums[wv][0] = f;
+    sums[wv][1] = o;
   }
-}
-
-// tile_view[g] = view owning tile g of the given tile-size slot.
-__global__ void __launch_bounds__(256) k_tile_view_slot(const vs_view* __restrict__ views, int n_views,
-                                                        int32_t* __restrict__ tile_view, int64_t n_tiles, int slot) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n_tiles) return;
-  tile_view[g] = find_view_tile(views, n_views, g, slot);
+  __syncthreads();
+  f -= mine_f;
+  o -= mine_o;
+  uint32_t total_f = 0, total_o = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    f += w < wv ? sums[w][0] : 0u;
+    o += w < wv ? sums[w][1] : 0u;
+    total_f += sums[w][0];
+    total_o += sums[w][1];
+  }
+  const uint32_t others = ((uint32_t)n + 1u + total_f + 3u) & ~3u, need = others + 4u * total_o;   // words
+  if (tid == 0) {
+    uint32_t base = kGroupNoRun;
+    if (total_f <= 0xffffu && total_o <= 0xffffu) {
+      for (int q = 0; q < kPools && base == kGroupNoRun; ++q) {
+        const uint32_t p = (uint32_t)v * kPools + ((blockIdx.x + q) & (kPools - 1));
+        if (need > pool_words) break;
+        const uint32_t from = atomicAdd(&pools[p * kPoolApart], need);
+        if (from <= pool_words - need) base = p * pool_words + from;
+      }
+    }
+    run_base = base;
+    out.tx0 = (uint16_t)rx; out.ty0 = (uint16_t)ry; out.tw = (uint16_t)tw; out.th = (uint16_t)th;
+    out.base = base;
+    out.shift = (uint32_t)s;
+    *rec = out;
+  }
+  __syncthreads();
+  const uint32_t base = run_base;
+  if (base == kGroupNoRun) return;   // uniform
+  for (int e = e0; e < e1; ++e) {
+    const uint32_t c = hist[e], places = f | (o << 16);
+    list[base + e] = places;
+    hist[e] = places;
+    f += c & 0xffffu;
+    o += c >> 16;
+  }
+  if (tid == 0) list[base + n] = total_f | (total_o << 16);
+  __syncthreads();
+  uint32_t* fronts = list + base + n + 1;
+  uint4* rest = reinterpret_cast<uint4*>(list + base + others);
+  each([&](int r, uint32_t* h, bool is_front) {
+    const uint32_t old = atomicAdd(h, is_front ? 1u : 0x10000u), t = (uint32_t)(t0 + 256 * r);
+    if (is_front) fronts[old & 0xffffu] = t;
+    else rest[old >> 16] = make_uint4((uint32_t)box[r], (uint32_t)(box[r] >> 32), zlo[r], t);
+  });
 }
 
 __device__ inline int4 readlane4(int4 v, int lane) {
@@ -502,7 +364,7 @@ __device__ inline int4 readlane4(int4 v, int lane) {
 // Wavefronts work independently on the LDS tile (64-bit atomic minimum).
 // Against one lane per triangle and larger ones tested over the whole tile by
 // the wavefront that met them: metric scene 3.11 -> 2.36 ms, k = 9 scene 2.95 ->
-// 2.87 ms, a single 1024^2 view 92 -> 70 us, coarse shells (k = 7, 25,280
+// 2.87 ms (before the bins' lists became runs of groups), a single 1024^2 view 92 -> 70 us, coarse shells (k = 7, 25,280
 // triangles a layer, 16 views at 1000^2) 3.50 -> 0.71 ms, a 256^2 view of
 // 1,292-triangle shells 234 -> 42 us.  Sharing only chunks of at most 64 or 32
 // triangles: metric 2.75 and 3.07 ms; two or four lanes per triangle in full
@@ -520,11 +382,10 @@ __device__ inline int4 readlane4(int4 v, int lane) {
 // fragment counting on, nothing is skipped (the count covers every covered
 // pixel of every triangle).
 template <int B>
-__global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
-    const vs_view* __restrict__ views, const int32_t* __restrict__ bin_view, int64_t n_tiles, LayerTable L,
-    const ProjVert* __restrict__ proj, int64_t vpv, int slot, const uint32_t* __restrict__ count,
-    const uint64_t* __restrict__ offset, const uint32_t* __restrict__ cursor, const int32_t* __restrict__ list,
-    const SpanRec* __restrict__ spans, uint64_t capacity, unsigned long long* __restrict__ vis,
+__global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
+    const vs_view* __restrict__ views, const int32_t* __restrict__ bin_view, int64_t n_tiles, LayerTable L, BinGroups Q,
+    int group_log, const ProjVert* __restrict__ proj, int64_t vpv, int slot, const GroupRec* __restrict__ recs,
+    const uint32_t* __restrict__ list, unsigned long long* __restrict__ vis,
     unsigned long long* __restrict__ status, int count_frags) {
   constexpr int BH = bin_rows(B);              // bin rows
   constexpr int kSub = B < 8 ? B : 8;          // sub-tile edge of the depth bound
@@ -532,10 +393,15 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
   constexpr int kNsY = BH / kSub;              // sub-tile rows
   static_assert(B % kSub == 0 && BH % kSub == 0, "bins must be whole sub-tiles");
   __shared__ __align__(16) unsigned long long tile[B * BH];
-  __shared__ unsigned long long smax[kNs * kNsY];
+  __shared__ uint32_t smax[kNs * kNsY];   // per sub-tile, the depth word of its largest key
   __shared__ int32_t queue[2 * kRasterThreads];   // back-facing triangles that may lower a key
-  __shared__ int32_t bigs[kBigQueue];             // large triangles, left for the whole block
+  __shared__ int32_t late_bigs[kBigQueue];        // large triangles among those (large front-facing ones: in the queue)
   __shared__ uint32_t qn, bign;
+  __shared__ uint32_t seg_base[kSegs];            // groups that reach the tile: list word of their first front-facing entry here
+  __shared__ uint32_t seg_rest[kSegs];            // ... 16-byte record of their first other entry
+  __shared__ uint32_t seg_start[kSegs];           // ... and the entries before it, front-facing ones and others << 16
+  __shared__ uint32_t seg_n[3];                   // groups, front-facing entries, other entries
+  __shared__ uint32_t wave_n[kRasterThreads / 64];
   const int k = L.k;
   const int64_t n_bins = n_tiles * k;
   // XCD-contiguous remap of the block index
@@ -559,14 +425,98 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
   const ProjVert* P = proj + (int64_t)v * vpv + L.vert_off[l];
   const int32_t* tri = L.tri[l];
   const int32_t nvert = L.n_vert[l];
-  const uint32_t cnt = count[bid];
-  const bool overflow = offset[bid] + cnt > capacity;
-  const uint32_t n = overflow ? (uint32_t)L.n_tri[l] : cnt;
-  const int32_t* lst = list + (overflow ? 0 : offset[bid]);
-  const SpanRec* srec = spans + (int64_t)v * L.tri_off[k] + L.tri_off[l];   // records of this view and layer
-  // front-facing entries head the list (an overflowing bin scans its whole layer in one phase)
-  const uint32_t n_front = (overflow || count_frags) ? n : min(cursor[2 * bid], cnt);
+  const GroupRec* grec = recs + (int64_t)v * Q.off[k] + Q.off[l];
+  const int n_groups = Q.off[l + 1] - Q.off[l], n_tri = L.n_tri[l];
+  bool overflow = false;   // a group without a run reaches this tile
   unsigned long long frags = 0;
+  // Loads the groups from g0 on that reach this tile, as many as kSegs holds, and returns the group to go
+  // on from.  All triangles of a group without a run are taken for front-facing: nothing is skipped then.
+  // Called by the whole block.
+  auto load_segs = [&](int g0) -> int {
+    int have = 0;
+    while (g0 < n_groups) {   // uniform: 256 groups at a time, 64 where more than kSegs of those reach the tile
+      uint32_t base = 0, rest = 0, nf = 0, nb = 0;
+      if (g0 + tid < n_groups) {
+        const uint4 raw = *reinterpret_cast<const uint4*>(grec + g0 + tid);
+        const int mx = (tx >> raw.w) - (int)(raw.x & 0xffffu), my = (ty >> raw.w) - (int)(raw.x >> 16);
+        const int tw = (int)(raw.y & 0xffffu), th = (int)(raw.y >> 16);
+        if (mx >= 0 && mx < tw && my >= 0 && my < th) {
+          if (raw.z == kGroupNoRun) {
+            base = kSegAll + ((uint32_t)(g0 + tid) << group_log);
+            nf = (uint32_t)min(1 << group_log, n_tri - ((g0 + tid) << group_log));
+          } else {
+            const uint32_t* starts = list + raw.z + my * tw + mx;
+            const uint32_t at = starts[0], next = starts[1];
+            const uint32_t ids = raw.z + (uint32_t)(tw * th) + 1u, total_f = list[ids - 1u] & 0xffffu;
+            base = ids + (at & 0xffffu);
+            nf = (next & 0xffffu) - (at & 0xffffu);
+            rest = ((ids + total_f + 3u) >> 2) + (at >> 16);
+            nb = (next >> 16) - (at >> 16);
+          }
+        }
+      }
+      bool hit = nf + nb > 0;
+      int width = kRasterThreads, m = __syncthreads_count(hit);
+      if (have + m > kSegs) {
+        if (have > 0) break;
+        width = kSegs;
+        hit = hit && tid < kSegs;
+        m = __syncthreads_count(hit);
+      }
+      const uint64_t hits = __ballot(hit);
+      if (lane == 0) wave_n[tid >> 6] = (uint32_t)__popcll(hits);
+      __syncthreads();
+      if (hit) {
+        uint32_t at = (uint32_t)have + (uint32_t)__popcll(hits & __lanemask_lt());
+        for (int w = 0; w < (tid >> 6); ++w) at += wave_n[w];
+        seg_base[at] = base;
+        seg_rest[at] = rest;
+        seg_start[at] = nf | (nb << 16);
+      }
+      have += m;
+      g0 += width;
+      if (width < kRasterThreads) break;
+    }
+    __syncthreads();
+    if (tid < 64) {   // one wavefront sums the entries up
+      const uint32_t c = lane < have ? seg_start[lane] : 0u;
+      uint32_t f = c & 0xffffu, o = c >> 16;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t fb = __shfl_up(f, off), ob = __shfl_up(o, off);
+        if (lane >= off) {
+          f += fb;
+          o += ob;
+        }
+      }
+      if (lane < have) seg_start[lane] = (f - (c & 0xffffu)) | ((o - (c >> 16)) << 16);
+      if (lane == 63) {
+        seg_n[0] = (uint32_t)have;
+        seg_n[1] = f;
+        seg_n[2] = o;
+      }
+    }
+    __syncthreads();
+    return g0;
+  };
+  // The loaded group that holds front-facing (shift 0) or other (shift 16) entry c: the last one that
+  // starts at or before c (one without such entries starts where the next does).
+  auto find_seg = [&](uint32_t c, int shift) {
+    uint32_t a = 0, b = seg_n[0] - 1;
+    while (a < b) {
+      const uint32_t mid = (a + b + 1) / 2;
+      if (((seg_start[mid] >> shift) & 0xffffu) <= c) a = mid; else b = mid - 1;
+    }
+    return a;
+  };
+  auto front_entry = [&](uint32_t c) -> int32_t {
+    const uint32_t a = find_seg(c, 0), at = seg_base[a] + c - (seg_start[a] & 0xffffu);
+    return at >= kSegAll ? (int32_t)(at - kSegAll) : (int32_t)list[at];
+  };
+  auto other_entry = [&](uint32_t c) -> uint4 {
+    const uint32_t a = find_seg(c, 16);
+    return reinterpret_cast<const uint4*>(list)[seg_rest[a] + c - (seg_start[a] >> 16)];
+  };
   __syncthreads();
   // Triangles drawn by the whole wavefront, one after the other: every lane's triangle (big < 0:
   // none) is loaded at once, so that the wavefront waits for memory once, and handed round.  For
@@ -617,6 +567,9 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
       }
     }
   };
+  // where large triangles wait: front-facing ones in the queue, which is free until the others come
+  int32_t* bigs = queue;
+  uint32_t big_cap = kRasterThreads;
   // A triangle for the whole wavefront rather than one lane (its box clipped to the bin is i0..i1 x j0..j1).
   auto is_big = [&](const TriSetup& T, int i0, int i1, int j0, int j1) {
     const double spanx = fmax(T.X[0], fmax(T.X[1], T.X[2])) - fmin(T.X[0], fmin(T.X[1], T.X[2]));
@@ -664,25 +617,27 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
           }
         } else if (part == 0) {
           const uint32_t at = atomicAdd(&bign, 1u);
-          if (at < kBigQueue) bigs[at] = t;
+          if (at < big_cap) bigs[at] = t;
         }
       }
     }
   };
-  // Draw the large triangles that draw() met among entries c0..c1, dealt round the wavefronts; if they
-  // were more than the queue holds, the entries are gone through again.  Called by the whole block.
-  auto flush_bigs = [&](uint32_t c0, uint32_t c1) {
+  // Draw the large triangles that draw() met among the loaded groups' entries of one side, dealt round the
+  // wavefronts; if they were more than the queue holds, the entries are gone through again.  Called by the
+  // whole block.
+  auto flush_bigs = [&](bool fronts) {
     __syncthreads();
     const uint32_t nb = bign;
     if (nb == 0) return;   // uniform
     const uint32_t dealt = lane * (kRasterThreads / 64) + (tid >> 6);
-    if (nb <= kBigQueue) {
+    if (nb <= big_cap) {
       draw_bigs(dealt < nb ? bigs[dealt] : -1);
     } else {
-      for (uint32_t c = c0; c < c1; c += kRasterThreads) {
+      const uint32_t n = fronts ? seg_n[1] : seg_n[2];
+      for (uint32_t c = 0; c < n; c += kRasterThreads) {
         int32_t t = -1;
-        if (c + dealt < c1) {
-          const int32_t tc = overflow ? (int32_t)(c + dealt) : lst[c + dealt];
+        if (c + dealt < n) {
+          const int32_t tc = fronts ? front_entry(c + dealt) : (int32_t)other_entry(c + dealt).w;
           TriSetup T;
           if (setup_triangle<true>(tri, (uint32_t)tc, nvert, P, T) == kTriOk) {
             const PixRange pr = pixel_range(T, W, H);
@@ -696,21 +651,26 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
     __syncthreads();
     if (tid == 0) bign = 0;
   };
-  // The first two chunks of back-facing entries and their records are requested before the
-  // front-facing phase, so that their latency hides behind it.
-  const uint4* srec4 = reinterpret_cast<const uint4*>(srec);
-  const uint32_t cp0 = n_front + tid, cp1 = n_front + kRasterThreads + tid;
-  const int32_t pt0 = cp0 < n ? lst[cp0] : -1, pt1 = cp1 < n ? lst[cp1] : -1;
-  const uint4 pr0 = pt0 >= 0 ? srec4[pt0] : make_uint4(0u, 0u, 0u, 0u);
-  const uint4 pr1 = pt1 >= 0 ? srec4[pt1] : make_uint4(0u, 0u, 0u, 0u);
-  // phase 1: front-facing entries (every entry of an overflowing bin, or with fragment counting)
-  for (uint32_t c0 = 0; c0 < n_front; c0 += kRasterThreads) {
-    const int sh = share(n_front - c0);
-    const uint32_t c = c0 + (tid >> sh);
-    draw(c < n_front ? (overflow ? (int32_t)c : lst[c]) : -1, tid & ((1 << sh) - 1), 1 << sh);
+  // phase 1: front-facing entries
+  bool one_load = false, any_back = false;   // uniform
+  for (int g0 = 0; g0 < n_groups;) {
+    const int next = load_segs(g0);
+    one_load = g0 == 0 && next >= n_groups;
+    g0 = next;
+    const uint32_t n_front = seg_n[1], n_back = seg_n[2];
+    any_back = any_back || n_back > 0;
+    if (tid < (int)seg_n[0]) overflow = overflow || seg_base[tid] >= kSegAll;
+    for (uint32_t c0 = 0; c0 < n_front; c0 += kRasterThreads) {
+      const int sh = share(n_front - c0);
+      const uint32_t c = c0 + (tid >> sh);
+      draw(c < n_front ? front_entry(c) : -1, tid & ((1 << sh) - 1), 1 << sh);
+    }
+    flush_bigs(true);
+    if (!one_load) __syncthreads();   // the groups are loaded anew
   }
-  flush_bigs(0, n_front);
-  if (n_front < n) {   // uniform: back-facing entries follow
+  if (any_back) {   // uniform: back-facing entries follow
+    bigs = late_bigs;
+    big_cap = kBigQueue;
     __syncthreads();
     {
       // sub-tile maxima without LDS atomics: the kThr consecutive lanes of a sub-tile
@@ -730,55 +690,55 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
         }
 #pragma unroll
         for (int off = kThr / 2; off > 0; off >>= 1) m = max(m, (unsigned long long)__shfl_xor(m, off));
-        if (u == 0) smax[sub] = m;
+        if (u == 0) smax[sub] = (uint32_t)(m >> 32);
       }
     }
     __syncthreads();
     // phase 2: each back-facing entry is tested from its record (box and depth bound) alone;
     // the ones that may lower a key are queued in LDS and drawn 256 at a time, so that the
     // skipped majority costs no vertex loads and leaves no idle lanes behind.
-    for (uint32_t c0 = n_front, chunk = 0; c0 < n; c0 += kRasterThreads, ++chunk) {
-      const uint32_t c = c0 + tid;
-      bool keep = false;
-      int32_t t = 0;
-      if (c < n) {
-        uint4 r;
-        if (chunk < 2) {   // uniform
-          t = chunk == 0 ? pt0 : pt1;
-          r = chunk == 0 ? pr0 : pr1;
-        } else {
-          t = lst[c];
-          r = srec4[t];
+    for (int g0 = 0; g0 < n_groups;) {
+      g0 = one_load ? n_groups : load_segs(g0);
+      const uint32_t n = seg_n[2];
+      for (uint32_t c0 = 0; c0 < n; c0 += kRasterThreads) {
+        const uint32_t c = c0 + tid;
+        bool keep = false;
+        int32_t t = 0;
+        if (c < n) {
+          const uint4 r = other_entry(c);
+          t = (int32_t)r.w;
+          keep = count_frags != 0;   // every covered pixel is counted then: nothing is skipped
+          int i0, i1, j0, j1;
+          unpack_box((uint64_t)r.x | ((uint64_t)r.y << 32), i0, i1, j0, j1);
+          const int ci0 = max(i0, x0), ci1 = min(i1, x1), cj0 = max(j0, y0), cj1 = min(j1, y1);
+          if (ci0 <= ci1 && cj0 <= cj1)   // an entry of a macro tile may lie in other bins of it only
+            for (int sj = (cj0 - y0) / kSub; sj <= (cj1 - y0) / kSub; ++sj)
+              for (int si = (ci0 - x0) / kSub; si <= (ci1 - x0) / kSub; ++si)
+                keep = keep || smax[sj * kNs + si] >= r.z;
         }
-        int i0, i1, j0, j1;
-        unpack_box((uint64_t)r.x | ((uint64_t)r.y << 32), i0, i1, j0, j1);
-        const unsigned long long lb = ((unsigned long long)r.z << 32) | (uint32_t)t;
-        const int ci0 = max(i0, x0), ci1 = min(i1, x1), cj0 = max(j0, y0), cj1 = min(j1, y1);
-        for (int sj = (cj0 - y0) / kSub; sj <= (cj1 - y0) / kSub; ++sj)
-          for (int si = (ci0 - x0) / kSub; si <= (ci1 - x0) / kSub; ++si)
-            keep = keep || smax[sj * kNs + si] > lb;
-      }
-      const uint64_t kb = __ballot(keep);
-      uint32_t base = 0;
-      if (lane == 0 && kb) base = atomicAdd(&qn, (uint32_t)__popcll(kb));
-      base = __builtin_amdgcn_readfirstlane(base);
-      if (keep) queue[base + (uint32_t)__popcll(kb & __lanemask_lt())] = t;
-      __syncthreads();
-      uint32_t q = qn;
-      const bool last = c0 + kRasterThreads >= n;
-      while (q >= kRasterThreads || (last && q > 0)) {   // uniform
-        const int sh = share(q), e = tid >> sh;
-        draw(e < (int)q ? queue[e] : -1, tid & ((1 << sh) - 1), 1 << sh);
-        const uint32_t rest = q > kRasterThreads ? q - kRasterThreads : 0;
-        const int32_t moved = tid < (int)rest ? queue[kRasterThreads + tid] : 0;
+        const uint64_t kb = __ballot(keep);
+        uint32_t base = 0;
+        if (lane == 0 && kb) base = atomicAdd(&qn, (uint32_t)__popcll(kb));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (keep) queue[base + (uint32_t)__popcll(kb & __lanemask_lt())] = t;
         __syncthreads();
-        if (tid < (int)rest) queue[tid] = moved;
-        if (tid == 0) qn = rest;
-        __syncthreads();
-        q = rest;
+        uint32_t q = qn;
+        const bool last = c0 + kRasterThreads >= n;
+        while (q >= kRasterThreads || (last && q > 0)) {   // uniform
+          const int sh = share(q), e = tid >> sh;
+          draw(e < (int)q ? queue[e] : -1, tid & ((1 << sh) - 1), 1 << sh);
+          const uint32_t rest = q > kRasterThreads ? q - kRasterThreads : 0;
+          const int32_t moved = tid < (int)rest ? queue[kRasterThreads + tid] : 0;
+          __syncthreads();
+          if (tid < (int)rest) queue[tid] = moved;
+          if (tid == 0) qn = rest;
+          __syncthreads();
+          q = rest;
+        }
       }
+      flush_bigs(false);
+      if (!one_load) __syncthreads();   // the groups are loaded anew
     }
-    flush_bigs(n_front, n);
   }
   __syncthreads();
   // coalesced store of the finished tile: pairs of keys as 16-byte stores when
@@ -805,7 +765,7 @@ __global__ void __launch_bounds__(kRasterThreads) k_raster_bins(
     for (int off = 32; off > 0; off >>= 1) frags += __shfl_xor(frags, off);
     if ((tid & 63) == 0 && frags) atomicAdd(status + VS_STAT_FRAGMENTS, frags);
   }
-  if (tid == 0 && overflow) atomicAdd(status + VS_STAT_BIN_OVERFLOW, 1ull);
+  if (__syncthreads_or(overflow) && tid == 0) atomicAdd(status + VS_STAT_BIN_OVERFLOW, 1ull);
 }
 
 // Steps 2-3, direct form (reference path for tests): one thread per (view,

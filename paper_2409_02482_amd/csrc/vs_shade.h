@@ -177,14 +177,6 @@ __host__ __device__ inline int64_t shade_grid_blocks(int64_t n_tiles, int tiles 
   return ((n_tiles + kNumXcd - 1) / kNumXcd + tiles - 1) / tiles * kNumXcd;
 }
 
-// tile_view[g] = view owning 16-pixel tile g.
-__global__ void __launch_bounds__(256) k_tile_view(const vs_view* __restrict__ views, int n_views,
-                                                   int32_t* __restrict__ tile_view, int64_t n_tiles) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n_tiles) return;
-  tile_view[g] = find_view_tile(views, n_views, g, kShadeTileSlot);
-}
-
 // Forward: one thread per pixel, layers front to back.
 __global__ void __launch_bounds__(256) k_shade_fwd(const vs_view* __restrict__ views, int n_views,
                                                    const int32_t* __restrict__ tile_view,
@@ -233,32 +225,6 @@ __global__ void __launch_bounds__(256) k_shade_fwd(const vs_view* __restrict__ v
     if (eps_T > 0.f && __all(T < eps_T)) break;
   }
   if (c.valid) out[V.pix_offset + pix] = make_float4(Cr, Cg, Cb, 1.0f - T);
-}
-
-// Wavefront min / max without the LDS pipe: inclusive row scans with DPP
-// row shifts (row_shr:n moves lane i - n into lane i; lanes with no source
-// keep the identity), so lane 15 of each 16-lane row holds the row's result.
-// Call with every lane active.
-// Then row_bcast:15 (rows 1 and 3 take lane 15 / 47) and row_bcast:31 (rows 2 and 3
-// take lane 31) carry the row results to lane 63.
-__device__ inline int32_t wave_min(int32_t v) {
-  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x111, 0xf, 0xf, false));
-  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x112, 0xf, 0xf, false));
-  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x114, 0xf, 0xf, false));
-  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x118, 0xf, 0xf, false));
-  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x142, 0xa, 0xf, false));
-  v = min(v, __builtin_amdgcn_update_dpp(INT32_MAX, v, 0x143, 0xc, 0xf, false));
-  return __builtin_amdgcn_readlane(v, 63);
-}
-
-__device__ inline int32_t wave_max(int32_t v) {
-  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x111, 0xf, 0xf, false));
-  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x112, 0xf, 0xf, false));
-  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x114, 0xf, 0xf, false));
-  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x118, 0xf, 0xf, false));
-  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x142, 0xa, 0xf, false));
-  v = max(v, __builtin_amdgcn_update_dpp(INT32_MIN, v, 0x143, 0xc, 0xf, false));
-  return __builtin_amdgcn_readlane(v, 63);
 }
 
 // Orders this wavefront's LDS accesses (a wave's LDS instructions execute in order).

@@ -52,3 +52,50 @@ def test_triangle_paths(bin, n, boxes, size):
         assert_vis_equal(vis_numpy(views, vis, 1, 0)[0][None], want[None], f"n={n} bin {bin}")
         if count:
             assert P.read_status(ws)["fragments"] == ref["fragments"]
+
+
+def _check(sc, what, **kw):
+    for count in (False, True):
+        say(f"[gpu] {what} count {count}")
+        P, layers, views, vis, ws, _, _ = gpu_render(sc, count_fragments=count, **kw)
+        frags = 0
+        for v, cam in enumerate(sc.cameras):
+            for l, m in enumerate(sc.layers):
+                want, ref = O.raster(m, cam)
+                frags += ref["fragments"]
+                assert_vis_equal(vis_numpy(views, vis, sc.k, v)[l][None], want[None], f"{what} view {v} layer {l}")
+        st = P.read_status(ws)
+        assert not count or st["fragments"] == frags
+    return st
+
+
+def _shuffled(k, n_lat, n_lon, sizes):
+    """Displaced shells whose triangles come in random order: every group of consecutive ones reaches every tile."""
+    rng = np.random.default_rng([92, k, n_lat])
+    layers = [S.Mesh(m.xyz, m.uv, m.tri[rng.permutation(m.n_tri)]) for m in S.displaced_shells(2, k, n_lat, n_lon)]
+    tex = [S.uniform_texture(92, l, 8, 8, opaque=True) for l in range(k)]
+    return S.Scene("shuffled", layers, tex, S.ring_cameras(92, len(sizes), sizes))
+
+
+@pytest.mark.parametrize("bin", [16, 64])
+@pytest.mark.parametrize("k,n_lat,n_lon,sizes", [
+    (2, 160, 320, [(300, 200)]),        # 398 groups of 256 triangles a layer, all in the middle bins: loaded in turns
+    (4, 160, 321, [(120, 90)]),         # groups of 512
+    (1, 160, 320, [(61, 40)] * 21),     # groups of 1,024
+    (1, 5, 32, [(70, 70)]),             # exactly 256 triangles: one full group
+])
+def test_groups_in_random_order(bin, k, n_lat, n_lon, sizes):
+    _check(_shuffled(k, n_lat, n_lon, sizes), f"shuffled k={k} {n_lat}x{n_lon} {len(sizes)} views bin {bin}", bin=bin)
+
+
+@pytest.mark.parametrize("boxes", [SMALL, LARGE])
+def test_groups_over_more_tiles_than_a_table_holds(boxes):
+    """1,024 x 9 bins of 8 pixels under one group: its table counts 2 x 2 bins at a time."""
+    _check(_soup(7, 700, boxes, (8192, 72)), f"wide {len(boxes)}", bin=8)
+
+
+@pytest.mark.parametrize("capacity", [1, 600, 4000, 20000])
+def test_groups_without_list_space(capacity):
+    """Groups that find no room in the list are gone through triangle by triangle, next to groups that found some."""
+    sc = _shuffled(2, 60, 120, [(200, 150), (90, 140)])
+    assert _check(sc, f"capacity {capacity}", list_capacity=capacity)["bin_overflow"] > 0
