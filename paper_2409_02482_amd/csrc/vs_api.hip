@@ -1027,13 +1027,15 @@ vs_status ksdf_params(const char* who, const vs_ksdf_field* f, const vs_ksdf_opt
   P.inv_sdf = f->sdf_res / (f->hi - f->lo);
   P.inv_rgba = f->rgba_res / (f->hi - f->lo);
   P.inv_occ = o->occ_res / (f->hi - f->lo);
+  P.occ_frac = 31;
+  while (((int64_t)(P.occ_res + 1) << P.occ_frac) > (int64_t)1 << 32) --P.occ_frac;
   P.k = o->k;
   P.factor = 1;
   for (int j = 0; j < o->k; ++j) {
     P.off[j] = o->offsets[j];
     if (!(std::fabs(o->beta * o->offsets[j]) <= 60.0)) P.factor = 0;
-    P.cexp[0][j] = (float)std::exp(-(o->beta / 2.0) * o->offsets[j]);
-    P.cexp[1][j] = (float)std::exp(-o->beta * o->offsets[j]);
+    P.cexp[0][j] = (float)std::exp(o->beta / 2.0 * o->offsets[j]);
+    P.cexp[1][j] = (float)std::exp(o->beta * o->offsets[j]);
   }
   P.beta = o->beta;
   P.occ_threshold = o->occ_threshold;
@@ -1077,11 +1079,16 @@ extern "C" vs_status vs_ksdf_render(const vs_ksdf_field* field, const vs_ksdf_op
   if ((uintptr_t)out_rgba % 16 || (layers && (uintptr_t)layers % 16) || (samples && (uintptr_t)samples % 8))
     return fail(VS_ERR_ARG, "vs_ksdf_render: misaligned output");
   const int64_t total = views->host[views->n_views].pix_offset;
-  const int64_t blocks = ((total + vs::kKsdfRays - 1) / vs::kKsdfRays + 7) / 8 * 8;
+  // Rays a wavefront renders: its lanes set up one ray each, so more rays share that work, as long as the chip's 4,096
+  // places still see several wavefronts each (8 x 512^2 rays: 16 a wavefront 5.7 ms, 2 a wavefront 6.2 ms).
+  int per_wave = vs::kKsdfBatch;
+  while (per_wave > 2 && total / per_wave < 16384) per_wave /= 2;
+  const int64_t per_block = (int64_t)vs::kKsdfWaves * per_wave;
+  const int64_t blocks = ((total + per_block - 1) / per_block + 7) / 8 * 8;
   if (blocks > INT32_MAX) return fail(VS_ERR_SIZE, "vs_ksdf_render: too many pixels");
   auto launch = [&](auto kern) {
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, views->dev, views->n_views,
-                       total, P, occ, (float4*)out_rgba, (float4*)layers, samples);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(64 * vs::kKsdfWaves), 0, (hipStream_t)stream, P,
+                       views->dev, views->n_views, total, per_wave, occ, out_rgba, layers, samples);
   };
   const int n_total = P.n + P.m;
   if (n_total <= 64) launch(vs::k_ksdf_render<2>);
