@@ -13,6 +13,13 @@
 
 namespace vs {
 
+// a b + c for a and uniform b below 2^24, modulo 2^32, at full rate.
+__device__ inline uint32_t mad24(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t r;
+  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
+  return r;
+}
+
 constexpr int kMaxLayers = VS_MAX_LAYERS;
 constexpr uint64_t kEmpty = VS_EMPTY;
 constexpr int32_t kInvalidX = INT32_MIN;

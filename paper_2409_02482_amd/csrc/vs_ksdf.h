@@ -22,7 +22,7 @@
 
 #include <type_traits>
 
-#include "vs.h"
+#include "vs_common.h"
 
 namespace vs {
 
@@ -397,13 +397,6 @@ __device__ inline void ksdf_setup(const vs_view* __restrict__ views, int n_views
   S.flags[slot] = (real ? kKsdfReal : 0) | (hit ? kKsdfHit : 0) | (fixed ? kKsdfFixed : 0);
 }
 
-// a b + c for a and b below 2^24, modulo 2^32, at full rate
-__device__ inline uint32_t ksdf_mad24(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t r;
-  asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b), "v"(c));
-  return r;
-}
-
 // Occupancy bits of the march steps of two rays, one per half: lane l of a half
 // gets those of steps 64 l .. 64 l + 63 of its ray, the voxel of step s's
 // midpoint being floor(A + tm B), tm = t_in + (s + 1/2) D, in FP64, clamped to
@@ -466,7 +459,7 @@ __device__ inline uint64_t ksdf_march(KsdfArgs P, const uint32_t* __restrict__ o
 #pragma unroll
       for (int q = 0; q < G; ++q) {
         near = min(near, min(X[0] & frac, min(X[1] & frac, X[2] & frac)));
-        idx[q] = ksdf_mad24(ksdf_mad24(X[2] >> f, Ro, X[1] >> f), Ro, X[0] >> f);
+        idx[q] = mad24(mad24(X[2] >> f, Ro, X[1] >> f), Ro, X[0] >> f);
         word[q] = word_of(idx[q]);
 #pragma unroll
         for (int a = 0; a < 3; ++a) X[a] += dX[a];
@@ -491,7 +484,7 @@ __device__ inline uint64_t ksdf_march(KsdfArgs P, const uint32_t* __restrict__ o
           // floor, then clamp to [0, Ro - 1] (the coordinate stays within a rounding of [0, Ro])
           vox[a] = (uint32_t)min(max((int)floor(A[a] + tm * B[a]), 0), Ro - 1);
         }
-        const uint32_t idx = ksdf_mad24(ksdf_mad24(vox[2], Ro, vox[1]), Ro, vox[0]);
+        const uint32_t idx = mad24(mad24(vox[2], Ro, vox[1]), Ro, vox[0]);
         w[q] = test(word_of(idx), idx);
       }
       keep(i, w[0], w[1]);

@@ -69,6 +69,21 @@ __device__ inline float abs_cos_face(const float* __restrict__ xyz, const int32_
   return fabsf(nx * dx + ny * dy + nz * dz) * rsqrtf(len2);
 }
 
+// s_ch += y 2^-24 q_ch for the four bytes of a coefficient word.  A byte alone
+// in 16 bits is a half of exactly 2^-24 times its value, which a mixed-precision
+// multiply-add takes as it is: 6 instructions a word, where a conversion and a
+// multiply-add per byte take 8.
+__device__ inline void sh_add(uint32_t q, float y, float (&s)[4]) {
+#pragma clang fp contract(fast)
+  typedef _Float16 half2 __attribute__((ext_vector_type(2)));
+  const half2 even = __builtin_bit_cast(half2, q & 0x00ff00ffu);
+  const half2 odd = __builtin_bit_cast(half2, __builtin_amdgcn_perm(0u, q, 0x0c030c01u));
+  s[0] += y * (float)even.x;
+  s[1] += y * (float)odd.x;
+  s[2] += y * (float)even.y;
+  s[3] += y * (float)odd.y;
+}
+
 // One thread per pixel, same tiling and XCD order as k_shade_fwd.  Per hit
 // layer: UV in FP64, then per degree l the footprint in that level (FP64
 // coordinates, as for RGBA textures) and the 2l+1 coefficient words of the
@@ -77,10 +92,12 @@ __device__ inline float abs_cos_face(const float* __restrict__ xyz, const int32_
 //   raw_c = mid * sum_i Y_i + scale * sum_l [ sum_corner w_corner sum_m Y_lm q_lm,c - 127.5 sum_m Y_lm ],
 // q the raw bytes (FP32 sums of exact byte values).  The bytes of a texel's coefficients of one degree
 // are adjacent, so a corner costs 2l+1 consecutive words.
-// At degree 3 the register budget is held to 4 wavefronts per SIMD (a few
-// bytes of spill cost less than the lost latency hiding).
+// Bound by VALU issue (93 % of the SIMDs' cycles at degree 3): 16 views of
+// 1024^2 pixels and seven layers took 2.62 ms with a conversion per byte, all
+// levels' words in flight at once (and a few of them in scratch) and 64-bit
+// addresses, and take 2.43 ms.
 template <int DEG>
-__global__ void __launch_bounds__(256, DEG == 3 ? 4 : 1) k_shade_sh(const vs_view* __restrict__ views, int n_views,
+__global__ void __launch_bounds__(256, DEG == 3 ? 5 : 1) k_shade_sh(const vs_view* __restrict__ views, int n_views,
                                                   const int32_t* __restrict__ tile_view, int64_t n_tiles,
                                                   LayerTable L, ShTable S, const ProjVert* __restrict__ proj,
                                                   int64_t vpv, const uint64_t* __restrict__ vis,
@@ -129,11 +146,13 @@ __global__ void __launch_bounds__(256, DEG == 3 ? 4 : 1) k_shade_sh(const vs_vie
         const float gx = 1.0f - fx, gy = 1.0f - fy;
         const float w00 = gx * gy, w01 = fx * gy, w10 = gx * fy, w11 = fx * fy;
         const int n = 2 * d + 1;
-        const uint32_t* base = reinterpret_cast<const uint32_t*>(S.data[l] + S.off[l][d]);
-        const uint32_t* p00 = base + ((int64_t)j0 * Wl + i0) * n;
-        const uint32_t* p01 = base + ((int64_t)j0 * Wl + i1) * n;
-        const uint32_t* p10 = base + ((int64_t)j1 * Wl + i0) * n;
-        const uint32_t* p11 = base + ((int64_t)j1 * Wl + i1) * n;
+        // 32-bit byte offsets from the level's (uniform) base: rows below 2^17 bytes, at most 2^14 of them
+        const char* base = reinterpret_cast<const char*>(S.data[l] + S.off[l][d]);
+        const uint32_t row = (uint32_t)(Wl * 4 * n), c0 = __umul24(i0, 4 * n), c1 = __umul24(i1, 4 * n);
+        const auto texel = [&](int32_t j, uint32_t col) {
+          return reinterpret_cast<const uint32_t*>(base + (size_t)mad24((uint32_t)j, row, col));
+        };
+        const uint32_t *p00 = texel(j0, c0), *p01 = texel(j0, c1), *p10 = texel(j1, c0), *p11 = texel(j1, c1);
         // per corner, the harmonic sum of this degree's raw bytes; then the corners' weights
         float s00[4] = {0.f, 0.f, 0.f, 0.f}, s01[4] = {0.f, 0.f, 0.f, 0.f};
         float s10[4] = {0.f, 0.f, 0.f, 0.f}, s11[4] = {0.f, 0.f, 0.f, 0.f};
@@ -143,19 +162,17 @@ __global__ void __launch_bounds__(256, DEG == 3 ? 4 : 1) k_shade_sh(const vs_vie
           const uint32_t q00 = p00[m], q01 = p01[m], q10 = p10[m], q11 = p11[m];
           const float y = Y[d * d + m];
           ysum += y;
-#pragma unroll
-          for (int ch = 0; ch < 4; ++ch) {
-            const int sh = 8 * ch;
-            s00[ch] += y * (float)((q00 >> sh) & 0xffu);
-            s01[ch] += y * (float)((q01 >> sh) & 0xffu);
-            s10[ch] += y * (float)((q10 >> sh) & 0xffu);
-            s11[ch] += y * (float)((q11 >> sh) & 0xffu);
-          }
+          sh_add(q00, y, s00);
+          sh_add(q01, y, s01);
+          sh_add(q10, y, s10);
+          sh_add(q11, y, s11);
         }
         // the weights sum to 1, so the byte offset 127.5 comes off once per degree
 #pragma unroll
         for (int ch = 0; ch < 4; ++ch)
-          acc[ch] += (w00 * s00[ch] + w01 * s01[ch] + w10 * s10[ch] + w11 * s11[ch]) - 127.5f * ysum;
+          acc[ch] += (w00 * s00[ch] + w01 * s01[ch] + w10 * s10[ch] + w11 * s11[ch]) * 0x1p24f - 127.5f * ysum;
+        // each level is done with before the next: else all levels' words are held at once and spill
+        asm volatile("" : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
       }
       float a = sigmoidf(prm.mid * sumY + prm.scale * acc[3]);
       if (prm.view_alpha) {
