@@ -1034,8 +1034,9 @@ vs_status ksdf_params(const char* who, const vs_ksdf_field* f, const vs_ksdf_opt
   for (int j = 0; j < o->k; ++j) {
     P.off[j] = o->offsets[j];
     if (!(std::fabs(o->beta * o->offsets[j]) <= 60.0)) P.factor = 0;
-    P.cexp[0][j] = (float)std::exp(o->beta / 2.0 * o->offsets[j]);
-    P.cexp[1][j] = (float)std::exp(o->beta * o->offsets[j]);
+    P.cinv[0][j] = (float)std::exp(-(o->beta / 2.0) * o->offsets[j]);
+    P.cinv[1][j] = (float)std::exp(-o->beta * o->offsets[j]);
+    P.cexp[j] = (float)std::exp(o->beta * o->offsets[j]);
   }
   P.beta = o->beta;
   P.occ_threshold = o->occ_threshold;
@@ -1080,7 +1081,7 @@ extern "C" vs_status vs_ksdf_render(const vs_ksdf_field* field, const vs_ksdf_op
     return fail(VS_ERR_ARG, "vs_ksdf_render: misaligned output");
   const int64_t total = views->host[views->n_views].pix_offset;
   // Rays a wavefront renders: its lanes set up one ray each, so more rays share that work, as long as the chip's 4,096
-  // places still see several wavefronts each (8 x 512^2 rays: 16 a wavefront 5.7 ms, 2 a wavefront 6.2 ms).
+  // places still see several wavefronts each (8 x 512^2 rays: 16 a wavefront 5.85 ms, 4 5.90 ms, 2 6.11 ms).
   int per_wave = vs::kKsdfBatch;
   while (per_wave > 2 && total / per_wave < 16384) per_wave /= 2;
   const int64_t per_block = (int64_t)vs::kKsdfWaves * per_wave;

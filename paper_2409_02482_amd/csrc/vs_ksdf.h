@@ -5,13 +5,11 @@
 // are read trilinearly.  The occupancy grid is one thread per voxel, decided in
 // FP64 and packed to bits with a wavefront ballot.  Rendering is one pixel ray
 // per half wavefront (32 lanes): the ray's march steps are spread over the
-// lanes (a lane owns a contiguous run of steps, so occupied-length ranks are a
-// prefix sum of per-lane counts), and so are its samples, up to four
-// consecutive ones a lane.  Transmittance is a product along a lane's samples
-// and one multiplicative scan across lanes, the importance CDF likewise with
-// sums, inversion a search over the CDF in the wave's LDS, and the merge of new
-// samples (existing samples first on ties) a gather through a bit map of the
-// places that they take.
+// lanes (a ballot is 32 steps' bits; occupied-length ranks are a prefix sum of
+// words' counts), and so are its samples, up to four a lane.  Transmittance and
+// the importance CDF are scans across lanes, inversion a search over the CDF in
+// the wave's LDS, and the merge of new samples (existing samples first on ties)
+// a gather through a bit map of the places that they take.
 // Ray set-up, marching, sample positions and SDF values are FP64 (the
 // occupancy decisions and march steps match a plain FP64 evaluation exactly);
 // weights, appearance and blending are FP32.
@@ -36,8 +34,9 @@ struct KsdfParams {
   double lo, hi, h_occ;
   double inv_sdf, inv_rgba, inv_occ;       // R / (hi - lo) of each grid
   int32_t occ_frac;                        // fraction bits f of the march's fixed point: (occ_res + 1) 2^f <= 2^32
-  float cexp[2][VS_KSDF_MAX_SURFACES];     // exp(beta_r o_j) for beta_r = beta / 2 (round 0) and beta
-  int32_t factor;                          // 1: every |beta o_j| <= 60, so exp(beta_r (d + o_j)) = G cexp
+  float cinv[2][VS_KSDF_MAX_SURFACES];     // exp(-beta_r o_j) for beta_r = beta / 2 (round 0) and beta
+  float cexp[VS_KSDF_MAX_SURFACES];        // exp(beta o_j)
+  int32_t factor;                          // 1: every |beta o_j| <= 60, so exp(-beta_r (d + o_j)) = E cinv
   int32_t k;
   double off[VS_KSDF_MAX_SURFACES];
   double beta, occ_threshold, half_diag;
@@ -199,9 +198,8 @@ __device__ inline int ksdf_dpp_i(int old, int x) {
   return __builtin_amdgcn_update_dpp(old, x, CTRL, ROW_MASK, 0xf, false);
 }
 
-// Inclusive prefix sum / product within each half.  Lanes that a shift leaves
-// without a source add zero; the product has no such fill, so it is written as
-// instructions that leave those lanes alone (s_nop: a DPP source must have been
+// Inclusive prefix sum / product within each half.  The float ones are written
+// as instructions that leave lanes without a source alone (s_nop: a DPP source must have been
 // written two wait states before).
 __device__ inline int ksdf_hscan_add_i(int x) {
   x += ksdf_dpp_i<0x111>(0, x);
@@ -211,19 +209,13 @@ __device__ inline int ksdf_hscan_add_i(int x) {
   x += ksdf_dpp_i<0x142, 0xa>(0, x);
   return x;
 }
-template <int CTRL, int ROW_MASK = 0xf>
-__device__ inline double ksdf_dpp_d(double x) {
-  const uint64_t b = (uint64_t)__double_as_longlong(x);
-  const uint32_t lo = (uint32_t)ksdf_dpp_i<CTRL, ROW_MASK>(0, (int)(uint32_t)b);
-  const uint32_t hi = (uint32_t)ksdf_dpp_i<CTRL, ROW_MASK>(0, (int)(uint32_t)(b >> 32));
-  return __longlong_as_double((int64_t)((uint64_t)hi << 32 | lo));
-}
-__device__ inline double ksdf_hscan_add_d(double x) {
-  x += ksdf_dpp_d<0x111>(x);
-  x += ksdf_dpp_d<0x112>(x);
-  x += ksdf_dpp_d<0x114>(x);
-  x += ksdf_dpp_d<0x118>(x);
-  x += ksdf_dpp_d<0x142, 0xa>(x);
+__device__ inline float ksdf_hscan_add(float x) {
+  asm("s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_shr:1 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_shr:2 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_shr:4 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_shr:8 row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\tv_add_f32_dpp %0, %0, %0 row_bcast:15 row_mask:0xa bank_mask:0xf\n\ts_nop 1"
+      : "+v"(x));
   return x;
 }
 __device__ inline float ksdf_hscan_mul(float x) {
@@ -245,12 +237,6 @@ __device__ inline float ksdf_hlane(float x, int l, int h) {
 __device__ inline int ksdf_hlane_i(int x, int l, int h) {
   const int a = __builtin_amdgcn_readlane(x, l), b = __builtin_amdgcn_readlane(x, 32 + l);
   return h ? b : a;
-}
-
-__device__ inline double ksdf_hlane_d(double x, int l, int h) {
-  const uint64_t b = (uint64_t)__double_as_longlong(x);
-  const uint32_t lo = (uint32_t)ksdf_hlane_i((int)(uint32_t)b, l, h), hi = (uint32_t)ksdf_hlane_i((int)(uint32_t)(b >> 32), l, h);
-  return __longlong_as_double((int64_t)((uint64_t)hi << 32 | lo));
 }
 
 // Sums of four values over this lane's half: x's in lanes 0..7, z's in 8..15,
@@ -291,7 +277,7 @@ struct KsdfLds {
   double t[32 * NSL + 64];  // sample parameters
   double d[32 * NSL + 64];  // their SDF values
   union {
-    double cdf[128];        // importance CDF c_0..c_{N-1}, then infinite
+    float cdf[128];         // importance CDF c_0..c_{N-1}, then infinite
     struct {
       uint64_t mask[32];    // march: occupied-step bits per lane
       int32_t pre[32];      // march: exclusive prefix of occupied steps per lane
@@ -523,13 +509,13 @@ __device__ inline float ksdf_exp(double x) {
 
 // What the surfaces share of the opacity of the interval from a sample with SDF
 // value d to one with dn: 1 - Phi_{i+1} / Phi_i with Phi = 1 / (1 + exp(-beta x))
-// is (1 - r) / (1 + g_j), r = exp(-beta_r (d - dn)), g_j = exp(beta_r (dn + o_j)),
+// is (1 - r) / (1 + g_j), r = exp(-beta (d - dn)), g_j = exp(beta (dn + o_j)),
 // and not below 0.  q is 1 - r held to that and 0 next to a NaN, G is g without
 // o_j.  Neither overflows to NaN: far inside all surfaces g is 0, far outside
 // infinite, with opacity 0.
-__device__ inline void ksdf_interval(double beta_r, double d, double dn, float& q, float& G) {
-  q = fmaxf(-expm1f(-(float)(beta_r * (d - dn))), 0.f);
-  G = q > 0.f ? ksdf_exp(beta_r * dn) : 1.f;
+__device__ inline void ksdf_interval(double beta, double d, double dn, float& q, float& G) {
+  q = fmaxf(-expm1f(-(float)(beta * (d - dn))), 0.f);
+  G = q > 0.f ? ksdf_exp(beta * dn) : 1.f;
 }
 
 // NeuS interval weights of one surface, w_i = a_i prod_{l<i} (1 - a_l), for lane
@@ -537,16 +523,16 @@ __device__ inline void ksdf_interval(double beta_r, double d, double dn, float& 
 // exponential of its own where the offsets are too large for the factor to
 // stay a normal float.
 template <int NS>
-__device__ inline void ksdf_weights(KsdfArgs P, int round, int j, double beta_r, const double (&dn)[NS],
+__device__ inline void ksdf_weights(KsdfArgs P, int j, const double (&dn)[NS],
                                     const float (&q)[NS], const float (&G)[NS], float (&w)[NS], int l) {
 #pragma clang fp contract(fast)
   float a[NS], pass = 1.f;
-  const float c = P.cexp[round][j];
+  const float c = P.cexp[j];
 #pragma unroll
   for (int sl = 0; sl < NS; ++sl) a[sl] = 1.f + G[sl] * c;
   if (!P.factor) {
 #pragma unroll
-    for (int sl = 0; sl < NS; ++sl) a[sl] = q[sl] > 0.f ? 1.f + ksdf_exp(beta_r * (dn[sl] + P.off[j])) : 1.f;
+    for (int sl = 0; sl < NS; ++sl) a[sl] = q[sl] > 0.f ? 1.f + ksdf_exp(P.beta * (dn[sl] + P.off[j])) : 1.f;
   }
 #pragma unroll
   for (int sl = 0; sl < NS; ++sl) {
@@ -561,45 +547,66 @@ __device__ inline void ksdf_weights(KsdfArgs P, int round, int j, double beta_r,
   }
 }
 
-// Importance CDF of one round over Ncur samples: the surfaces' weights summed, plus the floor.
+// Importance CDF of one round over Ncur samples: the surfaces' weights summed,
+// plus the floor.  Sample 32 sl + l lies in lane l's slot sl.  The new samples'
+// positions follow from the CDF's last bits, and a normal jumps where a sample
+// crosses a cell face: so the weights keep this form, e_j = E cexp_j at both
+// ends of an interval, opacity (e_{i+1} - e_i) / (1 + e_{i+1}), one scan per 32
+// samples, none of it contracted.  e is held below 2^126, so that reciprocals
+// stay normal floats; an interval next to a NaN has weight 0, as have those
+// from the ray's last sample on.
 template <int NS, int NSL>
 __device__ inline void ksdf_cdf(KsdfArgs P, KsdfLds<NSL>& L, int round, double beta_r, int Ncur, int l, int h) {
-#pragma clang fp contract(fast)
-  float q[NS], G[NS], W[NS];
-  double d[NS];                // at the intervals' ends; samples past the last repeat it: intervals of opacity 0
+  float E[NS], En[NS], W[NS];
+  double d[NS], dn[NS];
 #pragma unroll
   for (int sl = 0; sl < NS; ++sl) {
-    d[sl] = L.d[min(NS * l + sl + 1, Ncur - 1)];
-    ksdf_interval(beta_r, L.d[min(NS * l + sl, Ncur - 1)], d[sl], q[sl], G[sl]);
+    const int i = 32 * sl + l;
+    d[sl] = L.d[min(i, Ncur - 1)];
+    dn[sl] = L.d[min(i + 1, Ncur - 1)];
+    if (isnan(d[sl]) || isnan(dn[sl])) d[sl] = dn[sl] = 0.0;
+    E[sl] = expf(-(float)(beta_r * d[sl]));
+    En[sl] = expf(-(float)(beta_r * dn[sl]));
     W[sl] = 0.f;
   }
   for (int j = 0; j < P.k; ++j) {
-    float w[NS];
-    ksdf_weights<NS>(P, round, j, beta_r, d, q, G, w, l);
+    const float c = P.cinv[round][j];
+    float carry = 1.f;
 #pragma unroll
-    for (int sl = 0; sl < NS; ++sl) W[sl] += w[sl];
+    for (int sl = 0; sl < NS; ++sl) {
+      float e = E[sl] * c, en = En[sl] * c;
+      if (!P.factor) {
+        e = expf(-(float)(beta_r * (d[sl] + P.off[j])));
+        en = expf(-(float)(beta_r * (dn[sl] + P.off[j])));
+      }
+      e = fminf(e, 0x1p126f);
+      en = fminf(en, 0x1p126f);
+      const float a = fmaxf((en - e) * __builtin_amdgcn_rcpf(1.f + en), 0.f);
+      const float t = ksdf_hscan_mul(1.f - a) * carry;
+      W[sl] += ksdf_hbelow(carry, t, l) * a;
+      if (sl + 1 < NS) carry = ksdf_hlane(t, 31, h);
+    }
   }
-  // summed in FP64: the new samples' positions follow the CDF's differences
-  double sum = 0.0;
+  float sum = 0.f;
 #pragma unroll
   for (int sl = 0; sl < NS; ++sl) {
-    W[sl] = NS * l + sl < Ncur - 1 ? W[sl] + P.pdf_floor : 0.f;
-    sum += (double)W[sl];
+    W[sl] = 32 * sl + l < Ncur - 1 ? W[sl] + P.pdf_floor : 0.f;
+    sum += W[sl];
   }
-  const double incl = ksdf_hscan_add_d(sum);
-  const double rS = 1.0 / ksdf_hlane_d(incl, 31, h);
-  double c = incl - sum;
+  const float rS = 1.f / ksdf_hlane(ksdf_hscan_add(sum), 31, h);
+  float carry = 0.f;
 #pragma unroll
-  for (int sl = 0; sl < NS; ++sl) {
-    const int i = NS * l + sl;
-    c += (double)W[sl];
-    if (i + 1 < 128) L.cdf[i + 1] = i < Ncur - 1 ? c * rS : (double)INFINITY;
+  for (int sl = 0; sl < 4; ++sl) {
+    const int i = 32 * sl + l;
+    float c = INFINITY;                    // places past the last sample's, which the search may read
+    if (sl < NS) {
+      const float part = ksdf_hscan_add(W[sl < NS ? sl : 0] * rS) + carry;
+      carry = ksdf_hlane(part, 31, h);
+      if (i < Ncur - 1) c = part;
+    }
+    if (i < 127) L.cdf[i + 1] = c;
   }
-  if (l == 0) L.cdf[0] = 0.0;
-  // places past the last lane's, which the search may read
-#pragma unroll
-  for (int p = 32 * NS + 1; p < 128; p += 32)
-    if (p + l < 128) L.cdf[p + l] = (double)INFINITY;
+  if (l == 0) L.cdf[0] = 0.f;
 }
 
 // Appearance of the ray's samples, per-surface quadrature and fixed-order
@@ -630,7 +637,7 @@ __device__ inline float ksdf_blend(KsdfArgs P, const KsdfLds<NSL>& L, const Ksdf
   for (int j = 0; j < P.k; ++j) {
 #pragma clang fp contract(fast)
     float w[NS];
-    ksdf_weights<NS>(P, 1, j, P.beta, d, q, G, w, l);
+    ksdf_weights<NS>(P, j, d, q, G, w, l);
     float pr = 0.f, pg = 0.f, pb = 0.f, pa = 0.f;
 #pragma unroll
     for (int sl = 0; sl < NS; ++sl) {
@@ -659,16 +666,15 @@ __device__ inline int64_t ksdf_block() {
 // of 32 exactly (NSL = slots per lane, from the sample count).
 //
 // Bound by VALU issue: 8 x 512^2 rays, k = 7, 64 + 32 samples, 1,024 steps took
-// 8.6 ms at 6.1e9 wavefront instructions and take 5.6 ms at 3.1e9, which is all
+// 8.6 ms at 6.1e9 wavefront instructions and take 5.9 ms at 3.3e9, which is all
 // the cycles the SIMDs have.  What went: each of a wavefront's 64 lanes setting
-// up its own ray (one lane does now), the FP64
-// march, one transmittance scan per 32 samples and surface (one per 96 now),
-// four half-wave sums per surface (one now), interval opacities from each
-// surface's own exponentials, rank searches in the merge, grid coordinates
-// derived from positions.  The CDF is FP64 for less error than an FP32 one
-// (mean error of a sample's position 9e-11 instead of 5e-10), at no cost seen.  A block is one wavefront, for its rays
-// may all miss while another's all hit (four a block: 0.6 ms more); LDS and
-// registers both allow 16 a CU.  Samples lie in LDS between the phases and
+// up its own ray (one lane does now), the FP64 march, exchanges between lanes
+// for the next sample's terms, in the blend one transmittance scan per 32
+// samples and surface (one per 96 now), four half-wave sums per surface (one
+// now) and opacities from each surface's own exponentials, rank searches in the
+// merge, grid coordinates derived from positions.  A block is one wavefront, for
+// its rays may all miss while another's all hit (four a block: 0.6 ms more); LDS
+// and registers both allow 16 a CU.  Samples lie in LDS between the phases and
 // parameters are asked for anew, so that nothing spills.
 template <int NSL>
 __global__ void __launch_bounds__(64 * kKsdfWaves, 4) k_ksdf_render(KsdfParams, const vs_view* __restrict__ views,
@@ -752,11 +758,13 @@ __global__ void __launch_bounds__(64 * kKsdfWaves, 4) k_ksdf_render(KsdfParams, 
       ksdf_wave_sync();
       for (int qn = l; qn < m2; qn += 32) {
         const double u = ((double)qn + 0.5) / (double)m2;
+        float uf = (float)u;                  // the largest float that is not above u
+        if ((double)uf > u) uf = __uint_as_float(__float_as_uint(uf) - 1);
         int a = 0;                            // largest i with cdf[i] <= u
 #pragma unroll
-        for (int st = 64; st > 0; st >>= 1) a += L.cdf[a + st] <= u ? st : 0;
+        for (int st = 64; st > 0; st >>= 1) a += L.cdf[a + st] <= uf ? st : 0;
         a = min(a, Ncur - 2);
-        const double ca = L.cdf[a], cb = L.cdf[a + 1];
+        const double ca = (double)L.cdf[a], cb = (double)L.cdf[a + 1];
         const double fr = cb > ca ? (u - ca) / (cb - ca) : 0.0;
         const double t = L.t[a] + fr * (L.t[a + 1] - L.t[a]);
         int below = a + 1;                    // existing samples <= t, which go first
