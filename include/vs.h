@@ -124,8 +124,9 @@ typedef struct vs_views {
 } vs_views;
 
 /* Raster options.  bin: screen-tile width in pixels, one of 8, 16, 32, 64, or
- * 0 for the library default (64); tiles are square except the 64-pixel ones,
- * which are 56 rows high.  The result is bit-identical for every value.
+ * 0 for the library's choice (64, or 32 or 16 for a call with few tiles, in a
+ * workspace of the same size); tiles are square except the 64-pixel ones, which
+ * are 56 rows high.  The result is bit-identical for every value.
  * The workspace must have been sized for the same bin value.
  * flags: VS_RASTER_COUNT_FRAGMENTS counts covered (triangle, pixel) pairs in
  * the status block (costs extra atomics); VS_RASTER_DIRECT uses the unbinned

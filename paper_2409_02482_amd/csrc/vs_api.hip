@@ -131,7 +131,14 @@ vs_status build_textures(const vs_texture* tex, int32_t k, vs::TexTable& X) {
 
 int bin_slot(int bin) { return bin == 8 ? 0 : bin == 16 ? 1 : bin == 32 ? 2 : bin == 64 ? 3 : -1; }
 
+// Bin size of a call that leaves it to the library.  A block draws one bin and the chip holds 1,280 blocks of 64-pixel
+// bins, so below about a thousand of them smaller bins are faster, whatever the meshes (us for 16 / 32 / 64 pixels; 3
+// layers of 1,300 triangles, 256^2: 28 / 35 / 52, 700 x 500: 49 / 45 / 61; 7 layers of 10^5, 256^2: 53 / 66 / 114, 512^2:
+// 89 / 63 / 89, 700 x 500, 693 bins: 96 / 67 / 89; 800^2, 1,365 bins: 171 / 88 / 77).
 constexpr int kDefaultBin = 64;
+int default_bin(const vs_view& tot, int k) {
+  return tot.tile_offset[3] * k >= 1024 ? kDefaultBin : tot.tile_offset[2] * k >= 512 ? 32 : 16;
+}
 
 vs::BinGroups bin_groups(const vs::LayerTable& L, int reps) {
   vs::BinGroups q;
@@ -143,23 +150,27 @@ vs::BinGroups bin_groups(const vs::LayerTable& L, int reps) {
 vs::WsLayout ws_layout(const vs::LayerTable& L, const vs_views* views, int bin, int64_t capacity = 0) {
   vs::WsLayout w;
   const int n_views = views->n_views;
-  w.bin = bin ? bin : kDefaultBin;
-  w.slot = bin_slot(w.bin);
   const vs_view& tot = views->host[n_views];
+  const int sized = bin ? bin : kDefaultBin, sized_slot = bin_slot(sized);     // what the space is reckoned by
+  w.bin = bin || capacity > 0 ? sized : default_bin(tot, L.k);
+  w.slot = bin_slot(w.bin);
   w.n_tiles16 = tot.tile_offset[1];
   w.n_tiles_bin = w.slot >= 0 ? tot.tile_offset[w.slot] : 0;
   w.n_bins = w.n_tiles_bin * L.k;
   const uint64_t tris = (uint64_t)n_views * (uint64_t)L.tri_off[L.k];
   w.reps = vs::bin_reps(L.tri_off[L.k], n_views);
   w.n_groups = (int64_t)n_views * bin_groups(L, w.reps).off[L.k];
-  const uint64_t factor = w.bin == 8 ? 4 : w.bin == 16 ? 3 : 2;
+  const uint64_t factor = sized == 8 ? 4 : sized == 16 ? 3 : 2;
+  const int64_t sized_tiles = sized_slot >= 0 ? tot.tile_offset[sized_slot] : 0;
   // 4 + `factor` words per triangle (a back face's entry has 4, a front face's one) and five per bin, less the
   // groups' records and the parts' counters
   const int64_t parts = (int64_t)vs::kPools * n_views, pool_bytes = parts * vs::kPoolApart * 4;
-  const int64_t words = 4 * (int64_t)tris + (int64_t)std::max<uint64_t>(tris * factor, 1u << 20) + 5 * w.n_bins -
+  const int64_t words = 4 * (int64_t)tris + (int64_t)std::max<uint64_t>(tris * factor, 1u << 20) + 5 * sized_tiles * L.k -
                         4 * w.n_groups - pool_bytes / 4;
   // a caller's count of entries: 4 words per triangle and one per entry, of which runs take up to 5 per entry
   w.capacity = capacity > 0 ? 4 * tris + (uint64_t)capacity : (uint64_t)std::max<int64_t>(words, 4 * (int64_t)tris);
+  // smaller bins' larger view table comes out of the list, so that a call's workspace does not depend on the choice
+  w.capacity -= (vs::align_up((size_t)w.n_tiles_bin * 4, 256) - vs::align_up((size_t)sized_tiles * 4, 256)) / 4;
   const uint64_t usable = std::min<uint64_t>({w.capacity, (uint64_t)vs::kSegAll, capacity > 0 ? 5 * (uint64_t)capacity : ~0ull});
   w.pool_words = (uint32_t)(usable / (uint64_t)parts / 4 * 4);
   size_t off = 0;

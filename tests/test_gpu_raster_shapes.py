@@ -99,3 +99,20 @@ def test_groups_without_list_space(capacity):
     """Groups that find no room in the list are gone through triangle by triangle, next to groups that found some."""
     sc = _shuffled(2, 60, 120, [(200, 150), (90, 140)])
     assert _check(sc, f"capacity {capacity}", list_capacity=capacity)["bin_overflow"] > 0
+
+
+@pytest.mark.parametrize("k,size", [(3, (256, 256)), (3, (640, 336)), (4, (512, 300)), (5, (600, 560)), (7, (900, 900))])
+def test_library_choice_of_bin(k, size):
+    """Calls that leave the bin to the library, on both sides of the counts at which it takes 16, 32 and 64 pixels: the
+    visibility of every explicit size, in a workspace of the default's 64-pixel size."""
+    import torch
+    import paper_2409_02482_amd as P
+    layers = P.Layers(S.displaced_shells(3, k, 20, 40))
+    views = P.Views(S.ring_cameras(4, 1, [size]))
+    assert P.workspace_bytes(layers, views) == P.workspace_bytes(layers, views, 64)
+    vis, ws = P.raster(layers, views, count_fragments=True)
+    st = P.read_status(ws)
+    assert st["bin_overflow"] == 0
+    for b in (16, 32, 64):
+        other, ws2 = P.raster(layers, views, bin=b, count_fragments=True)
+        assert torch.equal(vis, other) and P.read_status(ws2)["fragments"] == st["fragments"], b
