@@ -111,17 +111,6 @@ __device__ inline void ksdf_corners(KsdfArgs P, double cx, double cy, double cz,
 #pragma unroll
       for (int dx = 0; dx < 2; ++dx) g[dz][dy][dx] = (double)ksdf_at(P.sdf, base + (dz * R1 + dy) * R1 + dx);
 }
-__device__ inline double ksdf_lerp(double a, double b, double f) { return __builtin_fma(f, b - a, a); }
-
-// SDF at a sample: interpolated one axis after the other.
-__device__ inline double ksdf_sample(KsdfArgs P, double cx, double cy, double cz) {
-  double g[2][2][2], fx, fy, fz;
-  ksdf_corners(P, cx, cy, cz, g, fx, fy, fz);
-  const double y0 = ksdf_lerp(ksdf_lerp(g[0][0][0], g[0][0][1], fx), ksdf_lerp(g[0][1][0], g[0][1][1], fx), fy);
-  const double y1 = ksdf_lerp(ksdf_lerp(g[1][0][0], g[1][0][1], fx), ksdf_lerp(g[1][1][0], g[1][1][1], fx), fy);
-  return ksdf_lerp(y0, y1, fz);
-}
-
 // Trilinear lookup of the RGBA grid: FP64 grid coordinates, FP32 weights and sum.
 __device__ inline float4 ksdf_rgba(KsdfArgs P, double cx, double cy, double cz) {
 #pragma clang fp contract(fast)
@@ -286,41 +275,42 @@ struct KsdfLds {
   uint32_t place[4];        // bit p: a new sample goes to place p
 };
 
-// LDS of one wavefront's rays, each set up by one lane.  The ray's coordinates
-// in a grid at parameter t are A + t B.
+// LDS of one wavefront's rays, each set up by one lane.
 struct KsdfRays {
-  double o[3][kKsdfBatch], v[3][kKsdfBatch];         // origin and unit direction
-  double A[2][3][kKsdfBatch], B[2][3][kKsdfBatch];   // of the SDF and RGBA grids
+  double o[3][kKsdfBatch], v[3][kKsdfBatch];   // origin and unit direction
   double t_in[kKsdfBatch], D[kKsdfBatch];      // interval start and march step
   int32_t flags[kKsdfBatch];
 };
 enum { kKsdfReal = 1, kKsdfHit = 2, kKsdfFixed = 4 };
-enum { kKsdfSdf = 0, kKsdfRgba = 1 };
 
-// Coordinate of parameter t along one axis of a grid.
-__device__ inline double ksdf_coord(const KsdfRays& S, int grid, int axis, int slot, double t) {
-  return __builtin_fma(t, S.B[grid][axis][slot], S.A[grid][axis][slot]);
+// A ray's position at parameter t, relative to the cube's corner, along one
+// axis, with the steps of a plain evaluation: a ray may run along a cell face,
+// and the cell decides about its normals.
+__device__ inline double ksdf_from_lo(KsdfArgs P, const KsdfRays& S, int axis, int slot, double t) {
+  return (S.o[axis][slot] + t * S.v[axis][slot]) - P.lo;
+}
+__device__ inline double ksdf_sample(KsdfArgs P, const KsdfRays& S, int slot, double t) {
+  return ksdf_sdf(P, ksdf_from_lo(P, S, 0, slot, t) * P.inv_sdf, ksdf_from_lo(P, S, 1, slot, t) * P.inv_sdf,
+                  ksdf_from_lo(P, S, 2, slot, t) * P.inv_sdf);
 }
 
 // |cos| of the angle between the ray and the gradient of the trilinear SDF
-// inside the sample's cell; 0 where the gradient is.  Its scale does not matter.
-// The gradient changes from cell to cell, so the cell is found with the steps
-// of a plain evaluation: a ray may run along a cell face.
-__device__ inline double ksdf_abs_cos(KsdfArgs P, const KsdfRays& S, int slot, double t) {
-  double g[2][2][2], fx, fy, fz, d[2][2], a[2][2], c[3];
-#pragma unroll
-  for (int q = 0; q < 3; ++q) c[q] = ((S.o[q][slot] + t * S.v[q][slot]) - P.lo) * P.inv_sdf;
+// inside the cell at grid coordinates c (along each axis, the corner
+// differences of the cell's 4 grid lines weighted by the other two axes'
+// weights); 0 where the gradient is.  Its scale does not matter.
+__device__ inline double ksdf_abs_cos(KsdfArgs P, const KsdfRays& S, int slot, const double (&c)[3]) {
+  double g[2][2][2], fx, fy, fz;
   ksdf_corners(P, c[0], c[1], c[2], g, fx, fy, fz);
+  const double wx[2] = {1.0 - fx, fx}, wy[2] = {1.0 - fy, fy}, wz[2] = {1.0 - fz, fz};
+  double gx = 0.0, gy = 0.0, gz = 0.0;
 #pragma unroll
-  for (int y = 0; y < 2; ++y)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      d[y][x] = g[1][y][x] - g[0][y][x];
-      a[y][x] = __builtin_fma(fz, d[y][x], g[0][y][x]);
+    for (int b = 0; b < 2; ++b) {
+      gx = __builtin_fma(wy[a] * wz[b], g[b][a][1] - g[b][a][0], gx);
+      gy = __builtin_fma(wx[a] * wz[b], g[b][1][a] - g[b][0][a], gy);
+      gz = __builtin_fma(wx[a] * wy[b], g[1][b][a] - g[0][b][a], gz);
     }
-  const double gx = ksdf_lerp(a[0][1] - a[0][0], a[1][1] - a[1][0], fy);
-  const double gy = ksdf_lerp(a[1][0] - a[0][0], a[1][1] - a[0][1], fx);
-  const double gz = ksdf_lerp(ksdf_lerp(d[0][0], d[0][1], fx), ksdf_lerp(d[1][0], d[1][1], fx), fy);
   const double n2 = (gx * gx + gy * gy) + gz * gz;
   const double gv = (gx * S.v[0][slot] + gy * S.v[1][slot]) + gz * S.v[2][slot];
   return n2 > 0.0 ? fabs(gv) / sqrt(n2) : 0.0;
@@ -369,14 +359,9 @@ __device__ inline void ksdf_setup(const vs_view* __restrict__ views, int n_views
   bool fixed = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2] < 2.0;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    const double from = o[a] - P.lo;
-    fixed = fixed && fabs(from * P.inv_occ) < far;
+    fixed = fixed && fabs((o[a] - P.lo) * P.inv_occ) < far;
     S.o[a][slot] = o[a];
     S.v[a][slot] = v[a];
-    S.A[kKsdfSdf][a][slot] = from * P.inv_sdf;
-    S.B[kKsdfSdf][a][slot] = v[a] * P.inv_sdf;
-    S.A[kKsdfRgba][a][slot] = from * P.inv_rgba;
-    S.B[kKsdfRgba][a][slot] = v[a] * P.inv_rgba;
   }
   S.t_in[slot] = t_in;
   S.D[slot] = hit ? (t_out - t_in) / (double)P.steps : 0.0;
@@ -504,17 +489,19 @@ __device__ inline int ksdf_select(uint64_t mask, int r) {
 __device__ inline float ksdf_exp(double x) {
   const float xh = (float)x;
   const float e = expf(xh);
-  return isinf(e) ? e : e + e * (float)(x - (double)xh);
+  return e > 0.f && e < INFINITY ? e + e * (float)(x - (double)xh) : e;
 }
 
 // What the surfaces share of the opacity of the interval from a sample with SDF
 // value d to one with dn: 1 - Phi_{i+1} / Phi_i with Phi = 1 / (1 + exp(-beta x))
 // is (1 - r) / (1 + g_j), r = exp(-beta (d - dn)), g_j = exp(beta (dn + o_j)),
-// and not below 0.  q is 1 - r held to that and 0 next to a NaN, G is g without
-// o_j.  Neither overflows to NaN: far inside all surfaces g is 0, far outside
-// infinite, with opacity 0.
+// and not below 0.  q is 1 - r held to that, G is g without o_j.  Neither
+// overflows to NaN: far inside all surfaces g is 0, far outside infinite, with
+// opacity 0.  Next to a NaN the opacity is 0, but 1 from a NaN to a point so far
+// inside that Phi is 0 in a float.
 __device__ inline void ksdf_interval(double beta, double d, double dn, float& q, float& G) {
   q = fmaxf(-expm1f(-(float)(beta * (d - dn))), 0.f);
+  if (isnan(d) && isinf(expf(-(float)(beta * dn)))) q = 1.f;
   G = q > 0.f ? ksdf_exp(beta * dn) : 1.f;
 }
 
@@ -552,9 +539,8 @@ __device__ inline void ksdf_weights(KsdfArgs P, int j, const double (&dn)[NS],
 // positions follow from the CDF's last bits, and a normal jumps where a sample
 // crosses a cell face: so the weights keep this form, e_j = E cexp_j at both
 // ends of an interval, opacity (e_{i+1} - e_i) / (1 + e_{i+1}), one scan per 32
-// samples, none of it contracted.  e is held below 2^126, so that reciprocals
-// stay normal floats; an interval next to a NaN has weight 0, as have those
-// from the ray's last sample on.
+// samples, none of it contracted; 0 where Phi_i = 0 (e_i infinite), 1 where only
+// Phi_{i+1} = 0.  Samples past the last repeat it: intervals of weight 0.
 template <int NS, int NSL>
 __device__ inline void ksdf_cdf(KsdfArgs P, KsdfLds<NSL>& L, int round, double beta_r, int Ncur, int l, int h) {
   float E[NS], En[NS], W[NS];
@@ -564,7 +550,6 @@ __device__ inline void ksdf_cdf(KsdfArgs P, KsdfLds<NSL>& L, int round, double b
     const int i = 32 * sl + l;
     d[sl] = L.d[min(i, Ncur - 1)];
     dn[sl] = L.d[min(i + 1, Ncur - 1)];
-    if (isnan(d[sl]) || isnan(dn[sl])) d[sl] = dn[sl] = 0.0;
     E[sl] = expf(-(float)(beta_r * d[sl]));
     En[sl] = expf(-(float)(beta_r * dn[sl]));
     W[sl] = 0.f;
@@ -579,9 +564,9 @@ __device__ inline void ksdf_cdf(KsdfArgs P, KsdfLds<NSL>& L, int round, double b
         e = expf(-(float)(beta_r * (d[sl] + P.off[j])));
         en = expf(-(float)(beta_r * (dn[sl] + P.off[j])));
       }
-      e = fminf(e, 0x1p126f);
-      en = fminf(en, 0x1p126f);
-      const float a = fmaxf((en - e) * __builtin_amdgcn_rcpf(1.f + en), 0.f);
+      float a = fmaxf((en - e) * __builtin_amdgcn_rcpf(1.f + en), 0.f);
+      a = en == INFINITY ? 1.f : a;
+      a = e == INFINITY ? 0.f : a;
       const float t = ksdf_hscan_mul(1.f - a) * carry;
       W[sl] += ksdf_hbelow(carry, t, l) * a;
       if (sl + 1 < NS) carry = ksdf_hlane(t, 31, h);
@@ -627,9 +612,10 @@ __device__ inline float ksdf_blend(KsdfArgs P, const KsdfLds<NSL>& L, const Ksdf
     ksdf_interval(P.beta, L.d[min(i, N - 1)], d[sl], q[sl], G[sl]);
     if (i < N - 1) {
       const double t = L.t[i];
-      app[sl] = ksdf_rgba(ksdf_args(), ksdf_coord(S, kKsdfRgba, 0, slot, t), ksdf_coord(S, kKsdfRgba, 1, slot, t),
-                          ksdf_coord(S, kKsdfRgba, 2, slot, t));
-      const double vdn = ksdf_abs_cos(ksdf_args(), S, slot, t);
+      const double x = ksdf_from_lo(P, S, 0, slot, t), y = ksdf_from_lo(P, S, 1, slot, t), z = ksdf_from_lo(P, S, 2, slot, t);
+      app[sl] = ksdf_rgba(ksdf_args(), x * P.inv_rgba, y * P.inv_rgba, z * P.inv_rgba);
+      const double c[3] = {x * P.inv_sdf, y * P.inv_sdf, z * P.inv_sdf};
+      const double vdn = ksdf_abs_cos(ksdf_args(), S, slot, c);
       aw[sl] = (2.f / (1.f + expf(-10.f * (float)vdn)) - 1.f) * app[sl].w;
     }
   }
@@ -672,10 +658,10 @@ __device__ inline int64_t ksdf_block() {
 // for the next sample's terms, in the blend one transmittance scan per 32
 // samples and surface (one per 96 now), four half-wave sums per surface (one
 // now) and opacities from each surface's own exponentials, rank searches in the
-// merge, grid coordinates derived from positions.  A block is one wavefront, for
-// its rays may all miss while another's all hit (four a block: 0.6 ms more); LDS
-// and registers both allow 16 a CU.  Samples lie in LDS between the phases and
-// parameters are asked for anew, so that nothing spills.
+// merge.  A block is one wavefront, for its rays may all miss while another's
+// all hit (four a block: 0.6 ms more); registers allow 16 a CU.  Samples lie in
+// LDS between the phases and parameters are asked for anew, so that nothing
+// spills.
 template <int NSL>
 __global__ void __launch_bounds__(64 * kKsdfWaves, 4) k_ksdf_render(KsdfParams, const vs_view* __restrict__ views,
                                                      int n_views, int64_t total, int per_wave,
@@ -738,8 +724,7 @@ __global__ void __launch_bounds__(64 * kKsdfWaves, 4) k_ksdf_render(KsdfParams, 
         for (int st = 16; st > 0; st >>= 1) a += L.pre[a + st] <= qi ? st : 0;
         const int s = 64 * a + ksdf_select(L.mask[a], qi - L.pre[a]);
         t = S.t_in[slot] + ((double)s + (rho - qf)) * S.D[slot];
-        d = ksdf_sample(ksdf_args(), ksdf_coord(S, kKsdfSdf, 0, slot, t), ksdf_coord(S, kKsdfSdf, 1, slot, t),
-                        ksdf_coord(S, kKsdfSdf, 2, slot, t));
+        d = ksdf_sample(ksdf_args(), S, slot, t);
       }
       L.t[i] = t;
       L.d[i] = d;
@@ -772,10 +757,7 @@ __global__ void __launch_bounds__(64 * kKsdfWaves, 4) k_ksdf_render(KsdfParams, 
         const int p = below + qn;
         atomicOr(&L.place[p >> 5], 1u << (p & 31));
         L.t[32 * NSL + qn] = t;
-        L.d[32 * NSL + qn] =
-            live ? ksdf_sample(ksdf_args(), ksdf_coord(S, kKsdfSdf, 0, slot, t), ksdf_coord(S, kKsdfSdf, 1, slot, t),
-                               ksdf_coord(S, kKsdfSdf, 2, slot, t))
-                 : 1e30;
+        L.d[32 * NSL + qn] = live ? ksdf_sample(ksdf_args(), S, slot, t) : 1e30;
       }
       ksdf_wave_sync();
       // the merged order: place p is the next new sample if its bit is set, else the next existing one
