@@ -396,7 +396,7 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
   __shared__ uint32_t smax[kNs * kNsY];   // per sub-tile, the depth word of its largest key
   __shared__ int32_t queue[2 * kRasterThreads];   // back-facing triangles that may lower a key
   __shared__ int32_t late_bigs[kBigQueue];        // large triangles among those (large front-facing ones: in the queue)
-  __shared__ uint32_t qn, bign;
+  __shared__ uint32_t qadd[3], bign;              // entries queued by a chunk, for three chunks in turn
   __shared__ uint32_t seg_base[kSegs];            // groups that reach the tile: list word of their first front-facing entry here
   __shared__ uint32_t seg_rest[kSegs];            // ... 16-byte record of their first other entry
   __shared__ uint32_t seg_start[kSegs];           // ... and the entries before it, front-facing ones and others << 16
@@ -419,7 +419,7 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
   const int x0 = tx * B, y0 = ty * BH;
   const int x1 = min(x0 + B, W) - 1, y1 = min(y0 + BH, H) - 1;
   const int tid = threadIdx.x, lane = tid & 63;
-  if (tid == 0) qn = bign = 0;
+  if (tid == 0) qadd[0] = qadd[1] = qadd[2] = bign = 0;
   for (int p = tid; p < B * BH / 2; p += kRasterThreads)   // 16-byte stores
     reinterpret_cast<ulonglong2*>(tile)[p] = make_ulonglong2(kEmpty, kEmpty);
   const ProjVert* P = proj + (int64_t)v * vpv + L.vert_off[l];
@@ -696,7 +696,11 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
     __syncthreads();
     // phase 2: each back-facing entry is tested from its record (box and depth bound) alone;
     // the ones that may lower a key are queued in LDS and drawn 256 at a time, so that the
-    // skipped majority costs no vertex loads and leaves no idle lanes behind.
+    // skipped majority costs no vertex loads and leaves no idle lanes behind.  A wavefront may be at the
+    // next chunk while another still reads what this one queued: each chunk counts in a word of its own,
+    // cleared between the barrier after its last reader and the one before its next use.
+    uint32_t q = 0;   // queue entries, uniform
+    int turn = 0;
     for (int g0 = 0; g0 < n_groups;) {
       g0 = one_load ? n_groups : load_segs(g0);
       const uint32_t n = seg_n[2];
@@ -718,11 +722,13 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
         }
         const uint64_t kb = __ballot(keep);
         uint32_t base = 0;
-        if (lane == 0 && kb) base = atomicAdd(&qn, (uint32_t)__popcll(kb));
-        base = __builtin_amdgcn_readfirstlane(base);
+        if (lane == 0 && kb) base = atomicAdd(&qadd[turn], (uint32_t)__popcll(kb));
+        base = q + __builtin_amdgcn_readfirstlane(base);
         if (keep) queue[base + (uint32_t)__popcll(kb & __lanemask_lt())] = t;
         __syncthreads();
-        uint32_t q = qn;
+        q += qadd[turn];
+        if (tid == 0) qadd[turn == 0 ? 2 : turn - 1] = 0;
+        turn = turn == 2 ? 0 : turn + 1;
         const bool last = c0 + kRasterThreads >= n;
         while (q >= kRasterThreads || (last && q > 0)) {   // uniform
           const int sh = share(q), e = tid >> sh;
@@ -731,7 +737,6 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
           const int32_t moved = tid < (int)rest ? queue[kRasterThreads + tid] : 0;
           __syncthreads();
           if (tid < (int)rest) queue[tid] = moved;
-          if (tid == 0) qn = rest;
           __syncthreads();
           q = rest;
         }
