@@ -164,15 +164,15 @@ vs::WsLayout ws_layout(const vs::LayerTable& L, const vs_views* views, int bin, 
   const int64_t sized_tiles = sized_slot >= 0 ? tot.tile_offset[sized_slot] : 0;
   // 4 + `factor` words per triangle (a back face's entry has 4, a front face's one) and five per bin, less the
   // groups' records and the parts' counters
-  const int64_t parts = (int64_t)vs::kPools * n_views, pool_bytes = parts * vs::kPoolApart * 4;
+  const int64_t parts = (int64_t)vs::kParts * n_views, parts_bytes = parts * vs::kPartApart * 4;
   const int64_t words = 4 * (int64_t)tris + (int64_t)std::max<uint64_t>(tris * factor, 1u << 20) + 5 * sized_tiles * L.k -
-                        4 * w.n_groups - pool_bytes / 4;
+                        4 * w.n_groups - parts_bytes / 4;
   // a caller's count of entries: 4 words per triangle and one per entry, of which runs take up to 5 per entry
   w.capacity = capacity > 0 ? 4 * tris + (uint64_t)capacity : (uint64_t)std::max<int64_t>(words, 4 * (int64_t)tris);
   // smaller bins' larger view table comes out of the list, so that a call's workspace does not depend on the choice
   w.capacity -= (vs::align_up((size_t)w.n_tiles_bin * 4, 256) - vs::align_up((size_t)sized_tiles * 4, 256)) / 4;
   const uint64_t usable = std::min<uint64_t>({w.capacity, (uint64_t)vs::kSegAll, capacity > 0 ? 5 * (uint64_t)capacity : ~0ull});
-  w.pool_words = (uint32_t)(usable / (uint64_t)parts / 4 * 4);
+  w.part_words = (uint32_t)(usable / (uint64_t)parts / 4 * 4);
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off += vs::align_up(bytes, 256); return o; };
   w.status = take(256);
@@ -181,7 +181,7 @@ vs::WsLayout ws_layout(const vs::LayerTable& L, const vs_views* views, int bin, 
   // everything below depends on the bin size; render and backward read only the part above
   w.bin_view = take((size_t)w.n_tiles_bin * 4);
   w.recs = take((size_t)w.n_groups * sizeof(vs::GroupRec));
-  w.pools = take((size_t)pool_bytes);
+  w.parts = take((size_t)parts_bytes);
   w.list = take((size_t)w.capacity * 4);
   w.total = off;
   return w;
@@ -276,7 +276,7 @@ vs_status vs_raster_layers(const vs_mesh* layers, int32_t k, const vs_views* vie
   auto* bin_view = (int32_t*)(base + lay.bin_view);
   auto* recs = (vs::GroupRec*)(base + lay.recs);
   auto* list = (uint32_t*)(base + lay.list);
-  auto* pools = (uint32_t*)(base + lay.pools);
+  auto* parts = (uint32_t*)(base + lay.parts);
   const int64_t vpv = L.vert_off[k];
   const int nv = views->n_views;
   const int64_t ntri = L.tri_off[k];
@@ -290,7 +290,7 @@ vs_status vs_raster_layers(const vs_mesh* layers, int32_t k, const vs_views* vie
   setup.n_tiles16 = lay.n_tiles16;
   setup.n_tiles_bin = direct ? 0 : lay.n_tiles_bin;
   setup.status = status;
-  setup.pools = pools;
+  setup.parts = parts;
   setup.n_views = nv;
   setup.slot = lay.slot;
   setup.proj_blocks = (int32_t)grid_1d(vpv, 256);
@@ -311,7 +311,7 @@ vs_status vs_raster_layers(const vs_mesh* layers, int32_t k, const vs_views* vie
   const dim3 bin_grid((unsigned)((groups.off[k] + 7) / 8 * 8), (unsigned)nv);
   auto binned = [&](auto kern) {
     hipLaunchKernelGGL(kern, bin_grid, dim3(256), 0, s, views->dev, L, groups, (const vs::ProjVert*)proj, vpv, recs,
-                       list, lay.pool_words, pools, status);
+                       list, lay.part_words, parts, status);
   };
   switch (B * 8 + lay.reps) {
     case 8 * 8 + 1: binned(vs::k_bin<8, 1>); break;

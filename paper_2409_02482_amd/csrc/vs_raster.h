@@ -19,6 +19,7 @@
 #pragma once
 
 #include "vs_common.h"
+#include "vs_lists.h"
 
 namespace vs {
 
@@ -48,12 +49,11 @@ __global__ void __launch_bounds__(256) k_fill_u64(uint64_t* __restrict__ p, int6
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = val;
 }
 
-// The list is shared out in kPools equal parts per view, one for the groups of each XCD, in which runs
-// are reserved by atomics on the parts' own words, kPoolApart words from each other: requests to one
+// The list is shared out in kParts equal parts per view, one for the groups of each XCD, in which runs
+// are reserved by atomics on the parts' own words, kPartApart words from each other: requests to one
 // word are served one after the other (about 6 ns each; on a single word 168k groups would take 1 ms).
 // A run that its part has no room for goes to the view's next parts.
-constexpr int kPools = 8;
-constexpr int kPoolApart = 16;
+constexpr int kPartApart = 16;
 
 // Everything that binning, drawing and shading find ready, one launch: the first blocks take step 1
 // for every (view, layer, vertex), proj_blocks per view; the next ones tile_view[g] = view owning
@@ -66,7 +66,7 @@ struct SetupArgs {
   int32_t* bin_view;
   int64_t n_tiles16, n_tiles_bin;
   unsigned long long* status;
-  uint32_t* pools;
+  uint32_t* parts;
   int32_t n_views, slot, proj_blocks, tile_blocks;
 };
 
@@ -76,7 +76,7 @@ __global__ void __launch_bounds__(256) k_setup(SetupArgs A, LayerTable L) {
     const int v = (int)(blockIdx.x / (uint32_t)A.proj_blocks);
     const int64_t g = (int64_t)(blockIdx.x - (uint32_t)v * (uint32_t)A.proj_blocks) * 256 + threadIdx.x;
     if (blockIdx.x == 0 && threadIdx.x < VS_STAT_COUNT) A.status[threadIdx.x] = 0ull;
-    if (g < kPools) A.pools[(v * kPools + (int)g) * kPoolApart] = 0u;
+    if (g < kParts) A.parts[(v * kParts + (int)g) * kPartApart] = 0u;
     if (g >= A.vpv) return;
     int l = 0;
     while (l + 1 < L.k && L.vert_off[l + 1] <= g) ++l;
@@ -145,7 +145,6 @@ struct alignas(16) GroupRec {
   uint32_t base;               // kGroupNoRun: no room in the list, its bins go through all of its triangles
   uint32_t shift;
 };
-constexpr uint32_t kGroupNoRun = 0xffffffffu;
 constexpr int kGroupTiles = 4096;
 constexpr uint32_t kSegAll = 0xf0000000u;   // a raster segment of all triangles from id base - kSegAll on; the list ends before it
 
@@ -168,8 +167,8 @@ inline int bin_reps(int64_t n_tri, int n_views) {
 template <int B, int R>
 __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, LayerTable L, BinGroups Q,
                                              const ProjVert* __restrict__ proj, int64_t vpv,
-                                             GroupRec* __restrict__ recs, uint32_t* __restrict__ list, uint32_t pool_words,
-                                             uint32_t* __restrict__ pools,
+                                             GroupRec* __restrict__ recs, uint32_t* __restrict__ list, uint32_t part_words,
+                                             uint32_t* __restrict__ parts,
                                              unsigned long long* __restrict__ status) {
   constexpr int BH = bin_rows(B);
   __shared__ uint32_t hist[kGroupTiles];   // per macro tile: front entries, other entries << 16; then their next places
@@ -314,12 +313,11 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
   if (tid == 0) {
     uint32_t base = kGroupNoRun;
     if (total_f <= 0xffffu && total_o <= 0xffffu) {
-      for (int q = 0; q < kPools && base == kGroupNoRun; ++q) {
-        const uint32_t p = (uint32_t)v * kPools + ((blockIdx.x + q) & (kPools - 1));
-        if (need > pool_words) break;
-        const uint32_t from = atomicAdd(&pools[p * kPoolApart], need);
-        if (from <= pool_words - need) base = p * pool_words + from;
-      }
+      uint32_t* mine = parts + v * kParts * kPartApart;
+      base = reserve_run(need, part_words, blockIdx.x & (kParts - 1),
+                         [&](uint32_t p) { return __hip_atomic_load(mine + p * kPartApart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+                         [&](uint32_t p, uint32_t n) { return atomicAdd(mine + p * kPartApart, n); });
+      if (base != kGroupNoRun) base += (uint32_t)v * kParts * part_words;
     }
     run_base = base;
     out.tx0 = (uint16_t)rx; out.ty0 = (uint16_t)ry; out.tw = (uint16_t)tw; out.th = (uint16_t)th;
