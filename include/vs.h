@@ -137,7 +137,10 @@ typedef struct vs_views {
 typedef struct vs_raster_opts {
   int32_t bin;
   int32_t flags;
-  int64_t list_capacity;      /* triangle-list entries reserved in the workspace; 0 = automatic.
+  int64_t list_capacity;      /* triangle-list entries, (triangle, bin) pairs, that the workspace
+                                 has room for, up to 0xe0000000; 0 = automatic: twice as many as
+                                 there are triangles in the views (three and four times in bins of
+                                 16 and 8 pixels), 2^20 at least.
                                  Bins that do not fit are still rasterised exactly, more slowly,
                                  and counted in VS_STAT_BIN_OVERFLOW. */
 } vs_raster_opts;

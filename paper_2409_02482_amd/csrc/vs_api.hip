@@ -161,29 +161,30 @@ vs::WsLayout ws_layout(const vs::LayerTable& L, const vs_views* views, int bin, 
   w.reps = vs::bin_reps(L.tri_off[L.k], n_views);
   w.n_groups = (int64_t)n_views * bin_groups(L, w.reps).off[L.k];
   const uint64_t factor = sized == 8 ? 4 : sized == 16 ? 3 : 2;
+  const uint64_t entries = capacity > 0 ? (uint64_t)capacity : std::max<uint64_t>(tris * factor, 1u << 20);
   const int64_t sized_tiles = sized_slot >= 0 ? tot.tile_offset[sized_slot] : 0;
-  // 4 + `factor` words per triangle (a back face's entry has 4, a front face's one) and five per bin, less the
-  // groups' records and the parts' counters
-  const int64_t parts = (int64_t)vs::kParts * n_views, parts_bytes = parts * vs::kPartApart * 4;
-  const int64_t words = 4 * (int64_t)tris + (int64_t)std::max<uint64_t>(tris * factor, 1u << 20) + 5 * sized_tiles * L.k -
-                        4 * w.n_groups - parts_bytes / 4;
-  // a caller's count of entries: 4 words per triangle and one per entry, of which runs take up to 5 per entry
-  w.capacity = capacity > 0 ? 4 * tris + (uint64_t)capacity : (uint64_t)std::max<int64_t>(words, 4 * (int64_t)tris);
-  // smaller bins' larger view table comes out of the list, so that a call's workspace does not depend on the choice
-  w.capacity -= (vs::align_up((size_t)w.n_tiles_bin * 4, 256) - vs::align_up((size_t)sized_tiles * 4, 256)) / 4;
-  const uint64_t usable = std::min<uint64_t>({w.capacity, (uint64_t)vs::kSegAll, capacity > 0 ? 5 * (uint64_t)capacity : ~0ull});
-  w.part_words = (uint32_t)(usable / (uint64_t)parts / 4 * 4);
   size_t off = 0;
   auto take = [&](size_t bytes) { const size_t o = off; off += vs::align_up(bytes, 256); return o; };
   w.status = take(256);
   w.tile_view = take((size_t)w.n_tiles16 * 4);
   w.proj = take((size_t)n_views * (size_t)L.vert_off[L.k] * sizeof(vs::ProjVert));
-  // everything below depends on the bin size; render and backward read only the part above
+  // everything below depends on the bin size; render and backward read only the part above.  Its bytes are what the ABI
+  // has asked for from the start: 24 a bin (4 of them for its view), 16 per view and triangle, 8 per 1,024 bins, and 4 per
+  // entry, each rounded up.  The list has what the views of smaller bins, the groups' records and the counters leave: per
+  // triangle, bin and entry at least the words that record, table and entries can need (group_tiles).
+  auto bytes = [](uint64_t n, uint64_t each) { return vs::align_up((size_t)(n * each), 256); };
+  const uint64_t bins = (uint64_t)sized_tiles * L.k;
+  w.total = off + bytes(sized_tiles, 4) + bytes(bins, 4) + 2 * bytes(bins, 8) + bytes(tris, 16) +
+            bytes((bins + 1023) / 1024, 8) + bytes(entries, 4);
   w.bin_view = take((size_t)w.n_tiles_bin * 4);
   w.recs = take((size_t)w.n_groups * sizeof(vs::GroupRec));
-  w.parts = take((size_t)parts_bytes);
-  w.list = take((size_t)w.capacity * 4);
-  w.total = off;
+  w.parts = take(vs::kParts * vs::kPartApart * 8);
+  w.list = off;
+  const uint64_t words = std::min<uint64_t>((w.total - off) / 4, vs::kListWords);
+  // a caller's count of entries is kept to exactly, in one part: a run never lacks the words then
+  w.room.parts = capacity > 0 ? 1 : vs::kParts;
+  w.room.words = (uint32_t)(words / w.room.parts);
+  w.room.entries = capacity > 0 ? (uint32_t)std::min<uint64_t>(entries, vs::kListWords) : ~0u;
   return w;
 }
 
@@ -276,7 +277,7 @@ vs_status vs_raster_layers(const vs_mesh* layers, int32_t k, const vs_views* vie
   auto* bin_view = (int32_t*)(base + lay.bin_view);
   auto* recs = (vs::GroupRec*)(base + lay.recs);
   auto* list = (uint32_t*)(base + lay.list);
-  auto* parts = (uint32_t*)(base + lay.parts);
+  auto* parts = (unsigned long long*)(base + lay.parts);
   const int64_t vpv = L.vert_off[k];
   const int nv = views->n_views;
   const int64_t ntri = L.tri_off[k];
@@ -311,7 +312,7 @@ vs_status vs_raster_layers(const vs_mesh* layers, int32_t k, const vs_views* vie
   const dim3 bin_grid((unsigned)((groups.off[k] + 7) / 8 * 8), (unsigned)nv);
   auto binned = [&](auto kern) {
     hipLaunchKernelGGL(kern, bin_grid, dim3(256), 0, s, views->dev, L, groups, (const vs::ProjVert*)proj, vpv, recs,
-                       list, lay.part_words, parts, status);
+                       list, lay.room, parts, status);
   };
   switch (B * 8 + lay.reps) {
     case 8 * 8 + 1: binned(vs::k_bin<8, 1>); break;

@@ -10,6 +10,7 @@
 #include <stdint.h>
 
 #include "vs.h"
+#include "vs_lists.h"
 
 namespace vs {
 
@@ -61,12 +62,11 @@ struct WsLayout {
   size_t bin_view;   // int32 [raster bin tiles of all views]: owning view
   size_t proj;       // ProjVert [n_views][sum n_vert]
   size_t recs;       // GroupRec [n_views][groups of a view]
-  size_t parts;      // u32: words taken from each part of the list
-  size_t list;       // u32 [capacity]: the groups' runs (tile tables, triangle ids, back faces' records)
+  size_t parts;      // u64 per part of the list: words taken, entries << 32
+  size_t list;       // u32: the groups' runs (tile tables, triangle ids, back faces' entries)
   int64_t n_tiles16, n_tiles_bin, n_bins, n_groups;   // groups: of all views
   int reps;          // triangles per thread of a group's block
-  uint32_t part_words;   // words of a part of the list
-  uint64_t capacity;   // words of the list
+  ListRoom room;
   int bin, slot;
   size_t total;
 };

@@ -8,24 +8,46 @@
 namespace vs {
 
 constexpr uint32_t kGroupNoRun = 0xffffffffu;
-constexpr int kParts = 8;   // parts of a view's list, one for the groups of each XCD
+constexpr uint32_t kListWords = 0xe0000000u;   // most words of the list
+constexpr int kParts = 8;                      // parts of the list, one for the groups of each XCD
+constexpr int kPartApart = 8;                  // 64-bit words from one part's counter to the next one's
 
-// Room for a run of `need` words: its first word in the view's kParts parts of part_words each, or
-// kGroupNoRun.  Part p's counter holds the words taken from it: load(p) reads it, add(p, n) adds n modulo
-// 2^32 and returns what it held before.  The own part's counter is added to at once (one round trip to
+// Tiles that the table of a group of 256 R triangles counts at most: record, table and total of a full group
+// take four words per triangle, what the workspace holds per triangle beside its entries.
+__host__ __device__ constexpr int group_tiles(int R) { return 4 * 256 * R - 5; }
+
+// Smallest shift, from s on, at which a rectangle of tiles has at most `most` macro tiles of 2^shift x 2^shift.
+__host__ __device__ inline int macro_shift(int x0, int y0, int x1, int y1, int most, int s) {
+  while (((x1 >> s) - (x0 >> s) + 1) * ((y1 >> s) - (y0 >> s) + 1) > most) ++s;
+  return s;
+}
+
+// The list's parts: `words` each, and `entries` (triangles in tiles) that their runs may have.
+struct ListRoom {
+  uint32_t words, entries;
+  int32_t parts;
+};
+
+// Room for a run of `need` words with `entries` entries: its first word in the list, or kGroupNoRun.  A
+// part's counter holds the words taken from it and, << 32, their entries: load(p) reads it, add(p, n) adds n
+// modulo 2^64 and returns what it held before.  The own part's counter is added to at once (one round trip to
 // memory); another part's is looked at first, as it is only tried when the own one is full.  What found no
-// room is taken off again, so that later and smaller runs find what is left and a counter never passes
-// part_words by more than one run for each block that is running (2,048 of at most 332 k words, with parts
-// of at most 2^29): it cannot wrap and hand out words that are taken.
+// room is taken off again, so that later and smaller runs find what is left and a counter never passes its
+// part by more than one run for each block that is running (2,048 of at most 135 k words: below 2^32 - kListWords):
+// it cannot wrap and hand out words that are taken.
 template <class Load, class Add>
-__host__ __device__ inline uint32_t reserve_run(uint32_t need, uint32_t part_words, uint32_t own, Load load, Add add) {
-  if (need > part_words) return kGroupNoRun;
-  for (uint32_t q = 0; q < (uint32_t)kParts; ++q) {
-    const uint32_t p = (own + q) % kParts;
-    if (q > 0 && load(p) > part_words - need) continue;
-    const uint32_t from = add(p, need);
-    if (from <= part_words - need) return p * part_words + from;
-    add(p, 0u - need);
+__host__ __device__ inline uint32_t reserve_run(uint32_t need, uint32_t entries, ListRoom room, uint32_t own, Load load, Add add) {
+  if (need > room.words || entries > room.entries) return kGroupNoRun;
+  const uint64_t mine = ((uint64_t)entries << 32) | need;
+  const auto fits = [&](uint64_t taken) {
+    return (uint32_t)taken <= room.words - need && (uint32_t)(taken >> 32) <= room.entries - entries;
+  };
+  for (uint32_t q = 0; q < (uint32_t)room.parts; ++q) {
+    const uint32_t p = (own + q) % (uint32_t)room.parts;
+    if (q > 0 && !fits(load(p))) continue;
+    const uint64_t taken = add(p, mine);
+    if (fits(taken)) return p * room.words + (uint32_t)taken;
+    add(p, 0ull - mine);
   }
   return kGroupNoRun;
 }

@@ -19,7 +19,6 @@
 #pragma once
 
 #include "vs_common.h"
-#include "vs_lists.h"
 
 namespace vs {
 
@@ -49,11 +48,10 @@ __global__ void __launch_bounds__(256) k_fill_u64(uint64_t* __restrict__ p, int6
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = val;
 }
 
-// The list is shared out in kParts equal parts per view, one for the groups of each XCD, in which runs
-// are reserved by atomics on the parts' own words, kPartApart words from each other: requests to one
-// word are served one after the other (about 6 ns each; on a single word 168k groups would take 1 ms).
-// A run that its part has no room for goes to the view's next parts.
-constexpr int kPartApart = 16;
+// The list is shared out in kParts equal parts, one for the groups of each XCD, in which runs are reserved by
+// atomics on the parts' own counters: requests to one word are served one after the other (about 6 ns each;
+// on a single word 168k groups would take 1 ms).  A run that its part has no room for goes to the next one
+// that has: the views share the whole list, whatever their sizes.
 
 // Everything that binning, drawing and shading find ready, one launch: the first blocks take step 1
 // for every (view, layer, vertex), proj_blocks per view; the next ones tile_view[g] = view owning
@@ -66,7 +64,7 @@ struct SetupArgs {
   int32_t* bin_view;
   int64_t n_tiles16, n_tiles_bin;
   unsigned long long* status;
-  uint32_t* parts;
+  unsigned long long* parts;
   int32_t n_views, slot, proj_blocks, tile_blocks;
 };
 
@@ -76,7 +74,7 @@ __global__ void __launch_bounds__(256) k_setup(SetupArgs A, LayerTable L) {
     const int v = (int)(blockIdx.x / (uint32_t)A.proj_blocks);
     const int64_t g = (int64_t)(blockIdx.x - (uint32_t)v * (uint32_t)A.proj_blocks) * 256 + threadIdx.x;
     if (blockIdx.x == 0 && threadIdx.x < VS_STAT_COUNT) A.status[threadIdx.x] = 0ull;
-    if (g < kParts) A.parts[(v * kParts + (int)g) * kPartApart] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x < kParts) A.parts[threadIdx.x * kPartApart] = 0ull;
     if (g >= A.vpv) return;
     int l = 0;
     while (l + 1 < L.k && L.vert_off[l + 1] <= g) ++l;
@@ -112,15 +110,7 @@ __device__ inline int cull_slot(int r) {
                                                                         : VS_STAT_BAD_INDEX;
 }
 
-// List record of one back-facing triangle in one bin, four words: its pixel
-// bounding box clipped to the view, packed in 52 bits,
-//   i0 | i1 << 13 | j0 << 26 | j1 << 39,
-// the depth bits of its lower-bound key (depth_lower_key >> 32), and its id.
-// "Front" marks a negative screen area before orientation normalisation,
-// which is the front side of an outward, counter-clockwise wound closed mesh
-// under this camera convention (y down).  Front faces are drawn first; the
-// raster uses the box and the bound to skip, without loading its vertices, a
-// back-facing triangle that cannot lower any key.
+// A triangle's pixel bounding box clipped to the view, packed in 52 bits: i0 | i1 << 13 | j0 << 26 | j1 << 39.
 __device__ inline uint64_t pack_box(int i0, int i1, int j0, int j1) {
   return (uint64_t)i0 | ((uint64_t)i1 << 13) | ((uint64_t)j0 << 26) | ((uint64_t)j1 << 39);
 }
@@ -135,19 +125,29 @@ struct BinGroups {
 };
 
 // Record of one group in one view.  Its tiles' rectangle is counted in macro tiles of
-// 2^shift x 2^shift bins (shift 0 unless the rectangle has more than kGroupTiles of them).  The
-// group's run of the list, from word `base` (a multiple of 4): per macro tile of the rectangle, row
+// 2^shift x 2^shift bins (shift 0 unless the rectangle has more of them than a table).  The
+// group's run of the list, from word `base`: per macro tile of the rectangle, row
 // by row, how many front-facing entries and, << 16, how many others come before its own, then both
-// totals in the same form; the front-facing entries (triangle ids); and, from the next multiple of 4
-// words, the others (records of 4 words).
+// totals in the same form; the front-facing entries (triangle ids); the others.
+// "Front" marks a negative screen area before orientation normalisation, which is the front side of
+// an outward, counter-clockwise wound closed mesh under this camera convention (y down).  Front
+// faces are drawn first; an entry of another triangle says where it lies in the macro tile and how
+// near it can be, so that the raster can skip one that cannot lower any key without loading its
+// vertices:
+//   index in the group | box << 10 | depth << 22,
+// the box in units of unit_log(B, shift) pixels from the macro tile's corner (first column, first
+// row, last column, last row, three bits each), the depth as (z - near) >> near_shift in 10 bits, z the
+// high word of the triangle's depth_lower_key and near the group's smallest one, its low 19 bits
+// cleared: no larger than z when taken apart, and as fine as a thousandth of the group's range.
 struct alignas(16) GroupRec {
   uint16_t tx0, ty0, tw, th;   // tw = 0: reaches no bin
   uint32_t base;               // kGroupNoRun: no room in the list, its bins go through all of its triangles
-  uint32_t shift;
+  uint32_t form;               // shift | near_shift << 4 | near >> 19 << 9
 };
-constexpr int kGroupTiles = 4096;
 constexpr uint32_t kSegAll = 0xf0000000u;   // a raster segment of all triangles from id base - kSegAll on; the list ends before it
-
+static_assert(kListWords <= kSegAll, "words of the list and triangle ids of a segment are told apart");
+__host__ __device__ constexpr int bin_log(int B) { return B == 64 ? 6 : B == 32 ? 5 : B == 16 ? 4 : 3; }
+__host__ __device__ inline int unit_log(int B, int shift) { return max(3, bin_log(B) + shift - 3); }
 
 // Triangles per thread of a group's block: larger groups cost a bin fewer runs to go through, smaller
 // ones fill the chip.  One 1024^2 view of seven layers (696 groups of 1,024), binning and raster kernel
@@ -164,15 +164,18 @@ inline int bin_reps(int64_t n_tri, int n_views) {
 // scatter that read the records back: metric scene 1.49 -> 0.39 ms, k = 9 scene 3.61 -> 1.34 ms, one
 // 1024^2 view 99 -> 15 us (the raster kernel, which now looks the runs up, 2.36 -> 2.66 ms, 2.87 -> 3.45 ms and
 // 70 -> 74 us).
+// One word an entry, front-facing or not, and one list for all views: 64 views at 800^2 of three shells of
+// 1,292 triangles take 0.77 ms in all and every group has a run; records of four words and a list shared out to
+// the views in equal parts left more than half of the groups without one (1.82 ms; 2.79 with lists per bin).
 template <int B, int R>
 __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, LayerTable L, BinGroups Q,
                                              const ProjVert* __restrict__ proj, int64_t vpv,
-                                             GroupRec* __restrict__ recs, uint32_t* __restrict__ list, uint32_t part_words,
-                                             uint32_t* __restrict__ parts,
+                                             GroupRec* __restrict__ recs, uint32_t* __restrict__ list, ListRoom room,
+                                             unsigned long long* __restrict__ parts,
                                              unsigned long long* __restrict__ status) {
   constexpr int BH = bin_rows(B);
-  __shared__ uint32_t hist[kGroupTiles];   // per macro tile: front entries, other entries << 16; then their next places
-  __shared__ int32_t ext[4][4];
+  __shared__ uint32_t hist[group_tiles(R)];   // per macro tile: front entries, other entries << 16; then their next places
+  __shared__ int32_t ext[4][6];
   __shared__ uint32_t sums[4][2];
   __shared__ uint32_t run_base;
   const int k = L.k, tid = threadIdx.x, wv = tid >> 6, lane = tid & 63;
@@ -210,9 +213,9 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
   fetch(0, qa);
   if (R > 1) fetch(1, qb);
   uint64_t box[R];
-  uint32_t zlo[R];
+  int32_t zlo[R];
   uint32_t live = 0, front = 0;
-  int32_t ex0 = INT32_MAX, ey0 = INT32_MAX, ex1 = -1, ey1 = -1;
+  int32_t ex0 = INT32_MAX, ey0 = INT32_MAX, ex1 = -1, ey1 = -1, near = INT32_MAX, far = 0;   // tiles, depth bounds
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     TriLoad& qr = (r & 1) ? qb : qa;
@@ -229,41 +232,46 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
         if (pr.i0 <= pr.i1 && pr.j0 <= pr.j1) {
           const int tx0 = pr.i0 / B, tx1 = pr.i1 / B, ty0 = pr.j0 / BH, ty1 = pr.j1 / BH;
           box[r] = pack_box(pr.i0, pr.i1, pr.j0, pr.j1);
-          zlo[r] = (uint32_t)(depth_lower_key(T, (uint32_t)t) >> 32);
           ex0 = min(ex0, tx0); ey0 = min(ey0, ty0); ex1 = max(ex1, tx1); ey1 = max(ey1, ty1);
           live |= 1u << r;
-          if (T.orig_sign < 0) front |= 1u << r;
+          if (T.orig_sign < 0) {
+            front |= 1u << r;
+          } else {
+            zlo[r] = (int32_t)(depth_lower_key(T, (uint32_t)t) >> 32);   // a positive float's bits: in order as integers
+            near = min(near, zlo[r]); far = max(far, zlo[r]);
+          }
         }
       }
     }
     if (r + 2 < R) fetch(r + 2, qr);   // this record slot is free now
   }
-  // the group's rectangle of tiles
+  // the group's rectangle of tiles, and the depth bounds of its triangles that are not front-facing
   ex0 = wave_min(ex0); ey0 = wave_min(ey0); ex1 = wave_max(ex1); ey1 = wave_max(ey1);
+  near = wave_min(near); far = wave_max(far);
   if (lane == 0) {
-    ext[wv][0] = ex0; ext[wv][1] = ey0; ext[wv][2] = ex1; ext[wv][3] = ey1;
+    ext[wv][0] = ex0; ext[wv][1] = ey0; ext[wv][2] = ex1; ext[wv][3] = ey1; ext[wv][4] = near; ext[wv][5] = far;
   }
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
     ex0 = min(ex0, ext[w][0]); ey0 = min(ey0, ext[w][1]); ex1 = max(ex1, ext[w][2]); ey1 = max(ey1, ext[w][3]);
+    near = min(near, ext[w][4]); far = max(far, ext[w][5]);
   }
   ex0 = __builtin_amdgcn_readfirstlane(ex0); ey0 = __builtin_amdgcn_readfirstlane(ey0);
   ex1 = __builtin_amdgcn_readfirstlane(ex1); ey1 = __builtin_amdgcn_readfirstlane(ey1);
   GroupRec out;
   out.tx0 = out.ty0 = out.tw = out.th = 0;
   out.base = kGroupNoRun;
-  out.shift = 0;
+  out.form = 0;
   if (ex1 < ex0) {   // uniform
     if (tid == 0) *rec = out;
     return;
   }
-  int s = 0;
-  while (((ex1 >> s) - (ex0 >> s) + 1) * ((ey1 >> s) - (ey0 >> s) + 1) > kGroupTiles) ++s;
+  const int s = macro_shift(ex0, ey0, ex1, ey1, group_tiles(R), 0);
   const int rx = ex0 >> s, ry = ey0 >> s, tw = (ex1 >> s) - rx + 1, th = (ey1 >> s) - ry + 1, n = tw * th;
   for (int e = tid; e < n; e += 256) hist[e] = 0;
   __syncthreads();
-  // each (triangle, macro tile): use(its histogram word, what to add to it)
+  // each (triangle, macro tile): use(repetition, tile's column and row, its histogram word, front-facing)
   auto each = [&](auto use) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -273,10 +281,10 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
       const int x0 = (i0 / B) >> s, y0 = (j0 / BH) >> s, x1 = (i1 / B) >> s, y1 = (j1 / BH) >> s;
       const bool f = (front >> r) & 1u;
       for (int y = y0; y <= y1; ++y)
-        for (int x = x0; x <= x1; ++x) use(r, &hist[(y - ry) * tw + (x - rx)], f);
+        for (int x = x0; x <= x1; ++x) use(r, x, y, &hist[(y - ry) * tw + (x - rx)], f);
     }
   };
-  each([&](int, uint32_t* h, bool f) { atomicAdd(h, f ? 1u : 0x10000u); });
+  each([&](int, int, int, uint32_t* h, bool f) { atomicAdd(h, f ? 1u : 0x10000u); });
   __syncthreads();
   // exclusive prefix sums over the tiles, `per` consecutive ones per thread
   const int per = (n + 255) / 256, e0 = min(tid * per, n), e1 = min(e0 + per, n);
@@ -309,20 +317,20 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
     total_f += sums[w][0];
     total_o += sums[w][1];
   }
-  const uint32_t others = ((uint32_t)n + 1u + total_f + 3u) & ~3u, need = others + 4u * total_o;   // words
+  const uint32_t entries = total_f + total_o, need = (uint32_t)n + 1u + entries;   // words
+  near = __builtin_amdgcn_readfirstlane(total_o ? near & ~0x7ffff : 0);
+  far = __builtin_amdgcn_readfirstlane(total_o ? far : 0);
+  const int near_shift = max(0, 22 - __clz(far - near));   // the range in 10 bits
   if (tid == 0) {
     uint32_t base = kGroupNoRun;
-    if (total_f <= 0xffffu && total_o <= 0xffffu) {
-      uint32_t* mine = parts + v * kParts * kPartApart;
-      base = reserve_run(need, part_words, blockIdx.x & (kParts - 1),
-                         [&](uint32_t p) { return __hip_atomic_load(mine + p * kPartApart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
-                         [&](uint32_t p, uint32_t n) { return atomicAdd(mine + p * kPartApart, n); });
-      if (base != kGroupNoRun) base += (uint32_t)v * kParts * part_words;
-    }
+    if (total_f <= 0xffffu && total_o <= 0xffffu)
+      base = reserve_run(need, entries, room, blockIdx.x,
+                         [&](uint32_t p) { return __hip_atomic_load(parts + p * kPartApart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+                         [&](uint32_t p, uint64_t n) { return atomicAdd(parts + p * kPartApart, (unsigned long long)n); });
     run_base = base;
     out.tx0 = (uint16_t)rx; out.ty0 = (uint16_t)ry; out.tw = (uint16_t)tw; out.th = (uint16_t)th;
     out.base = base;
-    out.shift = (uint32_t)s;
+    out.form = (uint32_t)s | (uint32_t)near_shift << 4 | (uint32_t)near >> 19 << 9;
     *rec = out;
   }
   __syncthreads();
@@ -338,11 +346,21 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
   if (tid == 0) list[base + n] = total_f | (total_o << 16);
   __syncthreads();
   uint32_t* fronts = list + base + n + 1;
-  uint4* rest = reinterpret_cast<uint4*>(list + base + others);
-  each([&](int r, uint32_t* h, bool is_front) {
-    const uint32_t old = atomicAdd(h, is_front ? 1u : 0x10000u), t = (uint32_t)(t0 + 256 * r);
-    if (is_front) fronts[old & 0xffffu] = t;
-    else rest[old >> 16] = make_uint4((uint32_t)box[r], (uint32_t)(box[r] >> 32), zlo[r], t);
+  uint32_t* rest = fronts + total_f;
+  const int ul = unit_log(B, s);
+  each([&](int r, int x, int y, uint32_t* h, bool is_front) {
+    const uint32_t old = atomicAdd(h, is_front ? 1u : 0x10000u);
+    if (is_front) {
+      fronts[old & 0xffffu] = (uint32_t)(t0 + 256 * r);
+    } else {
+      int i0, i1, j0, j1;
+      unpack_box(box[r], i0, i1, j0, j1);
+      const int ax = x * (B << s), ay = y * (BH << s);
+      const uint32_t c0 = (uint32_t)(max(i0 - ax, 0) >> ul), c1 = (uint32_t)(min(i1 - ax, (B << s) - 1) >> ul);
+      const uint32_t r0 = (uint32_t)(max(j0 - ay, 0) >> ul), r1 = (uint32_t)(min(j1 - ay, (BH << s) - 1) >> ul);
+      rest[old >> 16] = (uint32_t)(256 * r + tid) | c0 << 10 | r0 << 13 | c1 << 16 | r1 << 19 |
+                        (uint32_t)(zlo[r] - near) >> near_shift << 22;
+    }
   });
 }
 
@@ -386,7 +404,7 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
     const uint32_t* __restrict__ list, unsigned long long* __restrict__ vis,
     unsigned long long* __restrict__ status, int count_frags) {
   constexpr int BH = bin_rows(B);              // bin rows
-  constexpr int kSub = B < 8 ? B : 8;          // sub-tile edge of the depth bound
+  constexpr int kSub = 8;                      // sub-tile edge of the depth bound
   constexpr int kNs = B / kSub;                // sub-tiles per row
   constexpr int kNsY = BH / kSub;              // sub-tile rows
   static_assert(B % kSub == 0 && BH % kSub == 0, "bins must be whole sub-tiles");
@@ -396,10 +414,12 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
   __shared__ int32_t late_bigs[kBigQueue];        // large triangles among those (large front-facing ones: in the queue)
   __shared__ uint32_t qadd[3], bign;              // entries queued by a chunk, for three chunks in turn
   __shared__ uint32_t seg_base[kSegs];            // groups that reach the tile: list word of their first front-facing entry here
-  __shared__ uint32_t seg_rest[kSegs];            // ... 16-byte record of their first other entry
+  __shared__ uint32_t seg_rest[kSegs];            // ... from there to their first other entry | shift << 18 | near_shift << 22
+  __shared__ uint32_t seg_group[kSegs];           // ... the group's number in the layer << 12 | near >> 19
   __shared__ uint32_t seg_start[kSegs];           // ... and the entries before it, front-facing ones and others << 16
   __shared__ uint32_t seg_n[3];                   // groups, front-facing entries, other entries
-  __shared__ uint32_t wave_n[kRasterThreads / 64];
+  __shared__ uint32_t wave_n[2][kRasterThreads / 64];   // groups found by each wavefront, for two batches in turn
+  __shared__ uint32_t no_run;                     // a group without a run reaches this tile
   const int k = L.k;
   const int64_t n_bins = n_tiles * k;
   // XCD-contiguous remap of the block index
@@ -417,7 +437,7 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
   const int x0 = tx * B, y0 = ty * BH;
   const int x1 = min(x0 + B, W) - 1, y1 = min(y0 + BH, H) - 1;
   const int tid = threadIdx.x, lane = tid & 63;
-  if (tid == 0) qadd[0] = qadd[1] = qadd[2] = bign = 0;
+  if (tid == 0) qadd[0] = qadd[1] = qadd[2] = bign = no_run = 0;
   for (int p = tid; p < B * BH / 2; p += kRasterThreads)   // 16-byte stores
     reinterpret_cast<ulonglong2*>(tile)[p] = make_ulonglong2(kEmpty, kEmpty);
   const ProjVert* P = proj + (int64_t)v * vpv + L.vert_off[l];
@@ -425,18 +445,18 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
   const int32_t nvert = L.n_vert[l];
   const GroupRec* grec = recs + (int64_t)v * Q.off[k] + Q.off[l];
   const int n_groups = Q.off[l + 1] - Q.off[l], n_tri = L.n_tri[l];
-  bool overflow = false;   // a group without a run reaches this tile
   unsigned long long frags = 0;
   // Loads the groups from g0 on that reach this tile, as many as kSegs holds, and returns the group to go
   // on from.  All triangles of a group without a run are taken for front-facing: nothing is skipped then.
   // Called by the whole block.
   auto load_segs = [&](int g0) -> int {
-    int have = 0;
-    while (g0 < n_groups) {   // uniform: 256 groups at a time, 64 where more than kSegs of those reach the tile
-      uint32_t base = 0, rest = 0, nf = 0, nb = 0;
+    int have = 0, turn = 0;
+    while (g0 < n_groups) {   // uniform: 256 groups at a time, kSegs where more than kSegs of those reach the tile
+      uint32_t base = 0, rest = 0, near = 0, nf = 0, nb = 0;
       if (g0 + tid < n_groups) {
         const uint4 raw = *reinterpret_cast<const uint4*>(grec + g0 + tid);
-        const int mx = (tx >> raw.w) - (int)(raw.x & 0xffffu), my = (ty >> raw.w) - (int)(raw.x >> 16);
+        const int s = (int)(raw.w & 15u);
+        const int mx = (tx >> s) - (int)(raw.x & 0xffffu), my = (ty >> s) - (int)(raw.x >> 16);
         const int tw = (int)(raw.y & 0xffffu), th = (int)(raw.y >> 16);
         if (mx >= 0 && mx < tw && my >= 0 && my < th) {
           if (raw.z == kGroupNoRun) {
@@ -448,31 +468,37 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
             const uint32_t ids = raw.z + (uint32_t)(tw * th) + 1u, total_f = list[ids - 1u] & 0xffffu;
             base = ids + (at & 0xffffu);
             nf = (next & 0xffffu) - (at & 0xffffu);
-            rest = ((ids + total_f + 3u) >> 2) + (at >> 16);
+            rest = (total_f - (at & 0xffffu) + (at >> 16)) | (raw.w & 15u) << 18 | (raw.w >> 4 & 31u) << 22;
+            near = raw.w >> 9;
             nb = (next >> 16) - (at >> 16);
           }
         }
       }
       bool hit = nf + nb > 0;
-      int width = kRasterThreads, m = __syncthreads_count(hit);
+      uint64_t hits = __ballot(hit);
+      int width = kRasterThreads, m = 0;
+      if (lane == 0) wave_n[turn][tid >> 6] = (uint32_t)__popcll(hits);
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kRasterThreads / 64; ++w) m += (int)wave_n[turn][w];
       if (have + m > kSegs) {
         if (have > 0) break;
-        width = kSegs;
+        width = kSegs;      // the first wavefront's groups alone; only it reads `have`
         hit = hit && tid < kSegs;
-        m = __syncthreads_count(hit);
+        hits = __ballot(hit);
+        m = __popcll(hits);
       }
-      const uint64_t hits = __ballot(hit);
-      if (lane == 0) wave_n[tid >> 6] = (uint32_t)__popcll(hits);
-      __syncthreads();
       if (hit) {
         uint32_t at = (uint32_t)have + (uint32_t)__popcll(hits & __lanemask_lt());
-        for (int w = 0; w < (tid >> 6); ++w) at += wave_n[w];
+        for (int w = 0; w < (tid >> 6); ++w) at += wave_n[turn][w];
         seg_base[at] = base;
         seg_rest[at] = rest;
+        seg_group[at] = (uint32_t)(g0 + tid) << 12 | near;
         seg_start[at] = nf | (nb << 16);
       }
       have += m;
       g0 += width;
+      turn ^= 1;
       if (width < kRasterThreads) break;
     }
     __syncthreads();
@@ -511,9 +537,25 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
     const uint32_t a = find_seg(c, 0), at = seg_base[a] + c - (seg_start[a] & 0xffffu);
     return at >= kSegAll ? (int32_t)(at - kSegAll) : (int32_t)list[at];
   };
-  auto other_entry = [&](uint32_t c) -> uint4 {
-    const uint32_t a = find_seg(c, 16);
-    return reinterpret_cast<const uint4*>(list)[seg_rest[a] + c - (seg_start[a] >> 16)];
+  // Other entry c of the loaded groups: its triangle; the columns and rows of 8 x 8 sub-tiles of this bin that its box
+  // may reach, none if first > last; and a bound that no depth word of its keys is below.
+  struct Other {
+    int32_t t, c0, c1, r0, r1;
+    uint32_t z;
+  };
+  auto other_entry = [&](uint32_t c) -> Other {
+    const uint32_t a = find_seg(c, 16), rest = seg_rest[a], group = seg_group[a];
+    const uint32_t e = list[seg_base[a] + (rest & 0x3ffffu) + c - (seg_start[a] >> 16)];
+    const int s = (int)(rest >> 18 & 15u), ul = unit_log(B, s), in = (1 << s) - 1;
+    const int dx = (tx & in) * B, dy = (ty & in) * BH;   // this bin's corner in the macro tile
+    Other o;
+    o.t = (int32_t)((group >> 12 << group_log) + (e & 1023u));
+    o.c0 = max(((int)(e >> 10 & 7u) << ul) - dx, 0) >> 3;
+    o.r0 = max(((int)(e >> 13 & 7u) << ul) - dy, 0) >> 3;
+    o.c1 = min((((int)(e >> 16 & 7u) + 1) << ul) - 1 - dx, B - 1) >> 3;
+    o.r1 = min((((int)(e >> 19 & 7u) + 1) << ul) - 1 - dy, BH - 1) >> 3;
+    o.z = ((group & 0xfffu) << 19) + (e >> 22 << (rest >> 22));
+    return o;
   };
   __syncthreads();
   // Triangles drawn by the whole wavefront, one after the other: every lane's triangle (big < 0:
@@ -635,7 +677,7 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
       for (uint32_t c = 0; c < n; c += kRasterThreads) {
         int32_t t = -1;
         if (c + dealt < n) {
-          const int32_t tc = fronts ? front_entry(c + dealt) : (int32_t)other_entry(c + dealt).w;
+          const int32_t tc = fronts ? front_entry(c + dealt) : other_entry(c + dealt).t;
           TriSetup T;
           if (setup_triangle<true>(tri, (uint32_t)tc, nvert, P, T) == kTriOk) {
             const PixRange pr = pixel_range(T, W, H);
@@ -657,7 +699,7 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
     g0 = next;
     const uint32_t n_front = seg_n[1], n_back = seg_n[2];
     any_back = any_back || n_back > 0;
-    if (tid < (int)seg_n[0]) overflow = overflow || seg_base[tid] >= kSegAll;
+    if (tid < (int)seg_n[0] && seg_base[tid] >= kSegAll) no_run = 1;
     for (uint32_t c0 = 0; c0 < n_front; c0 += kRasterThreads) {
       const int sh = share(n_front - c0);
       const uint32_t c = c0 + (tid >> sh);
@@ -692,7 +734,7 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
       }
     }
     __syncthreads();
-    // phase 2: each back-facing entry is tested from its record (box and depth bound) alone;
+    // phase 2: each back-facing entry is tested from its word (box and depth bound) alone;
     // the ones that may lower a key are queued in LDS and drawn 256 at a time, so that the
     // skipped majority costs no vertex loads and leaves no idle lanes behind.  A wavefront may be at the
     // next chunk while another still reads what this one queued: each chunk counts in a word of its own,
@@ -707,16 +749,11 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
         bool keep = false;
         int32_t t = 0;
         if (c < n) {
-          const uint4 r = other_entry(c);
-          t = (int32_t)r.w;
+          const Other o = other_entry(c);
+          t = o.t;
           keep = count_frags != 0;   // every covered pixel is counted then: nothing is skipped
-          int i0, i1, j0, j1;
-          unpack_box((uint64_t)r.x | ((uint64_t)r.y << 32), i0, i1, j0, j1);
-          const int ci0 = max(i0, x0), ci1 = min(i1, x1), cj0 = max(j0, y0), cj1 = min(j1, y1);
-          if (ci0 <= ci1 && cj0 <= cj1)   // an entry of a macro tile may lie in other bins of it only
-            for (int sj = (cj0 - y0) / kSub; sj <= (cj1 - y0) / kSub; ++sj)
-              for (int si = (ci0 - x0) / kSub; si <= (ci1 - x0) / kSub; ++si)
-                keep = keep || smax[sj * kNs + si] >= r.z;
+          for (int sj = o.r0; sj <= o.r1; ++sj)
+            for (int si = o.c0; si <= o.c1; ++si) keep = keep || smax[sj * kNs + si] >= o.z;
         }
         const uint64_t kb = __ballot(keep);
         uint32_t base = 0;
@@ -768,7 +805,7 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
     for (int off = 32; off > 0; off >>= 1) frags += __shfl_xor(frags, off);
     if ((tid & 63) == 0 && frags) atomicAdd(status + VS_STAT_FRAGMENTS, frags);
   }
-  if (__syncthreads_or(overflow) && tid == 0) atomicAdd(status + VS_STAT_BIN_OVERFLOW, 1ull);
+  if (tid == 0 && no_run) atomicAdd(status + VS_STAT_BIN_OVERFLOW, 1ull);
 }
 
 // Steps 2-3, direct form (reference path for tests): one thread per (view,

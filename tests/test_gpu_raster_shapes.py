@@ -116,3 +116,50 @@ def test_library_choice_of_bin(k, size):
     for b in (16, 32, 64):
         other, ws2 = P.raster(layers, views, bin=b, count_fragments=True)
         assert torch.equal(vis, other) and P.read_status(ws2)["fragments"] == st["fragments"], b
+
+
+@pytest.mark.parametrize("k,lat,lon,sizes", [
+    (3, 20, 34, [(800, 800)] * 64),
+    (1, 20, 34, [(800, 800)] * 100),
+    (5, 20, 40, [(1600, 1080)] * 24),
+    (7, 20, 34, [(96, 96)] * 40 + [(4096, 4096)] + [(96, 96)] * 23),
+])
+def test_coarse_shells_in_many_views(k, lat, lon, sizes):
+    """Large triangles in many views, and one large view among small ones: the default workspace holds all their entries."""
+    import torch
+    import paper_2409_02482_amd as P
+    say(f"[gpu] coarse shells k={k} {lat}x{lon} {len(sizes)} views")
+    layers = P.Layers(S.displaced_shells(2, k, lat, lon))
+    views = P.Views(S.ring_cameras(5, len(sizes), sizes))
+    vis, ws = P.raster(layers, views)
+    assert P.read_status(ws)["bin_overflow"] == 0
+    direct, _ = P.raster(layers, views, direct=True)
+    assert torch.equal(vis, direct)
+
+
+@pytest.mark.parametrize("bin", [8, 32, 64])
+@pytest.mark.parametrize("boxes,size", [(SMALL, (8192, 72)), (LARGE, (2048, 1100)), (SMALL + LARGE, (300, 5000))])
+def test_depth_bounds_of_back_faces(bin, boxes, size):
+    """Both windings over many depths, in macro tiles of one to several bins: a back face is skipped only where it cannot be
+    seen.  Against the unbinned path, with and without the fragment count that skips nothing."""
+    import torch
+    import paper_2409_02482_amd as P
+    sc = _soup(5, 3000, boxes, size)
+    layers, views = P.Layers(sc.layers), P.Views(sc.cameras)
+    say(f"[gpu] soup of 3000 {size} bin {bin}")
+    direct, ws = P.raster(layers, views, direct=True, count_fragments=True)
+    frags = P.read_status(ws)["fragments"]
+    assert torch.equal(P.raster(layers, views, bin=bin)[0], direct)
+    vis, ws = P.raster(layers, views, bin=bin, count_fragments=True)
+    assert torch.equal(vis, direct) and P.read_status(ws)["fragments"] == frags
+
+
+def test_capacity_is_a_count_of_pairs():
+    """list_capacity counts (triangle, bin) pairs: as many as the scene has fit, one fewer does not."""
+    from test_list_room import _boxes
+    sc = _shuffled(2, 60, 120, [(200, 150), (90, 140)])
+    b = _boxes(sc.layers, sc.cameras)
+    b = b[b[:, 0] == 1]
+    pairs = int(((b[:, 3] // 64 - b[:, 2] // 64 + 1) * (b[:, 5] // 56 - b[:, 4] // 56 + 1)).sum())
+    assert _check(sc, "capacity of all pairs", list_capacity=pairs)["bin_overflow"] == 0
+    assert _check(sc, "capacity one short", list_capacity=pairs - 1)["bin_overflow"] > 0

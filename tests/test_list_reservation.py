@@ -21,12 +21,13 @@ DRIVER = r'''
 #include <vector>
 #include "vs_lists.h"
 
-static std::atomic<uint32_t> counters[vs::kParts];
+static std::atomic<uint64_t> counters[vs::kParts];
+static std::atomic<uint32_t> narrow[vs::kParts];
 
 static uint32_t leaves_it(uint32_t need, uint32_t part_words, uint32_t own) {
   for (uint32_t q = 0; q < (uint32_t)vs::kParts; ++q) {
     const uint32_t p = (own + q) % vs::kParts;
-    const uint32_t from = counters[p].fetch_add(need);
+    const uint32_t from = narrow[p].fetch_add(need);
     if (from <= part_words - need) return p * part_words + from;
   }
   return vs::kGroupNoRun;
@@ -38,14 +39,15 @@ int main(int, char** a) {
   std::mt19937 rng(atoi(a[5]));
   std::vector<uint32_t> need(groups), base(groups);
   for (auto& n : need) n = std::uniform_int_distribution<uint32_t>(lo, hi)(rng);
+  const vs::ListRoom room = {part, ~0u, vs::kParts};
   for (int rule = 0; rule < 2; ++rule) {
     for (auto& c : counters) c = 0;
     std::atomic<uint32_t> next(0);
     auto work = [&] {
       for (uint32_t g; (g = next++) < groups;)
         base[g] = rule ? leaves_it(need[g], part, g & 7)
-                       : vs::reserve_run(need[g], part, g & 7, [](uint32_t p) { return counters[p].load(); },
-                                         [](uint32_t p, uint32_t n) { return counters[p].fetch_add(n); });
+                       : vs::reserve_run(need[g], need[g] / 2, room, g, [](uint32_t p) { return counters[p].load(); },
+                                         [](uint32_t p, uint64_t n) { return counters[p].fetch_add(n); });
     };
     std::vector<std::thread> pool;
     for (int t = 0; t < threads; ++t) pool.emplace_back(work);
@@ -60,7 +62,7 @@ int main(int, char** a) {
       }
     std::sort(runs.begin(), runs.end());
     for (size_t i = 1; i < runs.size(); ++i) overlaps += runs[i].first < runs[i - 1].second;
-    for (auto& c : counters) past += c > part;
+    for (auto& c : counters) past += (uint32_t)c.load() > part;
     printf("%zu %llu %llu %llu %llu\n", runs.size(), (unsigned long long)words, (unsigned long long)overlaps,
            (unsigned long long)outside, (unsigned long long)past);
   }
@@ -73,7 +75,7 @@ def driver(tmp_path_factory):
     d = tmp_path_factory.mktemp("lists")
     src, exe = d / "driver.hip", d / "driver"
     src.write_text(DRIVER)
-    subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-O2", "-std=c++17", "-pthread", "-I", CSRC, str(src), "-o", str(exe)])
+    subprocess.check_call([HIPCC, "--offload-host-only", "-O2", "-std=c++17", "-pthread", "-I", CSRC, str(src), "-o", str(exe)])
 
     def run(*args):
         rows = subprocess.check_output([str(exe), *[str(a) for a in args]], text=True).split("\n")[:2]

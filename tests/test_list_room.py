@@ -1,0 +1,199 @@
+"""CPU replay of the room that the raster's list has: every group's run is reserved as the binning kernel reserves it, by
+the library's own layout and reservation compiled for the host, in the workspace that the ABI asks for."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle as O
+import scenes as S
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2409_02482_amd", "csrc")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+# input words: k, n_views, bin, seed, capacity low, high; n_tri[k], n_vert[k]; (width, height)[n_views]; then per view, layer
+# and triangle: live, front, i0, i1, j0, j1.  Without boxes (seed < 0) only the layout is printed.
+DRIVER = r'''
+#include <random>
+#include "vs_api.hip"
+
+int main(int, char** a) {
+  FILE* f = fopen(a[1], "rb");
+  auto next = [&] { int32_t x = 0; if (fread(&x, 4, 1, f) != 1) abort(); return x; };
+  const int k = next(), nv = next(), bin = next(), seed = next();
+  const uint32_t lo = (uint32_t)next(), hi = (uint32_t)next();
+  const int64_t capacity = (int64_t)(((uint64_t)hi << 32) | lo);
+  vs::LayerTable L;
+  memset(&L, 0, sizeof(L));
+  L.k = k;
+  for (int l = 0; l < k; ++l) L.n_tri[l] = next(), L.tri_off[l + 1] = L.tri_off[l] + L.n_tri[l];
+  for (int l = 0; l < k; ++l) L.n_vert[l] = next(), L.vert_off[l + 1] = L.vert_off[l] + L.n_vert[l];
+  std::vector<vs_camera> cams(nv);
+  for (auto& c : cams) {
+    memset(&c, 0, sizeof(c));
+    c.width = next(); c.height = next();
+    c.fx = c.fy = 1.0; c.z_near = 0.1;
+  }
+  std::vector<vs_view> table(nv + 1);
+  if (vs_views_prepare(cams.data(), nv, table.data())) abort();
+  vs_views views;
+  memset(&views, 0, sizeof(views));
+  views.host = table.data(); views.dev = table.data(); views.n_views = nv;
+  const vs::WsLayout w = ws_layout(L, &views, bin, capacity);
+  printf("%zu %zu %u %u %d %d %d\n", w.total, w.list + (size_t)w.room.parts * w.room.words * 4, w.room.words, w.room.entries,
+         w.room.parts, w.bin, w.reps);
+  if (seed < 0) return 0;
+  const int B = w.bin, BH = vs::bin_rows(B), G = 256 * w.reps;
+  struct Group { uint32_t need, entries, own; };
+  std::vector<Group> groups;
+  uint64_t pairs = 0;
+  for (int v = 0; v < nv; ++v)
+    for (int l = 0, own = 0; l < k; ++l)
+      for (int t0 = 0; t0 < L.n_tri[l]; t0 += G, ++own) {
+        std::vector<std::array<int, 4>> box;
+        int e[4] = {1 << 30, 1 << 30, -1, -1};
+        for (int t = t0; t < std::min(t0 + G, L.n_tri[l]); ++t) {
+          const int live = next();
+          next();
+          const int i0 = next(), i1 = next(), j0 = next(), j1 = next();
+          if (!live) continue;
+          box.push_back({i0 / B, j0 / BH, i1 / B, j1 / BH});
+          for (int q = 0; q < 2; ++q) e[q] = std::min(e[q], box.back()[q]), e[2 + q] = std::max(e[2 + q], box.back()[2 + q]);
+          pairs += (uint64_t)(i1 / B - i0 / B + 1) * (j1 / BH - j0 / BH + 1);
+        }
+        if (box.empty()) continue;
+        const int s = vs::macro_shift(e[0], e[1], e[2], e[3], vs::group_tiles(w.reps), 0);
+        const uint32_t n = ((e[2] >> s) - (e[0] >> s) + 1) * ((e[3] >> s) - (e[1] >> s) + 1);
+        uint32_t entries = 0;
+        for (auto& b : box) entries += ((b[2] >> s) - (b[0] >> s) + 1) * ((b[3] >> s) - (b[1] >> s) + 1);
+        groups.push_back({n + 1 + entries, entries, (uint32_t)own});
+      }
+  std::shuffle(groups.begin(), groups.end(), std::mt19937(seed));
+  uint64_t counters[vs::kParts] = {};
+  size_t without = 0;
+  uint64_t words = 0;
+  for (auto& g : groups) {
+    words += g.need;
+    without += vs::kGroupNoRun == vs::reserve_run(g.need, g.entries, w.room, g.own, [&](uint32_t p) { return counters[p]; },
+                                                  [&](uint32_t p, uint64_t n) { const uint64_t c = counters[p]; counters[p] += n; return c; });
+  }
+  printf("%zu %zu %llu %llu\n", groups.size(), without, (unsigned long long)pairs, (unsigned long long)words);
+}
+'''
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    d = tmp_path_factory.mktemp("room")
+    src, exe = d / "driver.hip", d / "driver"
+    src.write_text("#include <array>\n" + DRIVER)
+    # host code only: the device image that it would register is absent, and nothing is launched
+    subprocess.check_call([HIPCC, "--offload-host-only", "-O1", "-std=c++17", "-w", "-ffp-contract=off", "-I",
+                           os.path.join(ROOT, "include"), "-I", CSRC, "-Wl,--unresolved-symbols=ignore-all", str(src), "-o", str(exe)])
+
+    def run(n_tri, n_vert, sizes, bin=0, capacity=0, seed=-1, boxes=None):
+        head = [len(n_tri), len(sizes), bin, seed, capacity & 0xffffffff, capacity >> 32, *n_tri, *n_vert, *np.ravel(sizes)]
+        with open(d / "in", "wb") as f:
+            f.write(np.array(head, np.int64).astype(np.uint32).tobytes())
+            if boxes is not None:
+                f.write(np.ascontiguousarray(boxes, np.int32).tobytes())
+        rows = subprocess.check_output([str(exe), str(d / "in")], text=True).split("\n")
+        lay = dict(zip(("total", "end", "words", "entries", "parts", "bin", "reps"), map(int, rows[0].split())))
+        if boxes is not None:
+            lay.update(zip(("groups", "without", "pairs", "need"), map(int, rows[1].split())))
+        return lay
+    return run
+
+
+def _boxes(layers, cams):
+    """Per view, layer and triangle: live, front, i0, i1, j0, j1 (the raster's cull and clip)."""
+    out = []
+    for cam in cams:
+        for m in layers:
+            X, Y, _, ok = O.project(m, cam)
+            x, y = X[m.tri], Y[m.tri]
+            area = (x[:, 1] - x[:, 0]) * (y[:, 2] - y[:, 0]) - (y[:, 1] - y[:, 0]) * (x[:, 2] - x[:, 0])
+            i0, i1 = np.maximum((x.min(1) + 127) >> 8, 0), np.minimum((x.max(1) - 128) >> 8, cam.width - 1)
+            j0, j1 = np.maximum((y.min(1) + 127) >> 8, 0), np.minimum((y.max(1) - 128) >> 8, cam.height - 1)
+            live = ok[m.tri].all(1) & (area != 0) & (i0 <= i1) & (j0 <= j1)
+            out.append(np.stack([live, area < 0, i0, i1, j0, j1], 1))
+    return np.concatenate(out)
+
+
+def _replay(driver, layers, cams, **kw):
+    sizes = [(c.width, c.height) for c in cams]
+    return driver([m.n_tri for m in layers], [len(m.xyz) for m in layers], sizes, seed=3, boxes=_boxes(layers, cams), **kw)
+
+
+def asked_from_the_start(n_tri, n_vert, sizes, bin, capacity):
+    """Workspace bytes as the ABI has had them from the start: per bin a view, a count, an offset and two cursors, per view
+    and triangle a record, per 1,024 bins a sum, per entry an id."""
+    up = lambda n: -(-int(n) // 256) * 256   # noqa: E731
+    b, k = bin or 64, len(n_tri)
+    tiles = lambda w, h: sum(-(-x // w) * -(-y // h) for x, y in sizes)   # noqa: E731
+    bt = tiles(b, 56 if b == 64 else b)
+    bins, tris = bt * k, len(sizes) * sum(n_tri)
+    entries = capacity or max(tris * {8: 4, 16: 3}.get(b, 2), 1 << 20)
+    return (256 + up(4 * tiles(16, 16)) + up(16 * len(sizes) * sum(n_vert)) + up(4 * bt) + up(4 * bins) + 2 * up(8 * bins) +
+            up(16 * tris) + up(8 * -(-bins // 1024)) + up(4 * entries))
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_workspace_is_what_it_was(driver, seed):
+    rng = np.random.default_rng([61, seed])
+    k, nv = int(rng.integers(1, 17)), int(np.exp(rng.uniform(0, np.log(300))))
+    n_tri = [int(x) for x in np.exp(rng.uniform(0, np.log(3e5), k))]
+    sizes = [tuple(int(x) for x in rng.integers(1, rng.choice([9, 200, 1100, 8193]), 2)) for _ in range(nv)]
+    for bin in (0, 8, 16, 32, 64):
+        for capacity in (0, 1, int(rng.integers(2, 10 ** 7)), 2 ** 32 - 1):
+            lay = driver(n_tri, n_tri, sizes, bin, capacity)
+            assert lay["total"] == asked_from_the_start(n_tri, n_tri, sizes, bin, capacity)
+            assert lay["end"] <= lay["total"]
+            if capacity:   # entries, records and tables of the most words: one part holds them all
+                G, groups = 256 * lay["reps"], 0
+                tables = 0
+                for w, h in sizes:
+                    tiles = -(-w // lay["bin"]) * -(-h // (56 if lay["bin"] == 64 else lay["bin"]))
+                    for n in n_tri:
+                        full, last = divmod(n, G)
+                        tables += full * min(4 * G - 4, tiles + 1) + (tiles + 1 if last else 0)
+                assert lay["parts"] == 1
+                assert lay["words"] >= min(min(capacity, lay["entries"]) + tables, 0xe0000000)
+
+
+COARSE = [
+    # shells, lat, lon, views
+    (3, 20, 34, [(800, 800)] * 64),
+    (1, 20, 34, [(800, 800)] * 100),
+    (3, 20, 34, [(1024, 1024)] * 48),
+    (5, 20, 40, [(1600, 1080)] * 24),
+    (9, 12, 24, [(1600, 1080)] * 24),
+    (2, 8, 14, [(700, 500)] * 8),
+    # one large view among small ones: the list is the call's, not a view's
+    (7, 20, 34, [(96, 96)] * 40 + [(4096, 4096)] + [(96, 96)] * 23),
+]
+
+
+@pytest.mark.parametrize("k,lat,lon,sizes", COARSE)
+def test_coarse_shells_in_many_views_fit(driver, k, lat, lon, sizes):
+    layers, cams = S.displaced_shells(2, k, lat, lon), S.ring_cameras(5, len(sizes), sizes)
+    got = _replay(driver, layers, cams)
+    assert got["pairs"] <= max(1 << 20, 2 * len(sizes) * sum(m.n_tri for m in layers))   # what the default is meant to hold
+    assert got["without"] == 0, got
+
+
+@pytest.mark.parametrize("seed", range(12))
+def test_a_capacity_holds_its_entries(driver, seed):
+    """Shuffled shells, coarse and fine: as many entries as (triangle, bin) pairs always fit, one fewer does not."""
+    rng = np.random.default_rng([62, seed])
+    k, lat = int(rng.integers(1, 5)), int(rng.integers(4, 60))
+    layers = [S.Mesh(m.xyz, m.uv, m.tri[rng.permutation(m.n_tri)]) for m in S.displaced_shells(2, k, lat, 2 * lat)]
+    sizes = [tuple(int(x) for x in rng.integers(20, 500, 2)) for _ in range(int(rng.integers(1, 5)))]
+    cams = S.ring_cameras(6, len(sizes), sizes)
+    for bin in (16, 32, 64):
+        full = _replay(driver, layers, cams, bin=bin, capacity=2 ** 31)
+        assert full["without"] == 0
+        assert _replay(driver, layers, cams, bin=bin, capacity=full["pairs"])["without"] == 0
+        assert _replay(driver, layers, cams, bin=bin, capacity=full["pairs"] - 1)["without"] > 0
