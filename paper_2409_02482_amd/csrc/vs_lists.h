@@ -16,6 +16,10 @@ constexpr int kPartApart = 8;                  // 64-bit words from one part's c
 // take four words per triangle, what the workspace holds per triangle beside its entries.
 __host__ __device__ constexpr int group_tiles(int R) { return 4 * 256 * R - 5; }
 
+// Most entries of a side (front-facing or not) that a table's 16-bit sums count.  A group with more, hundreds
+// of triangles over many tiles each, is counted in larger macro tiles: at last in four, four entries a triangle.
+constexpr uint32_t kSideEntries = 0xffffu;
+
 // Smallest shift, from s on, at which a rectangle of tiles has at most `most` macro tiles of 2^shift x 2^shift.
 __host__ __device__ inline int macro_shift(int x0, int y0, int x1, int y1, int most, int s) {
   while (((x1 >> s) - (x0 >> s) + 1) * ((y1 >> s) - (y0 >> s) + 1) > most) ++s;

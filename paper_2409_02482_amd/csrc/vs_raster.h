@@ -125,7 +125,8 @@ struct BinGroups {
 };
 
 // Record of one group in one view.  Its tiles' rectangle is counted in macro tiles of
-// 2^shift x 2^shift bins (shift 0 unless the rectangle has more of them than a table).  The
+// 2^shift x 2^shift bins (shift 0 unless the rectangle has more of them than a table, or the group more
+// entries than its sums).  The
 // group's run of the list, from word `base`: per macro tile of the rectangle, row
 // by row, how many front-facing entries and, << 16, how many others come before its own, then both
 // totals in the same form; the front-facing entries (triangle ids); the others.
@@ -267,10 +268,7 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
     if (tid == 0) *rec = out;
     return;
   }
-  const int s = macro_shift(ex0, ey0, ex1, ey1, group_tiles(R), 0);
-  const int rx = ex0 >> s, ry = ey0 >> s, tw = (ex1 >> s) - rx + 1, th = (ey1 >> s) - ry + 1, n = tw * th;
-  for (int e = tid; e < n; e += 256) hist[e] = 0;
-  __syncthreads();
+  int s = macro_shift(ex0, ey0, ex1, ey1, group_tiles(R), 0), rx, ry, tw, th, n, e0, e1;
   // each (triangle, macro tile): use(repetition, tile's column and row, its histogram word, front-facing)
   auto each = [&](auto use) {
 #pragma unroll
@@ -284,49 +282,57 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
         for (int x = x0; x <= x1; ++x) use(r, x, y, &hist[(y - ry) * tw + (x - rx)], f);
     }
   };
-  each([&](int, int, int, uint32_t* h, bool f) { atomicAdd(h, f ? 1u : 0x10000u); });
-  __syncthreads();
-  // exclusive prefix sums over the tiles, `per` consecutive ones per thread
-  const int per = (n + 255) / 256, e0 = min(tid * per, n), e1 = min(e0 + per, n);
-  uint32_t mine_f = 0, mine_o = 0;
-  for (int e = e0; e < e1; ++e) {
-    mine_f += hist[e] & 0xffffu;
-    mine_o += hist[e] >> 16;
-  }
-  uint32_t f = mine_f, o = mine_o;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t fb = __shfl_up(f, off), ob = __shfl_up(o, off);
-    if (lane >= off) {
-      f += fb;
-      o += ob;
+  uint32_t f, o, total_f, total_o;
+  for (;; s = macro_shift(ex0, ey0, ex1, ey1, group_tiles(R), s + 1)) {   // uniform; once unless a side has too many entries
+    rx = ex0 >> s; ry = ey0 >> s; tw = (ex1 >> s) - rx + 1; th = (ey1 >> s) - ry + 1; n = tw * th;
+    for (int e = tid; e < n; e += 256) hist[e] = 0;
+    __syncthreads();
+    each([&](int, int, int, uint32_t* h, bool is_front) { atomicAdd(h, is_front ? 1u : 0x10000u); });
+    __syncthreads();
+    // exclusive prefix sums over the tiles, `per` consecutive ones per thread
+    const int per = (n + 255) / 256;
+    e0 = min(tid * per, n); e1 = min(e0 + per, n);
+    uint32_t mine_f = 0, mine_o = 0;
+    for (int e = e0; e < e1; ++e) {
+      mine_f += hist[e] & 0xffffu;
+      mine_o += hist[e] >> 16;
     }
-  }
-  if (lane == 63) {
-    sums[wv][0] = f;
-    sums[wv][1] = o;
-  }
-  __syncthreads();
-  f -= mine_f;
-  o -= mine_o;
-  uint32_t total_f = 0, total_o = 0;
+    f = mine_f; o = mine_o;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    f += w < wv ? sums[w][0] : 0u;
-    o += w < wv ? sums[w][1] : 0u;
-    total_f += sums[w][0];
-    total_o += sums[w][1];
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t fb = __shfl_up(f, off), ob = __shfl_up(o, off);
+      if (lane >= off) {
+        f += fb;
+        o += ob;
+      }
+    }
+    if (lane == 63) {
+      sums[wv][0] = f;
+      sums[wv][1] = o;
+    }
+    __syncthreads();
+    f -= mine_f;
+    o -= mine_o;
+    total_f = total_o = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      f += w < wv ? sums[w][0] : 0u;
+      o += w < wv ? sums[w][1] : 0u;
+      total_f += sums[w][0];
+      total_o += sums[w][1];
+    }
+    if (max(total_f, total_o) <= kSideEntries) break;
+    __syncthreads();   // the counts and sums are written anew
   }
   const uint32_t entries = total_f + total_o, need = (uint32_t)n + 1u + entries;   // words
   near = __builtin_amdgcn_readfirstlane(total_o ? near & ~0x7ffff : 0);
   far = __builtin_amdgcn_readfirstlane(total_o ? far : 0);
   const int near_shift = max(0, 22 - __clz(far - near));   // the range in 10 bits
   if (tid == 0) {
-    uint32_t base = kGroupNoRun;
-    if (total_f <= 0xffffu && total_o <= 0xffffu)
-      base = reserve_run(need, entries, room, blockIdx.x,
-                         [&](uint32_t p) { return __hip_atomic_load(parts + p * kPartApart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
-                         [&](uint32_t p, uint64_t n) { return atomicAdd(parts + p * kPartApart, (unsigned long long)n); });
+    const uint32_t base = reserve_run(
+        need, entries, room, blockIdx.x,
+        [&](uint32_t p) { return __hip_atomic_load(parts + p * kPartApart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
+        [&](uint32_t p, uint64_t words) { return atomicAdd(parts + p * kPartApart, (unsigned long long)words); });
     run_base = base;
     out.tx0 = (uint16_t)rx; out.ty0 = (uint16_t)ry; out.tw = (uint16_t)tw; out.th = (uint16_t)th;
     out.base = base;

@@ -163,3 +163,9 @@ def test_capacity_is_a_count_of_pairs():
     pairs = int(((b[:, 3] // 64 - b[:, 2] // 64 + 1) * (b[:, 5] // 56 - b[:, 4] // 56 + 1)).sum())
     assert _check(sc, "capacity of all pairs", list_capacity=pairs)["bin_overflow"] == 0
     assert _check(sc, "capacity one short", list_capacity=pairs - 1)["bin_overflow"] > 0
+
+
+def test_more_entries_than_a_table_sums():
+    """256 triangles over most of 992 bins each: more entries of a side than a table's 16-bit sums, in macro tiles then."""
+    sc = _soup(6, 700, [(600, 600)], (256, 248))
+    assert _check(sc, "wide soup", bin=8)["bin_overflow"] == 0

@@ -52,22 +52,27 @@ int main(int, char** a) {
   for (int v = 0; v < nv; ++v)
     for (int l = 0, own = 0; l < k; ++l)
       for (int t0 = 0; t0 < L.n_tri[l]; t0 += G, ++own) {
-        std::vector<std::array<int, 4>> box;
+        std::vector<std::array<int, 5>> box;
         int e[4] = {1 << 30, 1 << 30, -1, -1};
         for (int t = t0; t < std::min(t0 + G, L.n_tri[l]); ++t) {
           const int live = next();
-          next();
+          const int front = next();
           const int i0 = next(), i1 = next(), j0 = next(), j1 = next();
           if (!live) continue;
-          box.push_back({i0 / B, j0 / BH, i1 / B, j1 / BH});
+          box.push_back({i0 / B, j0 / BH, i1 / B, j1 / BH, front});
           for (int q = 0; q < 2; ++q) e[q] = std::min(e[q], box.back()[q]), e[2 + q] = std::max(e[2 + q], box.back()[2 + q]);
           pairs += (uint64_t)(i1 / B - i0 / B + 1) * (j1 / BH - j0 / BH + 1);
         }
         if (box.empty()) continue;
-        const int s = vs::macro_shift(e[0], e[1], e[2], e[3], vs::group_tiles(w.reps), 0);
-        const uint32_t n = ((e[2] >> s) - (e[0] >> s) + 1) * ((e[3] >> s) - (e[1] >> s) + 1);
-        uint32_t entries = 0;
-        for (auto& b : box) entries += ((b[2] >> s) - (b[0] >> s) + 1) * ((b[3] >> s) - (b[1] >> s) + 1);
+        int s = vs::macro_shift(e[0], e[1], e[2], e[3], vs::group_tiles(w.reps), 0);
+        uint32_t n, side[2], entries;
+        for (;; s = vs::macro_shift(e[0], e[1], e[2], e[3], vs::group_tiles(w.reps), s + 1)) {
+          n = ((e[2] >> s) - (e[0] >> s) + 1) * ((e[3] >> s) - (e[1] >> s) + 1);
+          side[0] = side[1] = 0;
+          for (auto& b : box) side[b[4]] += ((b[2] >> s) - (b[0] >> s) + 1) * ((b[3] >> s) - (b[1] >> s) + 1);
+          entries = side[0] + side[1];
+          if (std::max(side[0], side[1]) <= vs::kSideEntries) break;
+        }
         groups.push_back({n + 1 + entries, entries, (uint32_t)own});
       }
   std::shuffle(groups.begin(), groups.end(), std::mt19937(seed));
