@@ -199,6 +199,14 @@ int64_t total_tiles(const vs_views* views, int slot) { return views->host[views-
 
 unsigned grid_1d(int64_t n, int block) { return (unsigned)((n + block - 1) / block); }
 
+// Grid of k_setup: per view the blocks of its vertices and its share of those of all tiles.
+dim3 setup_blocks(int64_t vpv, int64_t n_tiles16, int64_t n_tiles_bin, int n_views, uint32_t& proj_blocks,
+                  uint32_t& tile_blocks) {
+  proj_blocks = grid_1d(vpv, 256);
+  tile_blocks = grid_1d(n_tiles16, 256);
+  return dim3(proj_blocks + grid_1d((int64_t)tile_blocks + grid_1d(n_tiles_bin, 256), n_views), (unsigned)n_views);
+}
+
 }  // namespace
 
 extern "C" {
@@ -294,10 +302,8 @@ vs_status vs_raster_layers(const vs_mesh* layers, int32_t k, const vs_views* vie
   setup.parts = parts;
   setup.n_views = nv;
   setup.slot = lay.slot;
-  setup.proj_blocks = (int32_t)grid_1d(vpv, 256);
-  setup.tile_blocks = (int32_t)grid_1d(lay.n_tiles16, 256);
-  const unsigned setup_grid = (unsigned)setup.proj_blocks * (unsigned)nv + (unsigned)setup.tile_blocks + grid_1d(setup.n_tiles_bin, 256);
-  hipLaunchKernelGGL(vs::k_setup, dim3(setup_grid), dim3(256), 0, s, setup, L);
+  const dim3 setup_grid = setup_blocks(vpv, lay.n_tiles16, setup.n_tiles_bin, nv, setup.proj_blocks, setup.tile_blocks);
+  hipLaunchKernelGGL(vs::k_setup, setup_grid, dim3(256), 0, s, setup, L);
   if (direct) {
     const int64_t total_slots = (int64_t)k * views->host[nv].pix_offset;
     hipLaunchKernelGGL(vs::k_fill_u64, dim3((unsigned)std::min<int64_t>(grid_1d(total_slots, 256), 65536)),

@@ -53,8 +53,9 @@ __global__ void __launch_bounds__(256) k_fill_u64(uint64_t* __restrict__ p, int6
 // on a single word 168k groups would take 1 ms).  A run that its part has no room for goes to the next one
 // that has: the views share the whole list, whatever their sizes.
 
-// Everything that binning, drawing and shading find ready, one launch: the first blocks take step 1
-// for every (view, layer, vertex), proj_blocks per view; the next ones tile_view[g] = view owning
+// Everything that binning, drawing and shading find ready, one launch with the view in grid.y (views times
+// vertices may pass what one grid dimension holds): a view's first proj_blocks blocks take step 1 for every
+// (layer, vertex); the other blocks of all views, dealt round, take tile_view[g] = view owning
 // 16-pixel tile g, and then bin_view[g] likewise for the bins' tiles (n_tiles_bin = 0: none).
 struct SetupArgs {
   const vs_view* views;
@@ -65,25 +66,27 @@ struct SetupArgs {
   int64_t n_tiles16, n_tiles_bin;
   unsigned long long* status;
   unsigned long long* parts;
-  int32_t n_views, slot, proj_blocks, tile_blocks;
+  int32_t n_views, slot;
+  uint32_t proj_blocks, tile_blocks;
 };
 
 __global__ void __launch_bounds__(256) k_setup(SetupArgs A, LayerTable L) {
-  const uint32_t all_proj = (uint32_t)A.proj_blocks * (uint32_t)A.n_views;
-  if (blockIdx.x < all_proj) {
-    const int v = (int)(blockIdx.x / (uint32_t)A.proj_blocks);
-    const int64_t g = (int64_t)(blockIdx.x - (uint32_t)v * (uint32_t)A.proj_blocks) * 256 + threadIdx.x;
-    if (blockIdx.x == 0 && threadIdx.x < VS_STAT_COUNT) A.status[threadIdx.x] = 0ull;
-    if (blockIdx.x == 0 && threadIdx.x < kParts) A.parts[threadIdx.x * kPartApart] = 0ull;
+  const int v = (int)blockIdx.y;
+  if (blockIdx.x < A.proj_blocks) {
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (v == 0 && blockIdx.x == 0) {
+      if (threadIdx.x < VS_STAT_COUNT) A.status[threadIdx.x] = 0ull;
+      if (threadIdx.x < kParts) A.parts[threadIdx.x * kPartApart] = 0ull;
+    }
     if (g >= A.vpv) return;
     int l = 0;
     while (l + 1 < L.k && L.vert_off[l + 1] <= g) ++l;
     A.proj[(int64_t)v * A.vpv + g] = project_vertex(L.xyz[l] + 3 * (g - L.vert_off[l]), A.views[v].cam);
     return;
   }
-  const uint32_t b = blockIdx.x - all_proj;
-  const bool bins = b >= (uint32_t)A.tile_blocks;   // uniform
-  const int64_t g = (int64_t)(bins ? b - (uint32_t)A.tile_blocks : b) * 256 + threadIdx.x;
+  const int64_t b = (int64_t)(blockIdx.x - A.proj_blocks) * gridDim.y + v;
+  const bool bins = b >= A.tile_blocks;   // uniform
+  const int64_t g = (bins ? b - A.tile_blocks : b) * 256 + threadIdx.x;
   if (bins) {
     if (g < A.n_tiles_bin) A.bin_view[g] = find_view_tile(A.views, A.n_views, g, A.slot);
   } else if (g < A.n_tiles16) {
