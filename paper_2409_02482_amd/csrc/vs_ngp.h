@@ -530,7 +530,8 @@ __global__ void __launch_bounds__(256, LMAX <= 8 ? 2 : 1) k_ngp_backward(NgpTabl
 // levels; this takes 0.27 ms.
 // A window of more than kNgpSlots vertices (vertices finer than texels) adds each
 // corner with a global atomic, and so does a level with an infinite or NaN de,
-// which must reach its own four vertices only.
+// or one so large that a sum of products might overflow, for infinity times a
+// weight of zero is NaN: such a value must reach its own four vertices only.
 template <int LMAX>
 __global__ void __launch_bounds__(256) k_ngp_scatter(NgpTable T, NgpShape S, NgpStage G) {
   __shared__ int32_t first[LMAX][2];                       // per level: the window's first vertex (x, y)
@@ -567,10 +568,10 @@ __global__ void __launch_bounds__(256) k_ngp_scatter(NgpTable T, NgpShape S, Ngp
     de[1] = *reinterpret_cast<const ngp_f4*>(src + G.R);
     const int ex = cell[lv][0][15] + 2, ey = cell[lv][1][15] + 2;   // uniform
     const uint32_t vx0 = (uint32_t)first[lv][0], vy0 = (uint32_t)first[lv][1];
-    bool finite = true;
+    bool bounded = true;   // 256 texels' values of at most 2^112, weighted by at most 1, sum to a float (false for NaN)
 #pragma unroll
-    for (int q = 0; q < 8; ++q) finite = finite && __builtin_isfinite(de[q >> 2][q & 3]);
-    if ((int64_t)ex * ey <= kNgpSlots && __all(finite)) {
+    for (int q = 0; q < 8; ++q) bounded = bounded && fabsf(de[q >> 2][q & 3]) <= 0x1p112f;
+    if ((int64_t)ex * ey <= kNgpSlots && __all(bounded)) {
       const int4 cx = *reinterpret_cast<const int4*>(&cell[lv][0][4 * g]), cy = *reinterpret_cast<const int4*>(&cell[lv][1][4 * g]);
       const float4 fx = *reinterpret_cast<const float4*>(&frac[lv][0][4 * g]);
       const float4 fy = *reinterpret_cast<const float4*>(&frac[lv][1][4 * g]);

@@ -66,3 +66,44 @@ def test_a_gradient_that_is_not_finite_stays_with_its_texel(bad):
     tables = got[0][:hit.size]
     assert not np.isfinite(tables[hit]).any()
     assert np.abs(tables[~hit] - clean[0][:hit.size][~hit]).max() <= GRAD_RTOL * np.abs(clean[0][:hit.size]).max()
+
+
+def test_gradients_whose_sums_overflow_stay_with_their_vertices():
+    """Finite gradients near the largest float: a vertex whose sum fits a float has it, entries that no texel reaches stay
+    zero, next to coarse levels where a tile's column alone overflows.  The texture ends inside its last tiles."""
+    import torch
+    import paper_2409_02482_amd as P
+    res, log2, (w, h) = [1, 3, 9, 40, 60], 12, (40, 24)
+    ocfg = N.NgpConfig(res, log2)
+    params = S.ngp_params(57, 0, len(res), log2)
+    o1, s1 = N.param_layout(ocfg)["W1"]
+    params[:o1] *= np.float32(2.0 ** -4)      # the same network from smaller features: dL/de is 16 times as large
+    params[o1:o1 + int(np.prod(s1))] *= np.float32(2.0 ** 4)
+    f, Q = N.forward(params, ocfg, *N.texel_centres(w, h)), N.unpack(params, ocfg)
+    gt = np.random.default_rng(43).uniform(0.5, 1, (h, w, 4)).astype(np.float32)
+
+    def de_of(g):
+        d0 = g.reshape(-1, 4).astype(np.float64) * f["t"] * (1.0 - f["t"])
+        return ((((d0 @ Q["W3"]) * (f["z2"] > 0)) @ Q["W2"]) * (f["z1"] > 0)) @ Q["W1"]
+
+    gt *= np.float32(2.5e38 / np.abs(de_of(gt)).max())
+    de = de_of(gt)
+    want, total = np.zeros((len(res), 1 << log2, 2)), np.zeros((len(res), 1 << log2, 2))
+    for lv, (idx, wts) in enumerate(f["corners"]):
+        for q, wt in zip(idx, wts):
+            for c in range(2):
+                np.add.at(want[lv, :, c], q, wt * de[:, 2 * lv + c])
+                np.add.at(total[lv, :, c], q, np.abs(wt * de[:, 2 * lv + c]))
+    fx = (np.arange(16) + 0.5) / w   # level 0: one cell, the first tile's columns into its left vertices
+    assert np.abs(((1 - fx)[:, None] * de.reshape(h, w, -1)[:, :16, :2]).sum(1)).max() > 3.5e38
+    fits = total < 3e38
+    assert (np.abs(want) > 3.5e38).any() and (fits & (total > 0)).sum() > 1000   # both kinds are there
+    cfg = P.NgpConfig(res, log2)
+    say("[gpu] ngp scatter with sums that overflow")
+    dev, ws = [torch.from_numpy(params).cuda()], P.ngp_workspace(cfg, [(w, h)])
+    tex = P.ngp_bake(dev, cfg, [(w, h)], ws=ws)
+    got = P.ngp_backward(dev, cfg, [(w, h)], tex, [torch.from_numpy(gt).cuda()], ws)[0].cpu().numpy().astype(np.float64)
+    got = got[:want.size].reshape(want.shape)
+    assert np.isfinite(got[fits]).all()
+    assert np.abs(got - want)[fits].max() <= GRAD_RTOL * total[fits].max()
+    assert (got[total == 0] == 0).all()
