@@ -380,6 +380,15 @@ __global__ void __launch_bounds__(256, LMAX <= 8 ? 2 : 1) k_ngp_backward(NgpTabl
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
       for (int r = 0; r < 4; ++r) h2[mt][r] = fmaxf(h2[mt][r], 0.f);
+    if (!__all(valid)) {   // no hidden unit is on outside the texture: nothing of it meets an infinite weight or gradient
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          h1[mt][r] = valid ? h1[mt][r] : 0.f;
+          h2[mt][r] = valid ? h2[mt][r] : 0.f;
+        }
+    }
     // d2, and dW3 from h2 and d0
     ngp_f4 d2[4];
 #pragma unroll

@@ -107,3 +107,37 @@ def test_gradients_whose_sums_overflow_stay_with_their_vertices():
     assert np.isfinite(got[fits]).all()
     assert np.abs(got - want)[fits].max() <= GRAD_RTOL * total[fits].max()
     assert (got[total == 0] == 0).all()
+
+
+def test_texels_outside_the_texture_have_no_gradient():
+    """A unit that is off at every texel but on for an all-zero encoding, with an infinite weight behind it: the texels that
+    fill a tile up must not bring it into the gradients."""
+    import torch
+    import paper_2409_02482_amd as P
+    res, log2, (w, h) = [3, 9], 8, (19, 18)
+    ocfg, cfg = N.NgpConfig(res, log2), P.NgpConfig(res, log2)
+    lay = N.param_layout(ocfg)
+    params = S.ngp_params(57, 0, len(res), log2)
+
+    def part(name):
+        o, s = lay[name]
+        return params[o:o + int(np.prod(s))].reshape(s)
+
+    part("tables")[:] = np.abs(part("tables")) + 0.5
+    part("W1")[7], part("b1")[7] = -4.0, 1.0        # z1 = 1 - 4 sum(e) < 0 at every texel, 1 where e = 0
+    part("W2")[11, :] = 0.0
+    part("b2")[11] = 1.0
+    want_p = params.copy()
+    part("W2")[11, 7] = np.inf                       # inf * 0: this unit's sum is NaN, and the unit off
+    gt = np.random.default_rng(44).uniform(-1, 1, (h, w, 4)).astype(np.float32)
+    say("[gpu] ngp texels outside the texture")
+    grads = []
+    for p in (want_p, params):
+        if p is want_p:
+            o, s = lay["b2"]
+            p[o + 11] = -1.0                         # the same unit off by its bias
+        dev, ws = [torch.from_numpy(p).cuda()], P.ngp_workspace(cfg, [(w, h)])
+        tex = P.ngp_bake(dev, cfg, [(w, h)], ws=ws)
+        grads.append(P.ngp_backward(dev, cfg, [(w, h)], tex, [torch.from_numpy(gt).cuda()], ws)[0].cpu().numpy())
+    assert np.isfinite(grads[1]).all()
+    assert np.abs(grads[1] - grads[0]).max() <= GRAD_RTOL * np.abs(grads[0]).max()
