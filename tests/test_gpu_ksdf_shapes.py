@@ -59,3 +59,59 @@ def test_ksdf_lane_layouts(torch_cuda, k, n, m, steps, occ_res, sizes):  # noqa:
             gap = np.diff(want["samples"], axis=1).max(1)
             assert (np.abs(smp[sl] - want["samples"]).max(1) <= np.maximum(gap, 0.0))[~empty & keep].all()
     assert live > 0
+
+
+def _positions_at(t, d, offsets, beta, u, eps):
+    """Parameters at CDF values u [m] (clipped to 0..1) of one importance round over samples t, d [rays, N]."""
+    W = sum(K.neus_weights(d, o, beta) for o in offsets) + eps
+    cdf = np.concatenate([np.zeros((len(t), 1)), np.cumsum(W, 1) / W.sum(1, keepdims=True)], 1)
+    u = np.clip(u, 0.0, 1.0)
+    return np.stack([np.interp(u, cdf[r], t[r]) for r in range(len(t))])
+
+
+@pytest.mark.parametrize("k,n,m,steps,occ_res,sizes", [
+    (3, 20, 100, 320, 33, [(13, 17), (19, 5)]),
+    (2, 30, 6, 320, 40, [(31, 11)]),
+    (4, 64, 64, 2048, 64, [(16, 16)]),
+    (2, 97, 2, 64, 255, [(33, 7)]),
+    (7, 64, 32, 1024, 64, [(24, 20)]),
+    (16, 32, 32, 256, 16, [(21, 9)]),
+])
+def test_ksdf_merged_samples(torch_cuda, k, n, m, steps, occ_res, sizes):  # noqa: F811
+    """The merged list of a ray: in order, the uniform samples among it bit for bit, and each importance sample where the
+    oracle's CDF puts it within 1e-3 (a twentieth and less of the distance to the next sample, and a hundred times what FP32
+    weights move it)."""
+    torch = torch_cuda
+    g = S.ksdf_grids(71, 48, 24)
+    P, field, opts, oopts = _setup(torch, g, k, occ_res, n_uniform=n, n_importance=m, march_steps=steps)
+    _, _, uniform, _ = _setup(torch, g, k, occ_res, n_uniform=n, n_importance=0, march_steps=steps)
+    cams = S.ring_cameras(72, len(sizes), sizes)
+    occ = P.ksdf_occupancy(field, opts)
+    views = P.Views(cams)
+    say(f"[gpu] ksdf merge n={n} m={m} steps={steps}")
+    got = P.ksdf_render(field, opts, occ, views, samples=True)[-1].cpu().numpy()
+    base = P.ksdf_render(field, uniform, occ, views, samples=True)[-1].cpu().numpy()
+    o, v = (np.concatenate(x) for x in zip(*[K.camera_rays(c) for c in cams]))
+    live = (base[:, 0] >= 0) & ~K.march_on_face(o, v, oopts.occ_res, g.lo, g.hi, oopts.march_steps)
+    got, base, o, v = got[live], base[live], o[live], v[live]
+    assert live.sum() > 20 and (np.diff(got, axis=1) >= 0).all()
+    new = np.empty((len(got), m))
+    for r in range(len(got)):
+        rest = list(got[r])
+        for t in base[r]:
+            rest.remove(t)      # raises if it is not there
+        new[r] = rest
+
+    def sdf_along(tt):
+        return K.sdf_at(g, (o[:, None, :] + tt[..., None] * v[:, None, :]).reshape(-1, 3)).reshape(tt.shape)
+
+    t, d = base, sdf_along(base)
+    u = (np.arange(m // 2) + 0.5) / (m // 2)
+    bounds = [[], []]
+    for beta in (oopts.beta / 2.0, oopts.beta):
+        for side, delta in enumerate((-1e-3, 1e-3)):
+            bounds[side].append(_positions_at(t, d, oopts.offsets, beta, u + delta, oopts.pdf_floor))
+        tn = K.importance_round(t, d, oopts.offsets, beta, m // 2, oopts.pdf_floor)
+        t, d = K.merge_sorted(t, d, tn, sdf_along(tn))
+    low, high = (np.sort(np.concatenate(b, 1), 1) for b in bounds)
+    assert (new >= low - 1e-12).all() and (new <= high + 1e-12).all()
