@@ -158,7 +158,10 @@ vs::WsLayout ws_layout(const vs::LayerTable& L, const vs_views* views, int bin, 
   w.n_tiles_bin = w.slot >= 0 ? tot.tile_offset[w.slot] : 0;
   w.n_bins = w.n_tiles_bin * L.k;
   const uint64_t tris = (uint64_t)n_views * (uint64_t)L.tri_off[L.k];
-  w.reps = vs::bin_reps(L.tri_off[L.k], n_views);
+  w.reps = vs::bin_reps(L.tri_off[L.k], n_views, (w.n_tiles_bin + n_views - 1) / n_views);
+  w.most_tiles = vs::group_tiles(w.reps);
+  for (int l = 0; l < L.k && capacity > 0; ++l)   // the words for a caller's entries are exact
+    if (L.n_tri[l] / 1024 > vs::kWideGroups) w.most_tiles = std::min(w.most_tiles, 4 * 1024 - 5);
   w.n_groups = (int64_t)n_views * bin_groups(L, w.reps).off[L.k];
   const uint64_t factor = sized == 8 ? 4 : sized == 16 ? 3 : 2;
   const uint64_t entries = capacity > 0 ? (uint64_t)capacity : std::max<uint64_t>(tris * factor, 1u << 20);
@@ -318,7 +321,7 @@ vs_status vs_raster_layers(const vs_mesh* layers, int32_t k, const vs_views* vie
   const dim3 bin_grid((unsigned)((groups.off[k] + 7) / 8 * 8), (unsigned)nv);
   auto binned = [&](auto kern) {
     hipLaunchKernelGGL(kern, bin_grid, dim3(256), 0, s, views->dev, L, groups, (const vs::ProjVert*)proj, vpv, recs,
-                       list, lay.room, parts, status);
+                       list, lay.room, lay.most_tiles, parts, status);
   };
   switch (B * 8 + lay.reps) {
     case 8 * 8 + 1: binned(vs::k_bin<8, 1>); break;

@@ -66,6 +66,7 @@ struct WsLayout {
   size_t list;       // u32: the groups' runs (tile tables, triangle ids, back faces' entries)
   int64_t n_tiles16, n_tiles_bin, n_bins, n_groups;   // groups: of all views
   int reps;          // triangles per thread of a group's block
+  int most_tiles;    // ... and of a group's table
   ListRoom room;
   int bin, slot;
   size_t total;

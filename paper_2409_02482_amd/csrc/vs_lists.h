@@ -12,9 +12,13 @@ constexpr uint32_t kListWords = 0xe0000000u;   // most words of the list
 constexpr int kParts = 8;                      // parts of the list, one for the groups of each XCD
 constexpr int kPartApart = 8;                  // 64-bit words from one part's counter to the next one's
 
-// Tiles that the table of a group of 256 R triangles counts at most: record, table and total of a full group
-// take four words per triangle, what the workspace holds per triangle beside its entries.
-__host__ __device__ constexpr int group_tiles(int R) { return 4 * 256 * R - 5; }
+// Most tiles that the table of a group of 256 R triangles counts.  Record, table and total of a full group take
+// four words per triangle then, what the workspace holds per triangle beside its entries; 1,024 triangles may have
+// five words more, which the five words per bin beside them cover for up to kWideGroups such groups of a layer in a
+// view (4 x 4,092 words beyond those of the layer's last group), so that a view of 1,024 x 1,024 pixels is counted in
+// its bins of 16.
+constexpr int kWideGroups = 3270;
+__host__ __device__ constexpr int group_tiles(int R) { return R == 4 ? 4096 : 4 * 256 * R - 5; }
 
 // Most entries of a side (front-facing or not) that a table's 16-bit sums count.  A group with more, hundreds
 // of triangles over many tiles each, is counted in larger macro tiles: at last in four, four entries a triangle.

@@ -18,6 +18,8 @@
 //                  is skipped whole
 #pragma once
 
+#include <type_traits>
+
 #include "vs_common.h"
 
 namespace vs {
@@ -39,8 +41,10 @@ constexpr int kSmallSpan = 16384;   // small-triangle path: bbox extents <= 64 p
 // 39 / 42 / 44 us, the metric scene 2.35 / 2.36 / 2.36 ms.
 constexpr int kSmallArea = 512;
 constexpr uint32_t kBigQueue = 16;   // larger back-facing triangles of a bin that its block queues, and
-constexpr int kSegs = 56;            // groups whose entries it draws at once (31.2 KiB of LDS: five blocks a CU)
-static_assert(kBigQueue <= (uint32_t)kRasterThreads && kSegs <= 64, "one round deals the whole queue; one wavefront sums the groups up");
+// groups whose entries it draws at once: 31.2 KiB of LDS with 56, so five blocks a CU, for bins of 64 pixels; smaller bins
+// have LDS left, and in a mesh whose triangles come in no order many groups have an entry or two in each of them.
+__host__ __device__ constexpr int bin_segs(int B) { return B == 64 ? 56 : 224; }
+static_assert(kBigQueue <= (uint32_t)kRasterThreads && bin_segs(8) <= kRasterThreads, "one round deals the whole queue, or looks at all groups");
 
 // Fill n u64 words with a value (grid-stride).
 __global__ void __launch_bounds__(256) k_fill_u64(uint64_t* __restrict__ p, int64_t n, uint64_t val) {
@@ -157,9 +161,12 @@ __host__ __device__ inline int unit_log(int B, int shift) { return max(3, bin_lo
 // ones fill the chip.  One 1024^2 view of seven layers (696 groups of 1,024), binning and raster kernel
 // with one, two or four: 15.8 + 87, 15.4 + 74, 16.3 + 75 us; with eight, the metric scene takes 414 + 2639
 // us against 388 + 2660 with four, the k = 9 scene 1423 + 3261 against 1336 + 3452.
-inline int bin_reps(int64_t n_tri, int n_views) {
+// A view of more tiles than their table counts takes larger ones from 500 groups of 1,024 on: triangles that come in
+// no order reach all tiles, and a table of macro tiles gives every bin the entries of its neighbours as well.
+inline int bin_reps(int64_t n_tri, int n_views, int64_t tiles) {
   const int64_t groups = (n_tri + 1023) / 1024 * n_views;
-  return groups >= 2048 ? 4 : groups >= 300 ? 2 : 1;
+  const int reps = groups >= 2048 ? 4 : groups >= 300 ? 2 : 1;
+  return reps == 2 && groups >= 500 && tiles > group_tiles(2) ? 4 : reps;
 }
 
 // One block per group.  Its triangles' tiles are counted in LDS, so that only the group's one
@@ -174,7 +181,7 @@ inline int bin_reps(int64_t n_tri, int n_views) {
 template <int B, int R>
 __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, LayerTable L, BinGroups Q,
                                              const ProjVert* __restrict__ proj, int64_t vpv,
-                                             GroupRec* __restrict__ recs, uint32_t* __restrict__ list, ListRoom room,
+                                             GroupRec* __restrict__ recs, uint32_t* __restrict__ list, ListRoom room, int most,
                                              unsigned long long* __restrict__ parts,
                                              unsigned long long* __restrict__ status) {
   constexpr int BH = bin_rows(B);
@@ -271,7 +278,7 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
     if (tid == 0) *rec = out;
     return;
   }
-  int s = macro_shift(ex0, ey0, ex1, ey1, group_tiles(R), 0), rx, ry, tw, th, n, e0, e1;
+  int s = macro_shift(ex0, ey0, ex1, ey1, most, 0), rx, ry, tw, th, n, e0, e1;
   // each (triangle, macro tile): use(repetition, tile's column and row, its histogram word, front-facing)
   auto each = [&](auto use) {
 #pragma unroll
@@ -286,7 +293,7 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
     }
   };
   uint32_t f, o, total_f, total_o;
-  for (;; s = macro_shift(ex0, ey0, ex1, ey1, group_tiles(R), s + 1)) {   // uniform; once unless a side has too many entries
+  for (;; s = macro_shift(ex0, ey0, ex1, ey1, most, s + 1)) {   // uniform; once unless a side has too many entries
     rx = ex0 >> s; ry = ey0 >> s; tw = (ex1 >> s) - rx + 1; th = (ey1 >> s) - ry + 1; n = tw * th;
     for (int e = tid; e < n; e += 256) hist[e] = 0;
     __syncthreads();
@@ -416,6 +423,11 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
   constexpr int kSub = 8;                      // sub-tile edge of the depth bound
   constexpr int kNs = B / kSub;                // sub-tiles per row
   constexpr int kNsY = BH / kSub;              // sub-tile rows
+  constexpr int kSegs = bin_segs(B);
+  // entries before a group, front-facing ones and others << kHalf; a group has at most 1,024 in a tile
+  using Start = std::conditional_t<kSegs <= 63, uint32_t, uint64_t>;
+  constexpr int kHalf = 4 * sizeof(Start);
+  constexpr Start kLow = ((Start)1 << kHalf) - 1;
   static_assert(B % kSub == 0 && BH % kSub == 0, "bins must be whole sub-tiles");
   __shared__ __align__(16) unsigned long long tile[B * BH];
   __shared__ uint32_t smax[kNs * kNsY];   // per sub-tile, the depth word of its largest key
@@ -425,8 +437,9 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
   __shared__ uint32_t seg_base[kSegs];            // groups that reach the tile: list word of their first front-facing entry here
   __shared__ uint32_t seg_rest[kSegs];            // ... from there to their first other entry | shift << 18 | near_shift << 22
   __shared__ uint32_t seg_group[kSegs];           // ... the group's number in the layer << 12 | near >> 19
-  __shared__ uint32_t seg_start[kSegs];           // ... and the entries before it, front-facing ones and others << 16
+  __shared__ Start seg_start[kSegs];              // ... and the entries before it
   __shared__ uint32_t seg_n[3];                   // groups, front-facing entries, other entries
+  __shared__ int32_t seg_next;                    // first group that found no place
   __shared__ uint32_t wave_n[2][kRasterThreads / 64];   // groups found by each wavefront, for two batches in turn
   __shared__ uint32_t no_run;                     // a group without a run reaches this tile
   const int k = L.k;
@@ -460,7 +473,11 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
   // Called by the whole block.
   auto load_segs = [&](int g0) -> int {
     int have = 0, turn = 0;
-    while (g0 < n_groups) {   // uniform: 256 groups at a time, kSegs where more than kSegs of those reach the tile
+    bool full = false;
+    int me = tid;
+    asm volatile("" : "+v"(me));   // nothing derived from it is held in registers across the drawing
+    const int tid = me, lane = me & 63;
+    while (g0 < n_groups && !full) {   // uniform: 256 groups at a time
       uint32_t base = 0, rest = 0, near = 0, nf = 0, nb = 0;
       if (g0 + tid < n_groups) {
         const uint4 raw = *reinterpret_cast<const uint4*>(grec + g0 + tid);
@@ -483,67 +500,72 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
           }
         }
       }
-      bool hit = nf + nb > 0;
-      uint64_t hits = __ballot(hit);
-      int width = kRasterThreads, m = 0;
+      const bool hit = nf + nb > 0;
+      const uint64_t hits = __ballot(hit);
       if (lane == 0) wave_n[turn][tid >> 6] = (uint32_t)__popcll(hits);
       __syncthreads();
+      int at = have + (int)__popcll(hits & __lanemask_lt());
 #pragma unroll
-      for (int w = 0; w < kRasterThreads / 64; ++w) m += (int)wave_n[turn][w];
-      if (have + m > kSegs) {
-        if (have > 0) break;
-        width = kSegs;      // the first wavefront's groups alone; only it reads `have`
-        hit = hit && tid < kSegs;
-        hits = __ballot(hit);
-        m = __popcll(hits);
+      for (int w = 0; w < kRasterThreads / 64; ++w) {
+        const int n = __builtin_amdgcn_readfirstlane((int)wave_n[turn][w]);
+        at += w < (tid >> 6) ? n : 0;
+        have += n;
       }
-      if (hit) {
-        uint32_t at = (uint32_t)have + (uint32_t)__popcll(hits & __lanemask_lt());
-        for (int w = 0; w < (tid >> 6); ++w) at += wave_n[turn][w];
+      if (hit && at < kSegs) {
         seg_base[at] = base;
         seg_rest[at] = rest;
         seg_group[at] = (uint32_t)(g0 + tid) << 12 | near;
-        seg_start[at] = nf | (nb << 16);
+        seg_start[at] = (Start)nf | ((Start)nb << kHalf);
       }
-      have += m;
-      g0 += width;
+      if (hit && at == kSegs) seg_next = g0 + tid;
+      full = have > kSegs;
+      g0 += kRasterThreads;
       turn ^= 1;
-      if (width < kRasterThreads) break;
     }
+    have = min(have, kSegs);
     __syncthreads();
+    if (full) g0 = __builtin_amdgcn_readfirstlane(seg_next);
     if (tid < 64) {   // one wavefront sums the entries up
-      const uint32_t c = lane < have ? seg_start[lane] : 0u;
-      uint32_t f = c & 0xffffu, o = c >> 16;
+      uint32_t sum_f = 0, sum_o = 0;
+#pragma unroll 1
+      for (int c0 = 0; c0 < (kSegs <= 64 ? 1 : have); c0 += 64) {   // uniform
+        const int e = c0 + lane;
+        const Start c = e < have ? seg_start[e] : 0;
+        const uint32_t nf = (uint32_t)(c & kLow), nb = (uint32_t)(c >> kHalf);
+        uint32_t f = nf, o = nb;
 #pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t fb = __shfl_up(f, off), ob = __shfl_up(o, off);
-        if (lane >= off) {
-          f += fb;
-          o += ob;
+        for (int off = 1; off < 64; off <<= 1) {
+          const uint32_t fb = __shfl_up(f, off), ob = __shfl_up(o, off);
+          if (lane >= off) {
+            f += fb;
+            o += ob;
+          }
         }
+        if (e < have) seg_start[e] = (Start)(sum_f + f - nf) | ((Start)(sum_o + o - nb) << kHalf);
+        sum_f += __builtin_amdgcn_readlane(f, 63);
+        sum_o += __builtin_amdgcn_readlane(o, 63);
       }
-      if (lane < have) seg_start[lane] = (f - (c & 0xffffu)) | ((o - (c >> 16)) << 16);
-      if (lane == 63) {
+      if (lane == 0) {
         seg_n[0] = (uint32_t)have;
-        seg_n[1] = f;
-        seg_n[2] = o;
+        seg_n[1] = sum_f;
+        seg_n[2] = sum_o;
       }
     }
     __syncthreads();
     return g0;
   };
-  // The loaded group that holds front-facing (shift 0) or other (shift 16) entry c: the last one that
+  // The loaded group that holds front-facing (shift 0) or other (shift kHalf) entry c: the last one that
   // starts at or before c (one without such entries starts where the next does).
   auto find_seg = [&](uint32_t c, int shift) {
     uint32_t a = 0, b = seg_n[0] - 1;
     while (a < b) {
       const uint32_t mid = (a + b + 1) / 2;
-      if (((seg_start[mid] >> shift) & 0xffffu) <= c) a = mid; else b = mid - 1;
+      if ((uint32_t)((seg_start[mid] >> shift) & kLow) <= c) a = mid; else b = mid - 1;
     }
     return a;
   };
   auto front_entry = [&](uint32_t c) -> int32_t {
-    const uint32_t a = find_seg(c, 0), at = seg_base[a] + c - (seg_start[a] & 0xffffu);
+    const uint32_t a = find_seg(c, 0), at = seg_base[a] + c - (uint32_t)(seg_start[a] & kLow);
     return at >= kSegAll ? (int32_t)(at - kSegAll) : (int32_t)list[at];
   };
   // Other entry c of the loaded groups: its triangle; the columns and rows of 8 x 8 sub-tiles of this bin that its box
@@ -553,8 +575,8 @@ __global__ void __launch_bounds__(kRasterThreads, 5) k_raster_bins(
     uint32_t z;
   };
   auto other_entry = [&](uint32_t c) -> Other {
-    const uint32_t a = find_seg(c, 16), rest = seg_rest[a], group = seg_group[a];
-    const uint32_t e = list[seg_base[a] + (rest & 0x3ffffu) + c - (seg_start[a] >> 16)];
+    const uint32_t a = find_seg(c, kHalf), rest = seg_rest[a], group = seg_group[a];
+    const uint32_t e = list[seg_base[a] + (rest & 0x3ffffu) + c - (uint32_t)(seg_start[a] >> kHalf)];
     const int s = (int)(rest >> 18 & 15u), ul = unit_log(B, s), in = (1 << s) - 1;
     const int dx = (tx & in) * B, dy = (ty & in) * BH;   // this bin's corner in the macro tile
     Other o;

@@ -169,3 +169,19 @@ def test_more_entries_than_a_table_sums():
     """256 triangles over most of 992 bins each: more entries of a side than a table's 16-bit sums, in macro tiles then."""
     sc = _soup(6, 700, [(600, 600)], (256, 248))
     assert _check(sc, "wide soup", bin=8)["bin_overflow"] == 0
+
+
+@pytest.mark.parametrize("k,n_lat,size,bin", [(1, 520, (1024, 1024), 16), (2, 400, (1100, 1030), 16), (1, 300, (512, 300), 32)])
+def test_many_groups_in_random_order(k, n_lat, size, bin):
+    """More groups with an entry or two in a bin than a block takes at once, and groups enlarged for a view of many tiles."""
+    import torch
+    import paper_2409_02482_amd as P
+    say(f"[gpu] shuffled k={k} {n_lat}x{2 * n_lat} {size} bin {bin}")
+    sc = _shuffled(k, n_lat, 2 * n_lat, [size])
+    layers, views = P.Layers(sc.layers), P.Views(sc.cameras)
+    direct, ws = P.raster(layers, views, direct=True, count_fragments=True)
+    frags = P.read_status(ws)["fragments"]
+    assert torch.equal(P.raster(layers, views, bin=bin)[0], direct)
+    vis, ws = P.raster(layers, views, bin=bin, count_fragments=True)
+    st = P.read_status(ws)
+    assert torch.equal(vis, direct) and st["fragments"] == frags and st["bin_overflow"] == 0

@@ -42,8 +42,8 @@ int main(int, char** a) {
   memset(&views, 0, sizeof(views));
   views.host = table.data(); views.dev = table.data(); views.n_views = nv;
   const vs::WsLayout w = ws_layout(L, &views, bin, capacity);
-  printf("%zu %zu %u %u %d %d %d\n", w.total, w.list + (size_t)w.room.parts * w.room.words * 4, w.room.words, w.room.entries,
-         w.room.parts, w.bin, w.reps);
+  printf("%zu %zu %u %u %d %d %d %d\n", w.total, w.list + (size_t)w.room.parts * w.room.words * 4, w.room.words, w.room.entries,
+         w.room.parts, w.bin, w.reps, w.most_tiles);
   if (seed < 0) return 0;
   const int B = w.bin, BH = vs::bin_rows(B), G = 256 * w.reps;
   struct Group { uint32_t need, entries, own; };
@@ -64,9 +64,9 @@ int main(int, char** a) {
           pairs += (uint64_t)(i1 / B - i0 / B + 1) * (j1 / BH - j0 / BH + 1);
         }
         if (box.empty()) continue;
-        int s = vs::macro_shift(e[0], e[1], e[2], e[3], vs::group_tiles(w.reps), 0);
+        int s = vs::macro_shift(e[0], e[1], e[2], e[3], w.most_tiles, 0);
         uint32_t n, side[2], entries;
-        for (;; s = vs::macro_shift(e[0], e[1], e[2], e[3], vs::group_tiles(w.reps), s + 1)) {
+        for (;; s = vs::macro_shift(e[0], e[1], e[2], e[3], w.most_tiles, s + 1)) {
           n = ((e[2] >> s) - (e[0] >> s) + 1) * ((e[3] >> s) - (e[1] >> s) + 1);
           side[0] = side[1] = 0;
           for (auto& b : box) side[b[4]] += ((b[2] >> s) - (b[0] >> s) + 1) * ((b[3] >> s) - (b[1] >> s) + 1);
@@ -105,7 +105,7 @@ def driver(tmp_path_factory):
             if boxes is not None:
                 f.write(np.ascontiguousarray(boxes, np.int32).tobytes())
         rows = subprocess.check_output([str(exe), str(d / "in")], text=True).split("\n")
-        lay = dict(zip(("total", "end", "words", "entries", "parts", "bin", "reps"), map(int, rows[0].split())))
+        lay = dict(zip(("total", "end", "words", "entries", "parts", "bin", "reps", "most"), map(int, rows[0].split())))
         if boxes is not None:
             lay.update(zip(("groups", "without", "pairs", "need"), map(int, rows[1].split())))
         return lay
@@ -163,7 +163,7 @@ def test_workspace_is_what_it_was(driver, seed):
                     tiles = -(-w // lay["bin"]) * -(-h // (56 if lay["bin"] == 64 else lay["bin"]))
                     for n in n_tri:
                         full, last = divmod(n, G)
-                        tables += full * min(4 * G - 4, tiles + 1) + (tiles + 1 if last else 0)
+                        tables += full * (min(lay["most"], tiles) + 1) + (tiles + 1 if last else 0)
                 assert lay["parts"] == 1
                 assert lay["words"] >= min(min(capacity, lay["entries"]) + tables, 0xe0000000)
 
