@@ -172,7 +172,7 @@ vs::WsLayout ws_layout(const vs::LayerTable& L, const vs_views* views, int bin, 
   w.tile_view = take((size_t)w.n_tiles16 * 4);
   w.proj = take((size_t)n_views * (size_t)L.vert_off[L.k] * sizeof(vs::ProjVert));
   // everything below depends on the bin size; render and backward read only the part above.  Its bytes are what the ABI
-  // has asked for from the start: 24 a bin (4 of them for its view), 16 per view and triangle, 8 per 1,024 bins, and 4 per
+  // has always asked for: 4 a tile for its view, 20 a bin, 16 per view and triangle, 8 per 1,024 bins, and 4 per
   // entry, each rounded up.  The list has what the views of smaller bins, the groups' records and the counters leave: per
   // triangle, bin and entry at least the words that record, table and entries can need (group_tiles).
   auto bytes = [](uint64_t n, uint64_t each) { return vs::align_up((size_t)(n * each), 256); };

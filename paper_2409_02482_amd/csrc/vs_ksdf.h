@@ -652,8 +652,8 @@ __device__ inline int64_t ksdf_block() {
 // of 32 exactly (NSL = slots per lane, from the sample count).
 //
 // Bound by VALU issue: 8 x 512^2 rays, k = 7, 64 + 32 samples, 1,024 steps took
-// 8.6 ms at 6.1e9 wavefront instructions and take 5.9 ms at 3.3e9, which is all
-// the cycles the SIMDs have.  What went: each of a wavefront's 64 lanes setting
+// 8.6 ms at 6.1e9 wavefront instructions and take 5.9 ms at 3.6e9, nine tenths
+// of the cycles the SIMDs have.  What went: each of a wavefront's 64 lanes setting
 // up its own ray (one lane does now), the FP64 march, exchanges between lanes
 // for the next sample's terms, in the blend one transmittance scan per 32
 // samples and surface (one per 96 now), four half-wave sums per surface (one

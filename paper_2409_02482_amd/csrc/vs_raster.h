@@ -160,7 +160,8 @@ __host__ __device__ inline int unit_log(int B, int shift) { return max(3, bin_lo
 // Triangles per thread of a group's block: larger groups cost a bin fewer runs to go through, smaller
 // ones fill the chip.  One 1024^2 view of seven layers (696 groups of 1,024), binning and raster kernel
 // with one, two or four: 15.8 + 87, 15.4 + 74, 16.3 + 75 us; with eight, the metric scene takes 414 + 2639
-// us against 388 + 2660 with four, the k = 9 scene 1423 + 3261 against 1336 + 3452.
+// us against 388 + 2660 with four, the k = 9 scene 1423 + 3261 against 1336 + 3452 (all with back faces of
+// four words; now 14.6 + 76 us, 365 + 2540, 1285 + 3180).
 // A view of more tiles than their table counts takes larger ones from 500 groups of 1,024 on: triangles that come in
 // no order reach all tiles, and a table of macro tiles gives every bin the entries of its neighbours as well.
 inline int bin_reps(int64_t n_tri, int n_views, int64_t tiles) {
@@ -172,9 +173,9 @@ inline int bin_reps(int64_t n_tri, int n_views, int64_t tiles) {
 // One block per group.  Its triangles' tiles are counted in LDS, so that only the group's one
 // reservation of list space leaves the compute unit, and the counts' prefix sums give both the table
 // and every entry's place.  It replaces a count with atomics per triangle, three scan launches and a
-// scatter that read the records back: metric scene 1.49 -> 0.39 ms, k = 9 scene 3.61 -> 1.34 ms, one
-// 1024^2 view 99 -> 15 us (the raster kernel, which now looks the runs up, 2.36 -> 2.66 ms, 2.87 -> 3.45 ms and
-// 70 -> 74 us).
+// scatter that read the records back: metric scene 1.49 -> 0.37 ms, k = 9 scene 3.61 -> 1.29 ms, one
+// 1024^2 view 99 -> 15 us (the raster kernel, which now looks the runs up, 2.36 -> 2.54 ms, 2.87 -> 3.18 ms and
+// 70 -> 76 us).  Bound by VALU issue: set-up in FP64, 1,294 instructions a wavefront, 0.98 of the cycles.
 // One word an entry, front-facing or not, and one list for all views: 64 views at 800^2 of three shells of
 // 1,292 triangles take 0.77 ms in all and every group has a run; records of four words and a list shared out to
 // the views in equal parts left more than half of the groups without one (1.82 ms; 2.79 with lists per bin).

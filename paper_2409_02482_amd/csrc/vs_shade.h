@@ -256,8 +256,8 @@ __device__ inline int32_t abs_index(int32_t r, int32_t d, int32_t n, int wrap) {
 // Up to 9 layers seven blocks of 272-texel windows (21 KiB) share a CU at 72
 // registers (8 and 9 layers spill 5 and 14).  Windows of 320, 272 and 240 texels
 // at six, seven and eight blocks: metric scene 6.73 / 6.36 / 6.61 ms, 128 views at
-// 800^2 9.35 / 8.90 / 9.03, k = 9 scene 6.72 / 6.66 / 6.90, 384 texels at five
-// blocks 7.25 / 9.77 / 6.91.  Up to 16 layers, five blocks of 288 (384 texels at two, four blocks of
+// 800^2 9.35 / 8.90 / 9.03 (fastest launches; with 272 texels they average 9.7 in a fitting
+// loop), k = 9 scene 6.72 / 6.66 / 6.90, 384 texels at five blocks 7.25 / 9.77 / 6.91.  Up to 16 layers, five blocks of 288 (384 texels at two, four blocks of
 // 320): 12 layers, six views of 700 x 600, 550 us (690, 611); 16 layers 771 us (931, 842).
 // Two tiles per block (kShadeLossTiles) halve the atomics into the one double of
 // the loss sum, which the memory side takes one after the other (5.8 ns each,
