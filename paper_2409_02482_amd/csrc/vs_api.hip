@@ -1060,6 +1060,7 @@ vs_status ksdf_params(const char* who, const vs_ksdf_field* f, const vs_ksdf_opt
     P.cexp[j] = (float)std::exp(o->beta * o->offsets[j]);
   }
   P.beta = o->beta;
+  P.deep = -709.0 / o->beta - o->offsets[0];   // exp(-beta (d + o_0)) overflows a little below
   P.occ_threshold = o->occ_threshold;
   P.half_diag = std::sqrt(3.0) * P.h_occ / 2.0;
   P.n = o->n_uniform;

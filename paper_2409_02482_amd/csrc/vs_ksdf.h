@@ -40,6 +40,7 @@ struct KsdfParams {
   int32_t k;
   double off[VS_KSDF_MAX_SURFACES];
   double beta, occ_threshold, half_diag;
+  double deep;                             // no surface's Phi is 0 in FP64 above this distance
   int32_t n, m, steps;
   float pdf_floor;
 };
@@ -267,6 +268,7 @@ struct KsdfLds {
   double d[32 * NSL + 64];  // their SDF values
   union {
     float cdf[128];         // importance CDF c_0..c_{N-1}, then infinite
+    uint32_t odd[128];      // blend: ksdf_odd_surfaces of each interval, if any
     struct {
       uint64_t mask[32];    // march: occupied-step bits per lane
       int32_t pre[32];      // march: exclusive prefix of occupied steps per lane
@@ -495,14 +497,27 @@ __device__ inline float ksdf_exp(double x) {
 // What the surfaces share of the opacity of the interval from a sample with SDF
 // value d to one with dn: 1 - Phi_{i+1} / Phi_i with Phi = 1 / (1 + exp(-beta x))
 // is (1 - r) / (1 + g_j), r = exp(-beta (d - dn)), g_j = exp(beta (dn + o_j)),
-// and not below 0.  q is 1 - r held to that, G is g without o_j.  Neither
-// overflows to NaN: far inside all surfaces g is 0, far outside infinite, with
-// opacity 0.  Next to a NaN the opacity is 0, but 1 from a NaN to a point so far
-// inside that Phi is 0 in a float.
+// and not below 0.  q is 1 - r held to that (0 next to a NaN), G is g without o_j.
+// Far inside all surfaces g is 0, far outside infinite, with opacity 0.
 __device__ inline void ksdf_interval(double beta, double d, double dn, float& q, float& G) {
   q = fmaxf(-expm1f(-(float)(beta * (d - dn))), 0.f);
-  if (isnan(d) && isinf(expf(-(float)(beta * dn)))) q = 1.f;
   G = q > 0.f ? ksdf_exp(beta * dn) : 1.f;
+}
+
+// Surfaces whose opacity over the interval that form does not give: bit j, it is 0 for surface j, because Phi_i is
+// 0 in FP64 (exp(-beta x) overflows); bit 16 + j, it is 1, because only Phi_{i+1} is, or because d is a NaN and
+// Phi_{i+1} 0 in FP32, formed as in the importance weights (ksdf_cdf).
+constexpr double kKsdfDeep = 709.782712893384;   // log of the largest double
+static_assert(VS_KSDF_MAX_SURFACES <= 16, "bits of a word");
+__device__ inline uint32_t ksdf_odd_surfaces(KsdfArgs P, double d, double dn) {
+  uint32_t bits = 0;
+  for (int j = 0; j < P.k; ++j) {
+    const double x = -P.beta * (d + P.off[j]), xn = -P.beta * (dn + P.off[j]);
+    const float en = P.factor ? expf(-(float)(P.beta * dn)) * P.cinv[1][j] : expf((float)xn);
+    if (x > kKsdfDeep) bits |= 1u << j;
+    else if (xn > kKsdfDeep || (isnan(d) && isinf(en))) bits |= 0x10000u << j;
+  }
+  return bits;
 }
 
 // NeuS interval weights of one surface, w_i = a_i prod_{l<i} (1 - a_l), for lane
@@ -511,7 +526,8 @@ __device__ inline void ksdf_interval(double beta, double d, double dn, float& q,
 // stay a normal float.
 template <int NS>
 __device__ inline void ksdf_weights(KsdfArgs P, int j, const double (&dn)[NS],
-                                    const float (&q)[NS], const float (&G)[NS], float (&w)[NS], int l) {
+                                    const float (&q)[NS], const float (&G)[NS], const uint32_t* odd,
+                                    float (&w)[NS], int l) {
 #pragma clang fp contract(fast)
   float a[NS], pass = 1.f;
   const float c = P.cexp[j];
@@ -522,10 +538,16 @@ __device__ inline void ksdf_weights(KsdfArgs P, int j, const double (&dn)[NS],
     for (int sl = 0; sl < NS; ++sl) a[sl] = q[sl] > 0.f ? 1.f + ksdf_exp(P.beta * (dn[sl] + P.off[j])) : 1.f;
   }
 #pragma unroll
-  for (int sl = 0; sl < NS; ++sl) {
-    a[sl] = q[sl] * __builtin_amdgcn_rcpf(a[sl]);
-    pass *= 1.f - a[sl];
+  for (int sl = 0; sl < NS; ++sl) a[sl] = q[sl] * __builtin_amdgcn_rcpf(a[sl]);
+  if (odd) {   // uniform
+#pragma unroll
+    for (int sl = 0; sl < NS; ++sl) {
+      const uint32_t bits = odd[NS * l + sl] >> j;
+      a[sl] = bits & 1u ? 0.f : bits & 0x10000u ? 1.f : a[sl];
+    }
   }
+#pragma unroll
+  for (int sl = 0; sl < NS; ++sl) pass *= 1.f - a[sl];
   float T = ksdf_hbelow(1.f, ksdf_hscan_mul(pass), l);
 #pragma unroll
   for (int sl = 0; sl < NS; ++sl) {
@@ -597,8 +619,16 @@ __device__ inline void ksdf_cdf(KsdfArgs P, KsdfLds<NSL>& L, int round, double b
 // Appearance of the ray's samples, per-surface quadrature and fixed-order
 // blend; lanes 0, 16, 8, 24 hold r, g, b and alpha.
 template <int NS, int NSL>
-__device__ inline float ksdf_blend(KsdfArgs P, const KsdfLds<NSL>& L, const KsdfRays& S, int slot, int N, int l,
+__device__ inline float ksdf_blend(KsdfArgs P, KsdfLds<NSL>& L, const KsdfRays& S, int slot, int N, int l,
                                    int h, int comp, int64_t ray, int64_t total, bool live, float* __restrict__ layers) {
+  bool odd = false;
+#pragma unroll
+  for (int sl = 0; sl < NS; ++sl) odd = odd || !(L.d[min(32 * sl + l, N - 1)] > P.deep);   // true for NaN
+  odd = __any(odd);
+  if (odd) {
+    for (int i = l; i < 32 * NS; i += 32) L.odd[i] = ksdf_odd_surfaces(ksdf_args(), L.d[min(i, N - 1)], L.d[min(i + 1, N - 1)]);
+    ksdf_wave_sync();
+  }
   float4 app[NS];
   float q[NS], G[NS], aw[NS];
   double d[NS];
@@ -623,7 +653,7 @@ __device__ inline float ksdf_blend(KsdfArgs P, const KsdfLds<NSL>& L, const Ksdf
   for (int j = 0; j < P.k; ++j) {
 #pragma clang fp contract(fast)
     float w[NS];
-    ksdf_weights<NS>(P, j, d, q, G, w, l);
+    ksdf_weights<NS>(P, j, d, q, G, odd ? L.odd : nullptr, w, l);
     float pr = 0.f, pg = 0.f, pb = 0.f, pa = 0.f;
 #pragma unroll
     for (int sl = 0; sl < NS; ++sl) {

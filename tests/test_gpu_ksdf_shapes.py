@@ -115,3 +115,83 @@ def test_ksdf_merged_samples(torch_cuda, k, n, m, steps, occ_res, sizes):  # noq
         t, d = K.merge_sorted(t, d, tn, sdf_along(tn))
     low, high = (np.sort(np.concatenate(b, 1), 1) for b in bounds)
     assert (new >= low - 1e-12).all() and (new <= high + 1e-12).all()
+
+
+def _everywhere(torch, P, field, opts):
+    return P.ksdf_occupancy(field, opts).fill_(-1)
+
+
+def _at_samples(g, oopts, o, v, t):
+    """Layers [k, rays, 4] in 64 bits at the samples t that a render took (FP32 importance weights need not put them where
+    the oracle's would), and how many ends of intervals lie where the plain quotient does not hold.  Next to a NaN the opacity
+    is 0, but 1 from a NaN to a point so far inside that Phi is 0 in FP32 (that of the main surface, where offsets are a
+    factor); it is 0 from and 1 to a point where Phi is 0 in FP64."""
+    out, odd = [], 0
+    factor = all(abs(oopts.beta * off) <= 60.0 for off in oopts.offsets)
+    p = (o[:, None, :] + t[..., None] * v[:, None, :]).reshape(-1, 3)
+    with np.errstate(all="ignore"):
+        d = K.sdf_at(g, p).reshape(t.shape)
+        app = K.rgba_at(g, p).reshape(*t.shape, 4)[:, :-1]
+        nrm = K.sdf_normals(g, p).reshape(*t.shape, 3)[:, :-1]
+        vdn = np.nan_to_num(np.abs((nrm * v[:, None, :]).sum(-1)), nan=0.0)
+        aw = (2.0 / (1.0 + np.exp(-10.0 * vdn)) - 1.0) * app[..., 3]
+        for off in oopts.offsets:
+            x, y = -oopts.beta * (d[:, :-1] + off), -oopts.beta * (d[:, 1:] + off)
+            phi, nxt = 1.0 / (1.0 + np.exp(x)), 1.0 / (1.0 + np.exp(y))
+            a = np.where(phi > 0, np.maximum((phi - nxt) / phi, 0.0), 0.0)
+            a = np.where(np.isnan(x) | np.isnan(y), 0.0, a)
+            inside = np.float32(-oopts.beta * (d[:, 1:] + (0.0 if factor else off)))
+            a = np.where(np.isnan(x) & (np.isinf(np.exp(inside)) | (y > 709.79)), 1.0, a)
+            odd += int((np.isnan(x) | (x > 709.0)).sum())
+            w = np.cumprod(np.concatenate([np.ones((len(a), 1)), 1.0 - a[:, :-1]], 1), 1) * a
+            out.append(np.concatenate([(w[..., None] * app[..., :3]).sum(1), (w * aw).sum(1)[:, None]], 1))
+    return np.stack(out), odd
+
+
+def _check_layers(lay, want):
+    """Colours of all rays; opacities of all but the few rays that run along a cell face, where the normal jumps."""
+    err = np.abs(lay - want)
+    assert err[..., :3].max() <= TOL, err[..., :3].max()
+    assert (err[..., 3] > TOL).mean() <= 0.002, err[..., 3].max()
+
+
+@pytest.mark.parametrize("k,offsets,far,n,m", [
+    (1, [0.0], 0.25, 64, 32), (4, [-0.3, 0.0, 0.1, 0.4], 0.25, 64, 64), (3, None, 0.3, 33, 6), (16, None, 0.2, 16, 8)])
+def test_ksdf_from_far_inside(torch_cuda, k, offsets, far, n, m):  # noqa: F811
+    """A camera near the middle of the object, every voxel taken for occupied: where Phi is 0 in FP64 there is no opacity,
+    however the distance falls along the ray."""
+    torch = torch_cuda
+    g = S.ksdf_grids(71, 48, 24)
+    P, field, opts, oopts = _setup(torch, g, k, 64, offsets=offsets, n_uniform=n, n_importance=m, march_steps=512)
+    cams = S.ring_cameras(72, 2, [(31, 20), (16, 24)], far)
+    say(f"[gpu] ksdf from inside k={k} far={far}")
+    got, lay, smp = (x.cpu().numpy() for x in P.ksdf_render(field, opts, _everywhere(torch, P, field, opts), P.Views(cams),
+                                                           layers=True, samples=True))
+    o, v = (np.concatenate(x) for x in zip(*[K.camera_rays(c) for c in cams]))
+    want, odd = _at_samples(g, oopts, o, v, smp)
+    assert odd > 50
+    _check_layers(lay, want)
+    col, T = np.zeros((len(o), 3)), np.ones(len(o))
+    for C in lay.astype(np.float64):
+        col += (T * C[:, 3])[:, None] * C[:, :3]
+        T *= 1.0 - C[:, 3]
+    assert np.abs(got - np.concatenate([col, 1.0 - T[:, None]], 1)).max() <= TOL
+
+
+@pytest.mark.parametrize("bad", [np.nan, -np.inf, -1e30, 1e30])
+@pytest.mark.parametrize("k,offsets,n,m", [(3, None, 33, 6), (4, [-0.3, 0.0, 0.1, 0.4], 64, 64), (7, None, 64, 32)])
+def test_ksdf_fields_with_odd_values(torch_cuda, bad, k, offsets, n, m):  # noqa: F811
+    """Infinite, huge and NaN values in the distance grid."""
+    torch = torch_cuda
+    g = S.ksdf_grids(71, 48, 24)
+    g.sdf.reshape(-1)[np.random.default_rng([73, k]).integers(0, g.sdf.size, 400)] = bad
+    P, field, opts, oopts = _setup(torch, g, k, 64, offsets=offsets, n_uniform=n, n_importance=m, march_steps=512)
+    cam = S.ring_cameras(72, 1, [(48, 40)], 2.0)[0]
+    say(f"[gpu] ksdf fields with {bad} k={k}")
+    _, lay, smp = (x.cpu().numpy() for x in P.ksdf_render(field, opts, _everywhere(torch, P, field, opts), P.Views([cam]),
+                                                         layers=True, samples=True))
+    o, v = K.camera_rays(cam)
+    live = (smp[:, 0] >= 0) & np.isfinite(smp).all(1)
+    want, odd = _at_samples(g, oopts, o[live], v[live], smp[live])
+    assert live.sum() > 500 and (bad > 0 or odd > 100)
+    _check_layers(lay[:, live], want)
