@@ -62,7 +62,7 @@ struct WsLayout {
   size_t bin_view;   // int32 [raster bin tiles of all views]: owning view
   size_t proj;       // ProjVert [n_views][sum n_vert]
   size_t recs;       // GroupRec [n_views][groups of a view]
-  size_t parts;      // u64 per part of the list: words taken, entries << 32
+  size_t parts;      // u64 per part of the list: words asked of it (a caller's capacity: of the one part, and entries)
   size_t list;       // u32: the groups' runs (tile tables, triangle ids, back faces' entries)
   int64_t n_tiles16, n_tiles_bin, n_bins, n_groups;   // groups: of all views
   int reps;          // triangles per thread of a group's block

@@ -30,32 +30,31 @@ __host__ __device__ inline int macro_shift(int x0, int y0, int x1, int y1, int m
   return s;
 }
 
-// The list's parts: `words` each, and `entries` (triangles in tiles) that their runs may have.
+// The list's parts: `words` each.  A caller's capacity bounds the entries (triangles in tiles) of all runs, in one
+// part; ~0: no bound.
 struct ListRoom {
   uint32_t words, entries;
   int32_t parts;
 };
 
 // Room for a run of `need` words with `entries` entries: its first word in the list, or kGroupNoRun.  A
-// part's counter holds the words taken from it and, << 32, their entries: load(p) reads it, add(p, n) adds n
-// modulo 2^64 and returns what it held before.  The own part's counter is added to at once (one round trip to
-// memory); another part's is looked at first, as it is only tried when the own one is full.  What found no
-// room is taken off again, so that later and smaller runs find what is left and a counter never passes its
-// part by more than one run for each block that is running (2,048 of at most 135 k words: below 2^32 - kListWords):
-// it cannot wrap and hand out words that are taken.
-template <class Load, class Add>
-__host__ __device__ inline uint32_t reserve_run(uint32_t need, uint32_t entries, ListRoom room, uint32_t own, Load load, Add add) {
-  if (need > room.words || entries > room.entries) return kGroupNoRun;
-  const uint64_t mine = ((uint64_t)entries << 32) | need;
-  const auto fits = [&](uint64_t taken) {
-    return (uint32_t)taken <= room.words - need && (uint32_t)(taken >> 32) <= room.entries - entries;
-  };
+// part's counter holds the words asked of it: load(p) reads it, add(p, n) adds n and returns what it held
+// before; count(n) does so with the entries.  Counters only grow, and in 64 bits: what found no room stays
+// added (taken off again, it would be handed out twice, for what other groups got in the meantime lies above
+// it), and no counter can wrap.  The own part's counter is added to at once.  A look before that costs as much
+// again, as all groups' come to eight lines of memory (metric scene 365 -> 979 us); so a run that
+// finds no room there also uses up what is left of that part, less than itself.  Another part's is looked at first, so
+// that its room stays for runs that fit.
+template <class Load, class Add, class Count>
+__host__ __device__ inline uint32_t reserve_run(uint32_t need, uint32_t entries, ListRoom room, uint32_t own, Load load, Add add,
+                                                Count count) {
+  if (need > room.words) return kGroupNoRun;
+  if (room.entries != ~0u && count(entries) + entries > (uint64_t)room.entries) return kGroupNoRun;
   for (uint32_t q = 0; q < (uint32_t)room.parts; ++q) {
     const uint32_t p = (own + q) % (uint32_t)room.parts;
-    if (q > 0 && !fits(load(p))) continue;
-    const uint64_t taken = add(p, mine);
-    if (fits(taken)) return p * room.words + (uint32_t)taken;
-    add(p, 0ull - mine);
+    if (q > 0 && load(p) > room.words - need) continue;
+    const uint64_t from = add(p, need);
+    if (from <= room.words - need) return p * room.words + (uint32_t)from;
   }
   return kGroupNoRun;
 }

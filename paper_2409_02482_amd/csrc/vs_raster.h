@@ -343,7 +343,8 @@ __global__ void __launch_bounds__(256) k_bin(const vs_view* __restrict__ views, 
     const uint32_t base = reserve_run(
         need, entries, room, blockIdx.x,
         [&](uint32_t p) { return __hip_atomic_load(parts + p * kPartApart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); },
-        [&](uint32_t p, uint64_t words) { return atomicAdd(parts + p * kPartApart, (unsigned long long)words); });
+        [&](uint32_t p, uint64_t words) { return atomicAdd(parts + p * kPartApart, (unsigned long long)words); },
+        [&](uint64_t more) { return atomicAdd(parts + kPartApart, (unsigned long long)more); });   // one part then: the second counter
     run_base = base;
     out.tx0 = (uint16_t)rx; out.ty0 = (uint16_t)ry; out.tw = (uint16_t)tw; out.th = (uint16_t)th;
     out.base = base;

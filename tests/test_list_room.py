@@ -76,13 +76,14 @@ int main(int, char** a) {
         groups.push_back({n + 1 + entries, entries, (uint32_t)own});
       }
   std::shuffle(groups.begin(), groups.end(), std::mt19937(seed));
-  uint64_t counters[vs::kParts] = {};
+  uint64_t counters[vs::kParts] = {}, counted = 0;
   size_t without = 0;
   uint64_t words = 0;
   for (auto& g : groups) {
     words += g.need;
     without += vs::kGroupNoRun == vs::reserve_run(g.need, g.entries, w.room, g.own, [&](uint32_t p) { return counters[p]; },
-                                                  [&](uint32_t p, uint64_t n) { const uint64_t c = counters[p]; counters[p] += n; return c; });
+                                                  [&](uint32_t p, uint64_t n) { const uint64_t c = counters[p]; counters[p] += n; return c; },
+                                                  [&](uint64_t n) { counted += n; return counted - n; });
   }
   printf("%zu %zu %llu %llu\n", groups.size(), without, (unsigned long long)pairs, (unsigned long long)words);
 }
