@@ -185,3 +185,16 @@ def test_many_groups_in_random_order(k, n_lat, size, bin):
     vis, ws = P.raster(layers, views, bin=bin, count_fragments=True)
     st = P.read_status(ws)
     assert torch.equal(vis, direct) and st["fragments"] == frags and st["bin_overflow"] == 0
+
+
+@pytest.mark.parametrize("bin,capacity", [(64, 3000), (64, 300000), (16, 100000), (8, 1000000)])
+def test_many_groups_at_once_without_list_space(bin, capacity):
+    """Hundreds of groups ask for room at the same time and most find none: the others' runs stay theirs."""
+    import torch
+    import paper_2409_02482_amd as P
+    say(f"[gpu] 24 views, bin {bin}, capacity {capacity}")
+    layers = P.Layers(S.displaced_shells(2, 5, 40, 80))
+    views = P.Views(S.ring_cameras(5, 24, [(640, 500)] * 24))
+    vis, ws = P.raster(layers, views, bin=bin, list_capacity=capacity)
+    assert P.read_status(ws)["bin_overflow"] > 0
+    assert torch.equal(vis, P.raster(layers, views, direct=True)[0])
